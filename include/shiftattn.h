@@ -272,6 +272,10 @@ int sp_debug_validate_hints(const int32_t *cu_seqlens, const int32_t *lens, int3
  * sp_debug_set_tuning — override of an internal launch parameter for the CALLING THREAD (the
  * workspace-size helpers and the attention calls made by that thread see it; other threads keep
  * their own values), for tuning sweeps and tests.  Keys:
+ *   "decode_form"   how a decode call (and the short-chunk path) divides the keys: 0 (built-in choice), 1 (splits
+ *                   of one wave), 2 (workgroups with equal shares of the batch's keys; batches of up to 512
+ *                   sequences), 3 (splits of a workgroup where one round of them holds the batch).  The three
+ *                   keys below set parameters of form 1 and select it.
  *   "decode_chunk"  keys per decode split: 0 (built-in heuristic) or a multiple of 32 in
  *                   [128, 1024].  Changes what sp_attn_decode_workspace_size returns.
  *   "decode_ring"   32-key blocks a decode wave keeps in its LDS ring (one computed on, the

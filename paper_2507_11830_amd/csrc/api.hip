@@ -270,6 +270,11 @@ int sp_debug_set_tuning(const char *key, int32_t value) {
     set_decode_ring(value);
     return SP_OK;
   }
+  if (!strcmp(key, "decode_form")) {
+    if (value < 0 || value > 3) return fail(SP_ERR_UNSUPPORTED, "decode_form=%d (0..3)", value);
+    set_decode_form(value);
+    return SP_OK;
+  }
   if (!strcmp(key, "decode_fuse")) {
     if (value < 0 || value > 2) return fail(SP_ERR_UNSUPPORTED, "decode_fuse=%d (0, 1 or 2)", value);
     set_decode_fuse(value);

@@ -20,29 +20,12 @@
 #include <atomic>
 #include <mutex>
 
-#include "attn_tile.h"
+#include "decode_block.h"
 
 namespace sp {
 
 constexpr int kDecMinChunk = 128;
 constexpr int kDecMaxChunk = 1024;  // <= 64 pages per wave: one lane holds each page id
-
-struct DecodeArgs {
-  const char *k_pages, *v_pages, *q;
-  const char *k_new, *v_new;  // APPEND kernels: this step's K/V rows, bf16 [tokens][Hkv][D] (one token per sequence unless MQ)
-  const int32_t *seq_lens, *block_table;
-  const int32_t *cu_q, *ctx_lens;  // MQ kernels: query-token prefix sums [batch + 1], cached lengths [batch]
-  float *part_o;   // [row][nsplit][D], row = token * Hq + head (one token per sequence unless MQ)
-  float *part_ml;  // [row][nsplit][2]  (m in log2 units, l)
-  int max_pages, num_pages, Hq, Hkv, group, geff, n_hgroups, chunk, nsplit;
-  int q_cap;  // MQ kernels: query tokens per tile (32 / geff)
-  int route_cap;  // MQ kernels: 0, or (mixed batches) only sequences with at most this many query tokens are
-                  // served, and the partials are indexed [sequence][route_cap tokens][head] instead of by token row
-  int32_t *arrive;  // FUSE kernels: one arrival counter per (sequence, head group), zero between launches
-  char *out;        // FUSE kernels: bf16 [batch][Hq][D]
-  float sl2e;
-  float tau;  // lazy-rescale threshold in raw score units (8 / sl2e)
-};
 
 static thread_local int g_chunk_override = 0;  // tuning hooks of the calling thread (sp_debug_set_tuning), 0 = heuristic
 static thread_local int g_ring_override = 0;
@@ -84,24 +67,6 @@ size_t decode_workspace_bytes(int batch, int max_seq_len, int num_q_heads, int h
   int chunk = pick_chunk(batch, num_q_heads, max_seq_len);
   size_t nsplit = (size_t)(max_seq_len + chunk - 1) / chunk;
   return (size_t)batch * num_q_heads * nsplit * (head_dim + 2) * sizeof(float);
-}
-
-// Orders a wave's own LDS writes before its later LDS reads without a workgroup barrier: the
-// hardware runs one wave's LDS operations in order, so only the compiler has to be stopped from
-// moving them across this point.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// s_waitcnt on the vector-memory counter only (the other counters are not named, so they are
-// left alone).  The "memory" clobber keeps the compiler from moving LDS reads of the awaited
-// block above it.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // Fused combine (FUSE forms of the split kernel; OFF by default, tuning key "decode_fuse").  Every
@@ -501,101 +466,13 @@ __global__ __launch_bounds__(64, NT > 1 ? 1 : 2) void decode_split_kernel(Decode
       wave_lds_fence();
     }
 
-    f32x16 sacc[NT], sacc1[NT];  // two accumulators per tile halve the dependent MFMA chain a lone wave sits through
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[nt][r] = sacc1[nt][r] = 0.f;
-#pragma unroll
-    for (int s = 0; s < G::kDSteps; s += 2) {
-      bf16x8 kop0 = *(const lds_bf16x8 *)(sbk + kofs[s]);
-      bf16x8 kop1 = *(const lds_bf16x8 *)(sbk + kofs[s + 1]);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        sacc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop0, qreg[nt][s], sacc[nt], 0, 0, 0);
-        sacc1[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop1, qreg[nt][s + 1], sacc1[nt], 0, 0, 0);
-      }
-    }
-    bf16x8 pop[NT][2];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[nt][r] += sacc1[nt][r];
-      if (MQ) {
-        if (base + 32 > min(lim_min, kv1)) {  // the block reaches into the chunk: per-column causal limit
-          const int lim = min(lim_col[nt], kv1);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            int kv = base + 8 * (r >> 2) + 4 * half + (r & 3);
-            if (kv >= lim) sacc[nt][r] = -INFINITY;
+    attend_block<D, MQ, NT>(
+        sbk, sbv, kofs, vofs, qreg, o, m, l, base, kv1, lim_min, lim_col, half, a.sl2e, a.tau, L <= 256, [&]() __attribute__((always_inline)) {
+          if (VS) {  // behind V(i) in the queue: K(i+1) if there is one
+            if (i + 1 < nb) wait_vmcnt<NI>();
+            else wait_vmcnt<0>();
           }
-        }
-      } else if (base + 32 > kv1) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int kv = base + 8 * (r >> 2) + 4 * half + (r & 3);
-          if (kv >= kv1) sacc[nt][r] = -INFINITY;
-        }
-      }
-      float mx = sacc[nt][0];
-#pragma unroll
-      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[nt][r]);
-      mx = fmaxf(mx, other_half(mx));
-      // The running max only moves when some column's block max exceeds it by more than 2^8 in
-      // the exponent (tau); otherwise weights are taken against the stale max (bounded by 2^8,
-      // harmless in fp32/bf16) and the O accumulators need no rescale.
-      if (__builtin_amdgcn_ballot_w64(mx > m[nt] + a.tau) != 0) {  // wave-uniform, rare after the first block
-        const float m_new = fmaxf(m[nt], mx);
-        const float alpha = __builtin_amdgcn_exp2f((m[nt] - m_new) * a.sl2e);
-        m[nt] = m_new;
-        l[nt] *= alpha;
-#pragma unroll
-        for (int db = 0; db < G::kDBlocks; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[nt][db][r] *= alpha;
-      }
-      const float msc = m[nt] * a.sl2e;
-      float lsum = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[nt][r], a.sl2e, -msc));
-        sacc[nt][r] = p;
-        lsum += p;
-      }
-      l[nt] += lsum;
-      pop[nt][0] = pack8(sacc[nt], 0);
-      pop[nt][1] = pack8(sacc[nt], 8);
-    }
-    if (VS) {  // behind V(i) in the queue: K(i+1) if there is one
-      if (i + 1 < nb) wait_vmcnt<NI>();
-      else wait_vmcnt<0>();
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int db = 0; db < G::kDBlocks; ++db) {
-        bf16x8 vop = lds_read_vt(sbv + vofs[db] + 16 * ks * ROWB, ROWB);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          o[nt][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, pop[nt][ks], o[nt][db], 0, 0, 0);
-      }
-    if (L <= 256) {  // short sequences: weights as hi + lo, so the bf16 rounding of P (which only averages out over many keys) stays out of the tolerance
-      bf16x8 plo[NT][2];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        plo[nt][0] = pack8_residual(sacc[nt], 0, pop[nt][0]);
-        plo[nt][1] = pack8_residual(sacc[nt], 8, pop[nt][1]);
-      }
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int db = 0; db < G::kDBlocks; ++db) {
-          bf16x8 vop = lds_read_vt(sbv + vofs[db] + 16 * ks * ROWB, ROWB);
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            o[nt][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, plo[nt][ks], o[nt][db], 0, 0, 0);
-        }
-    }
+        });
     if (VS) {
       // Every read of V(i) and of K(i) has been consumed by a multiply above (the scheduling
       // barrier keeps the requests below them): their bytes may be replaced.
@@ -882,6 +759,14 @@ static void set_head_groups(DecodeArgs &a, int num_q_heads, int num_kv_heads) {
   a.q_cap = 32 / a.geff;
 }
 
+static thread_local int g_form = 0;
+void set_decode_form(int form) { g_form = form; }
+// Workgroup forms (attn_decode_stream.hip) unless the calling thread asks for one-wave splits or for one of their
+// launch parameters.
+static bool stream_allowed() {
+  return g_form != 1 && g_chunk_override == 0 && g_ring_override == 0 && g_fuse_mode != 2;
+}
+
 // ---- short query chunks (sp_attn_prefill with a few tokens per sequence) on the split kernel
 // A chunk qualifies when its tokens x the heads of a tile fit one 32-column tile of a wave, or
 // two where that measured faster than the prefill kernel: with at most four heads per KV head
@@ -966,6 +851,11 @@ int launch_decode_multi(const sp_cache_desc &c, const void *k_new, const void *v
   a.num_pages = c.num_pages;
   a.sl2e = scale * 1.44269504088896340736f;
   a.tau = 8.0f / a.sl2e;
+  if (stream_allowed()) {
+    a.out = (char *)out;
+    const int rc = launch_decode_stream(a, batch, max_q_len, tiles, max_kv_len, c.head_dim, workspace, workspace_bytes, g_form, stream);
+    if (rc != 1) return rc;
+  }
   a.chunk = pick_chunk(batch, num_q_heads, max_kv_len, max_q_len);
   a.nsplit = (max_kv_len + a.chunk - 1) / a.chunk;
   a.part_o = (float *)workspace;
@@ -995,7 +885,6 @@ int launch_decode(const sp_cache_desc &c, const void *k_new, const void *v_new, 
                   const int32_t *seq_lens, const int32_t *block_table, int batch, int max_pages,
                   int max_seq_len, int num_q_heads, float scale, void *workspace, size_t workspace_bytes,
                   hipStream_t stream) {
-  (void)workspace_bytes;
   DecodeArgs a;
   a.k_pages = (const char *)c.k_pages;
   a.v_pages = (const char *)c.v_pages;
@@ -1016,6 +905,11 @@ int launch_decode(const sp_cache_desc &c, const void *k_new, const void *v_new, 
   if (max_seq_len <= 0) {
     // every sequence is empty: the combine kernel alone writes the zero rows
     return launch_combine(nullptr, nullptr, out, (long)batch * num_q_heads, 1, c.head_dim, stream);
+  }
+  if (stream_allowed()) {
+    a.out = (char *)out;
+    const int rc = launch_decode_stream(a, batch, 1, 1, max_seq_len, c.head_dim, workspace, workspace_bytes, g_form, stream);
+    if (rc != 1) return rc;
   }
   a.chunk = pick_chunk(batch, num_q_heads, max_seq_len);
   a.nsplit = (max_seq_len + a.chunk - 1) / a.chunk;

@@ -32,6 +32,8 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) float lds_float;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
 
 // V^T operand for one (32-channel block, 16-key step): two transposing 8-byte reads.  `p` is
 // this lane's address for the first of its 4 consecutive key rows (lane n of a 16-lane group
