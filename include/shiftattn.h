@@ -106,8 +106,10 @@ int sp_kv_append(const sp_cache_desc *cache, const void *k_new, const void *v_ne
  *                   sp_attn_prefill_workspace_size(...) bytes the library may cut long key
  *                   ranges into pieces computed by separate workgroups and merged by a
  *                   log-sum-exp combine pass, which it does for batches of few query tokens on
- *                   long cached prefixes; with NULL / 0 (or less than that) it uses fewer
- *                   pieces or none.  The result is the same up to fp32 summation order.
+ *                   long cached prefixes, and for batches of a few hundred 256-row query tiles
+ *                   whose key ranges may differ a lot (only the ranges that the lengths on the
+ *                   device show to be long are cut then); with NULL / 0 (or less than that) it
+ *                   uses fewer pieces or none.  The result is the same up to fp32 summation order.
  *                   Batches whose chunks are all a few tokens long (max_q_len times the query
  *                   heads per KV head <= 32, for some shapes <= 64: the verification step of
  *                   speculative decoding) are served, when the workspace allows, by the decode
@@ -296,6 +298,10 @@ int sp_debug_validate_hints(const int32_t *cu_seqlens, const int32_t *lens, int3
  *                   tiles), 2 (same query columns, alternate key tiles, merged at the end).
  *                   Both give the same result up to fp32 summation order.  Launches that cut
  *                   key ranges into pieces always take form 2.
+ *   "prefill_cut"   whether the query tiles with long key ranges are cut by the lengths found on the device: 0
+ *                   (built-in choice from the hints), 1 (never), 2 (wherever the batch, up to 256 sequences, and
+ *                   the workspace allow it; not together with the two keys above or the next).  Changes what
+ *                   sp_attn_prefill_workspace_size returns.
  *   "prefill_order" which work item (sequence, query tile) a prefill workgroup takes: 0 (built-in
  *                   choice), 1 (by launch index: last query tiles of all sequences first), 2 (the
  *                   workgroup with the r-th launch index takes the r-th heaviest item; batches of

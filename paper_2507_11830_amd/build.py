@@ -90,8 +90,8 @@ def loop_spills(asm: str) -> dict:
 
 
 def _check_loop_spills(src: str, asm: str) -> None:
-    """The one-workgroup-per-query-tile prefill kernels (the C5a path) must keep their loops free of
-    spill code; the split forms are allowed the few reloads of their rarely taken short-row copy."""
+    """The 256-column prefill kernels (whole query tiles and the form that cuts long ones) must keep their loops
+    free of spill code; the 128-column forms are allowed the few reloads of their rarely taken short-row copy."""
     for kern, n in loop_spills(asm).items():
         if "prefill_kernel" not in kern:
             continue
@@ -105,7 +105,12 @@ def _compile(src: str, obj_dir: str = OBJ_DIR, extra_flags=(), product: bool = T
     base = os.path.basename(src).replace(".hip", "")
     obj = os.path.join(obj_dir, base + ".o")
     with open(src) as f:
-        uses_lds_dma = "global_load_lds" in f.read()
+        text = f.read()
+    for inc in re.findall(r'#include "(\w+\.h)"', text):  # kernels may live in a shared header
+        if os.path.exists(os.path.join(CSRC, inc)):
+            with open(os.path.join(CSRC, inc)) as f:
+                text += f.read()
+    uses_lds_dma = "global_load_lds" in text
     extra = ["-save-temps=obj"] if uses_lds_dma else []
     r = subprocess.run([HIPCC, *FLAGS, *extra_flags, *extra, "-c", src, "-o", obj], capture_output=True, text=True)
     if r.returncode != 0:
