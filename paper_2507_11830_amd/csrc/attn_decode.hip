@@ -810,6 +810,39 @@ size_t decode_routed_workspace_bytes(int batch, int max_kv_len, int num_q_heads,
   return (size_t)batch * a.q_cap * num_q_heads * nsplit * (head_dim + 2) * sizeof(float);
 }
 
+static void set_chunk_args(DecodeArgs &a, const sp_cache_desc &c, const void *k_new, const void *v_new, const void *q,
+                           const int32_t *cu_q, const int32_t *ctx_lens, const int32_t *block_table, int max_pages, float scale) {
+  a.k_pages = (const char *)c.k_pages;
+  a.v_pages = (const char *)c.v_pages;
+  a.k_new = (const char *)k_new;  // both NULL: the chunk's rows are in the cache already
+  a.v_new = (const char *)v_new;
+  a.q = (const char *)q;
+  a.seq_lens = nullptr;
+  a.arrive = nullptr;
+  a.out = nullptr;
+  a.cu_q = cu_q;
+  a.ctx_lens = ctx_lens;
+  a.block_table = block_table;
+  a.max_pages = max_pages;
+  a.num_pages = c.num_pages;
+  a.sl2e = scale * 1.44269504088896340736f;
+  a.tau = 8.0f / a.sl2e;
+}
+
+bool plan_decode_routed(DecodeArgs &a, const sp_cache_desc &c, const void *q, void *out, const int32_t *cu_q,
+                        const int32_t *ctx_lens, const int32_t *block_table, int batch, int max_pages, int max_kv_len,
+                        int num_q_heads, float scale, void *workspace, size_t workspace_bytes, int *shares, int *pieces) {
+  if (!stream_allowed() || g_form == 3 || batch > kMaxShareSeqs) return false;
+  set_head_groups(a, num_q_heads, c.num_kv_heads);
+  a.route_cap = a.q_cap;
+  set_chunk_args(a, c, nullptr, nullptr, q, cu_q, ctx_lens, block_table, max_pages, scale);
+  a.out = (char *)out;
+  dim3 wgs;
+  if (plan_decode_stream(a, batch, a.q_cap, 1, max_kv_len, c.head_dim, workspace, workspace_bytes, 2, false, &wgs, pieces) || a.row_splits != 0) return false;
+  *shares = (int)wgs.x;
+  return true;
+}
+
 // Returns SP_OK after launching, or 1 when the shape or the workspace does not qualify (the caller
 // then runs the general prefill kernel).  routed: serve only the sequences with at most
 // decode_route_cap query tokens (the caller's other kernel serves the rest).
@@ -836,21 +869,7 @@ int launch_decode_multi(const sp_cache_desc &c, const void *k_new, const void *v
     prows = (long)total_q * num_q_heads;
   }
   if (need == 0 || !workspace || workspace_bytes < need) return 1;
-  a.k_pages = (const char *)c.k_pages;
-  a.v_pages = (const char *)c.v_pages;
-  a.k_new = (const char *)k_new;  // both NULL: the chunk's rows are in the cache already
-  a.v_new = (const char *)v_new;
-  a.q = (const char *)q;
-  a.seq_lens = nullptr;
-  a.arrive = nullptr;
-  a.out = nullptr;
-  a.cu_q = cu_q;
-  a.ctx_lens = ctx_lens;
-  a.block_table = block_table;
-  a.max_pages = max_pages;
-  a.num_pages = c.num_pages;
-  a.sl2e = scale * 1.44269504088896340736f;
-  a.tau = 8.0f / a.sl2e;
+  set_chunk_args(a, c, k_new, v_new, q, cu_q, ctx_lens, block_table, max_pages, scale);
   if (stream_allowed()) {
     a.out = (char *)out;
     const int rc = launch_decode_stream(a, batch, max_q_len, tiles, max_kv_len, c.head_dim, workspace, workspace_bytes, g_form, stream);

@@ -22,6 +22,7 @@
 // matrix phases carry no address arithmetic.  The matrix pipe is then busy in about 85 % of the
 // cycles a CU is busy, and what limits the kernel beyond that is the clock the chip grants under
 // this load (it is power-limited from the first tile on).
+#include "decode_block.h"
 #include "prefill_tile.h"
 
 namespace sp {
@@ -242,6 +243,21 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
     }
   }
   const bool split = small_grid || kvs > 1;
+  // Mixed batch: both kinds of workgroups in one launch where the prefill ones take items by rank and the cached keys are
+  // up to kMixedBytes, all sequences taken as long as the longest.  Beyond that the decode half alone saturates HBM
+  // with all CUs, and starting on a part of them costs more than it hides (0.66 GB of keys: 148 us as two launches, 157 as one;
+  // 1.3 GB: 234 and 250; 0.17 GB: 51.6 and 45.9; smaller shares for the CUs that come late: the same there, and 8q/1kv
+  // batches of 30 MB 21 -> 25 us).
+  constexpr long kMixedBytes = 640L << 20;
+  if (a.route_cap > 0 && (long)batch * c.num_kv_heads * max_kv_len * c.head_dim * 4 <= kMixedBytes && a.ranked && a.cut_slots == 0 && kvs == 1 && g_split_mode == 0 && g_kv_splits == 0 && g_order_mode == 0) {
+    DecodeArgs d;
+    int shares, pieces;
+    if (plan_decode_routed(d, c, q, out, cu_q, ctx_lens, block_table, batch, max_pages, max_kv_len, num_q_heads, scale, workspace,
+                           workspace_bytes, &shares, &pieces)) {
+      const int rc = launch_mixed(a, d, shares, pieces, split, c.head_dim, batch, max_q_len, stream);
+      if (rc != 1) return rc;
+    }
+  }
   int rc = a.cut_slots > 0 ? launch_prefill_cut(a, c.head_dim, batch, max_q_len, stream)
            : c.head_dim == 128 ? launch_prefill_d<128>(a, split, batch, max_q_len, stream)
                              : launch_prefill_d<64>(a, split, batch, max_q_len, stream);

@@ -150,10 +150,22 @@ __device__ __forceinline__ void attend_block(const lds_char *sbk, const lds_char
   }
 }
 
+constexpr int kMaxShareSeqs = 512;  // longest batch of the equal-share decode (its rows' ends and lengths are held in LDS)
+
 // Equal-share decode.  a: everything but the workspace pointers and the split fields is set.  max_q: query tokens per
 // sequence at most, tiles: column tiles per wave.  Returns 1 without launching when the shape or the workspace
 // does not qualify.  form: 0 built-in choice, 2 equal shares, 3 fixed splits.
 int launch_decode_stream(DecodeArgs &a, int batch, int max_q, int tiles, int max_len, int head_dim, void *workspace,
                          size_t workspace_bytes, int form, hipStream_t stream);
+// Its parts: everything but the launches (returns 1 if launch_decode_stream would; alone = false: the workgroups run next
+// to prefill workgroups), and the merge of the partials of a plan with row_splits 0 over query chunks.
+int plan_decode_stream(DecodeArgs &a, int batch, int max_q, int tiles, int max_len, int head_dim, void *workspace,
+                       size_t workspace_bytes, int form, bool alone, dim3 *grid, int *pieces);
+void launch_decode_combine(const DecodeArgs &a, int max_pieces, int head_dim, hipStream_t stream);
+// Equal shares for the short sequences of a mixed batch (launch_decode_multi with routed = true): arguments, number of
+// shares and of partials per row.  False where they cannot be taken.
+bool plan_decode_routed(DecodeArgs &a, const sp_cache_desc &c, const void *q, void *out, const int32_t *cu_q,
+                        const int32_t *ctx_lens, const int32_t *block_table, int batch, int max_pages, int max_kv_len,
+                        int num_q_heads, float scale, void *workspace, size_t workspace_bytes, int *shares, int *pieces);
 
 }  // namespace sp

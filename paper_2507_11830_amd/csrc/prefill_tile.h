@@ -388,8 +388,10 @@ __device__ __forceinline__ bool ranked_item(const PrefillArgs &a, int tpt_shift,
 // CUT = true (with SPLIT = PART = false) is for batches of few rounds of workgroups whose items are of
 // different lengths: items longer than a CU's share of the launch are cut into pieces by the lengths found on
 // the device (ranked_item), and only those leave partials, for cut_combine_kernel.
-template <int D, int KVT, int PFD, bool SPLIT, bool PART, int CUT>
-__global__ __launch_bounds__(512, 2) void prefill_kernel(PrefillArgs a) {
+//
+// Args = MixedArgs (attn_mixed.hip): the launch also holds workgroups of another kernel, behind the prefill ones.
+template <int D, int KVT, int PFD, bool SPLIT, bool PART, int CUT, typename Args = PrefillArgs>
+__global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   using G = TileGeom<D>;
   using Z = SwzTile<D>;
   constexpr int COLS = SPLIT ? 128 : 256, KB = KVT / 32;
@@ -409,6 +411,12 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(PrefillArgs a) {
 #endif
 
   const int tid = threadIdx.x, lane = tid & 63;
+  if constexpr (!std::is_same<Args, PrefillArgs>::value) {
+    if (blockIdx.x >= a.first_other) {
+      a.template run_other<D>(smem, lane);
+      return;
+    }
+  }
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps branches on it scalar
   const int col = lane & 31, half = lane >> 5;
   const int grp = w >> 2;  // wave-uniform; waves w and w+4 share a SIMD: one wave of each group per SIMD
@@ -1153,21 +1161,14 @@ constexpr int KVT = 64, PFD = 4;
 template <int D>
 constexpr size_t kPrefillSmem = 4 * (size_t)KVT * D * 2;  // K[2] V[2], unpadded
 
-// Launches one prefill kernel instantiation with `cols` query columns per workgroup.
-inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, const PrefillArgs &a0, int batch,
-                      int max_q_len, hipStream_t stream) {
-  PrefillArgs a = a0;
+// Launch index space of `cols` query columns per workgroup; completes a.  SP_ERR_BAD_SHAPE if it exceeds the limits.
+inline int prefill_grid(PrefillArgs &a, int cols, int batch, int max_q_len, dim3 *grid) {
   int tpt = cols >> a.gshift;
   a.ntiles_x = (max_q_len + tpt - 1) / tpt;
-  if (!*attr_set) {  // benign if two threads race
-    hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return fail(SP_ERR_HIP, "prefill smem attribute: %s", hipGetErrorString(e));
-    *attr_set = true;
-  }
   long gx = (long)batch * a.n_hgroups;
   if (gx > 0x7fffffffL || a.ntiles_x > 65535)
     return fail(SP_ERR_BAD_SHAPE, "sp_attn_prefill: grid %ld x %d exceeds the launch limits", gx, a.ntiles_x);
-  dim3 grid((unsigned)gx, (unsigned)a.ntiles_x, (unsigned)a.kv_splits);
+  *grid = dim3((unsigned)gx, (unsigned)a.ntiles_x, (unsigned)a.kv_splits);
   if (a.ranked) {
     // Ranked workgroups take items by linear id, so the launch only needs as many workgroups as
     // there can be items: every sequence has at most q_len / tpt + 1 query tiles.  (The grid of
@@ -1177,8 +1178,27 @@ inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, cons
     const long items = (long)a.total_q / tpt + batch;
     const long wgs = items * a.n_hgroups * a.kv_splits + (a.cut_slots < kMostExtraPieces ? a.cut_slots : kMostExtraPieces);
     if (wgs > 0x7fffffffL) a.ranked = 0;  // workgroups are numbered in 32 bits
-    else grid = dim3((unsigned)wgs, 1, 1);
+    else *grid = dim3((unsigned)wgs, 1, 1);
   }
+  return SP_OK;
+}
+
+// Dynamic LDS of a kernel, asked for once.
+inline int grant_smem(const void *fn, bool *done, size_t smem) {
+  if (*done) return SP_OK;  // benign if two threads race
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  if (e != hipSuccess) return fail(SP_ERR_HIP, "prefill smem attribute: %s", hipGetErrorString(e));
+  *done = true;
+  return SP_OK;
+}
+
+// Launches one prefill kernel instantiation with `cols` query columns per workgroup.
+inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, const PrefillArgs &a0, int batch,
+                      int max_q_len, hipStream_t stream) {
+  PrefillArgs a = a0;
+  dim3 grid;
+  if (int rc = prefill_grid(a, cols, batch, max_q_len, &grid)) return rc;
+  if (int rc = grant_smem((const void *)fn, attr_set, smem)) return rc;
   hipLaunchKernelGGL(fn, grid, dim3(512), smem, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SP_ERR_HIP, "prefill launch: %s", hipGetErrorString(e));
@@ -1187,5 +1207,8 @@ inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, cons
 
 // attn_prefill_cut.hip: the CUT form and its combine pass.
 int launch_prefill_cut(const PrefillArgs &a, int head_dim, int batch, int max_q_len, hipStream_t stream);
+struct DecodeArgs;
+// attn_mixed.hip: ranked prefill workgroups of 128 (split) or 256 columns and `shares` workgroups of the equal-share decode.
+int launch_mixed(const PrefillArgs &a, const DecodeArgs &d, int shares, int pieces, bool split, int head_dim, int batch, int max_q_len, hipStream_t stream);
 
 }  // namespace sp
