@@ -1077,48 +1077,68 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   SP_TRACE_STAMP(2, 0);
   SP_TRACE_STAMP(3, 256);
 
-  if (SPLIT) {
-    // ---- merge the second group's running state into the first group's (same columns, same
-    // lane layout: wave w and wave w+4 hold the same (column, channel) positions).
-    constexpr int NST = 16 * G::kDBlocks + 2;  // floats of state per lane
-    static_assert(256 * NST * 4 <= 2 * REGION, "state must fit the tile buffers");
-    lds_float *xch = (lds_float *)smem + wq * 64 + lane;  // [value][wave][lane]
+  // The channel blocks this wave writes, db0 and on: with SPLIT each group finishes one half of them.
+  constexpr int HB = SPLIT ? G::kDBlocks / 2 : G::kDBlocks;
+  f32x16 fin[HB];
+  const int db0 = SPLIT ? grp * HB : 0;
+  if constexpr (SPLIT) {
+    // ---- merge of the two groups' running states (same columns, same lane layout: wave w and wave w+4 hold
+    // the same (column, channel) positions): each group hands over the half of O that the other one finishes,
+    // in 16-byte pieces, so that both share the merge and the stores (4 x 2048 tokens, 8q/1kv, two such workgroups a
+    // CU: 57.5 us when the first group did all of it in 4-byte pieces, 55.7 so).
+    constexpr int NQ = 4 * HB;  // 16-byte pieces of half a state per lane
+    static_assert(2 * 256 * (NQ * 16 + 8) <= 2 * REGION, "states must fit the tile buffers");
+    lds_f32x4 *xch = (lds_f32x4 *)smem + wq * 64 + lane;                        // [group][piece][wave][lane]
+    lds_f32x2 *xml = (lds_f32x2 *)(smem + 2 * 256 * NQ * 16) + wq * 64 + lane;  // [group][wave][lane]
     __syncthreads();  // every wave is done reading tiles
-    if (grp == 1) {
+    // values are selected, not indices: an index that depends on the group would put o into memory
 #pragma unroll
-      for (int db = 0; db < G::kDBlocks; ++db)
+    for (int n = 0; n < HB; ++n)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) xch[(16 * db + r) * 256] = o[db][r];
-      xch[(NST - 2) * 256] = m_used;
-      xch[(NST - 1) * 256] = l + l2;
-    }
+      for (int r4 = 0; r4 < 4; ++r4) {
+        f32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a0 = o[n][4 * r4 + e], a1 = o[G::kDBlocks - HB + n][4 * r4 + e];
+          x[e] = grp == 0 ? a1 : a0;
+          fin[n][4 * r4 + e] = grp == 0 ? a0 : a1;
+        }
+        xch[(grp * NQ + 4 * n + r4) * 256] = x;
+      }
+    xml[grp * 256] = (f32x2){m_used, l + l2};
     __syncthreads();
-    if (grp == 1) return;
-    const float m_b = xch[(NST - 2) * 256], l_b = xch[(NST - 1) * 256];
-    const float m_new = fmaxf(m_used, m_b);  // the first group always saw a key: finite
-    const float fa = __builtin_amdgcn_exp2f((m_used - m_new) * a.sl2e);
-    const float fb = __builtin_amdgcn_exp2f((m_b - m_new) * a.sl2e);  // 0 if the second group had no tile
-    l = (l + l2) * fa + l_b * fb;
+    const f32x2 ml = xml[(1 - grp) * 256];
+    const float m_new = fmaxf(m_used, ml[0]);  // the first group always saw a key: finite
+    const float fa = __builtin_amdgcn_exp2f((m_used - m_new) * a.sl2e);  // 0 for a group that had no tile
+    const float fb = __builtin_amdgcn_exp2f((ml[0] - m_new) * a.sl2e);
+    l = (l + l2) * fa + ml[1] * fb;
     l2 = 0.f;
 #pragma unroll
-    for (int db = 0; db < G::kDBlocks; ++db)
+    for (int n = 0; n < HB; ++n)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * fa + xch[(16 * db + r) * 256] * fb;
-    m_used = m_new;  // what l and o now refer to (a partial carries it along)
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 x = xch[((1 - grp) * NQ + 4 * n + r4) * 256];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) fin[n][4 * r4 + e] = fin[n][4 * r4 + e] * fa + x[e] * fb;
+      }
+    m_used = m_new;  // what l and fin now refer to (a partial carries it along)
+  } else {
+#pragma unroll
+    for (int db = 0; db < HB; ++db) fin[db] = o[db];
   }
 
   l += l2;
   float lt = l + other_half(l);
   if (PART) {  // un-normalised partial for the combine pass
     if (valid) {
-      float *po = a.part_o + prow * D;
+      float *po = a.part_o + prow * D + 32 * db0;
 #pragma unroll
-      for (int db = 0; db < G::kDBlocks; ++db)
+      for (int db = 0; db < HB; ++db)
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4)
           *reinterpret_cast<f32x4 *>(po + 32 * db + 8 * r4 + 4 * half) =
-              (f32x4){o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]};
-      if (half == 0) *reinterpret_cast<f32x2 *>(a.part_ml + prow * 2) = (f32x2){m_used * a.sl2e, lt};
+              (f32x4){fin[db][4 * r4], fin[db][4 * r4 + 1], fin[db][4 * r4 + 2], fin[db][4 * r4 + 3]};
+      if (half == 0 && db0 == 0) *reinterpret_cast<f32x2 *>(a.part_ml + prow * 2) = (f32x2){m_used * a.sl2e, lt};
     }
     return;
   }
@@ -1136,13 +1156,13 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // ---- normalise and store
   float inv = 1.0f / lt;
   if (valid) {
-    char *dst = a.out + out_off;
+    char *dst = a.out + out_off + 64 * db0;
 #pragma unroll
-    for (int db = 0; db < G::kDBlocks; ++db)
+    for (int db = 0; db < HB; ++db)
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4)
-        store4_bf16(dst + (32 * db + 8 * r4 + 4 * half) * 2, o[db][4 * r4] * inv, o[db][4 * r4 + 1] * inv,
-                    o[db][4 * r4 + 2] * inv, o[db][4 * r4 + 3] * inv);
+        store4_bf16(dst + (32 * db + 8 * r4 + 4 * half) * 2, fin[db][4 * r4] * inv, fin[db][4 * r4 + 1] * inv,
+                    fin[db][4 * r4 + 2] * inv, fin[db][4 * r4 + 3] * inv);
   }
 #ifdef SP_PREFILL_TRACE
   SP_TRACE_STAMP(4, 0);
