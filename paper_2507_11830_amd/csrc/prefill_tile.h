@@ -228,22 +228,45 @@ __device__ __forceinline__ bool ranked_item(const PrefillArgs &a, int tpt_shift,
       }
     w = wave_total(w);
     longest = wave_max_i(longest);
-    int limit = max((int)((float)w * (float)a.n_hgroups * (1.25f / 256)) + 1, max(kMinCutTiles, (longest + kMaxCutPieces - 1) / kMaxCutPieces));
+    const int base = max((int)((float)w * (float)a.n_hgroups * (1.25f / 256)) + 1, max(kMinCutTiles, (longest + kMaxCutPieces - 1) / kMaxCutPieces));
+    int limit = base;
+    int items = 0;
+#pragma unroll
+    for (int u = 0; u < kRankSlots; ++u) items += nt[u];
+    bool settled = wave_total(items) * a.n_hgroups > 256;
     int p[kRankSlots], total;  // pieces of cut items
     for (;;) {
+      int wgs = 0;
       total = 0;
 #pragma unroll
       for (int u = 0; u < kRankSlots; ++u) {
         p[u] = 0;
         if (u >= nslot) continue;
+        wgs += nt[u];
         // an item of t tiles has one piece for every n >= 0 with t > n * limit
-        for (int n = 1; n * limit < longest; ++n)
-          p[u] += (n == 1 ? 2 : 1) * (nt[u] - first_tile_ge(c[u], q[u], nt[u], 64 * n * limit + 1, tpt_shift));
+        for (int n = 1; n * limit < longest; ++n) {
+          const int more = nt[u] - first_tile_ge(c[u], q[u], nt[u], 64 * n * limit + 1, tpt_shift);
+          p[u] += (n == 1 ? 2 : 1) * more;
+          wgs += more;
+        }
         total += p[u];
       }
       total = wave_total(total);
-      if (total * a.n_hgroups <= a.cut_slots) break;  // always, by the bound above; a limit of `longest` cuts nothing
-      limit *= 2;
+      if (total * a.n_hgroups > a.cut_slots) {  // never, by the bound above; a limit of `longest` cuts nothing
+        limit *= 2;
+        settled = true;
+        continue;
+      }
+      if (settled || wave_total(wgs) * a.n_hgroups <= 256) break;
+      // One round of workgroups, with pieces up to 1.2 times as long, before a second round of a few (6 chunks at 8q/1kv,
+      // 114 items: 66 -> 55 us; 8 at 16q/2kv, 144 items: 62 -> 55.5; 2 at 32q/4kv, 206 items: 134 -> 129; where the second
+      // round is full of short items it had been the better one: 28 at 8q/1kv, 118 items: 57 -> 60; up to 1 us elsewhere).
+      if (5 * limit >= 6 * base) {
+        limit = base;
+        settled = true;
+      } else {
+        limit += max(1, base / 10);
+      }
     }
     if (r == 0 && out->tile == 0 && threadIdx.x == 0) *a.cut_used = total * a.n_hgroups;  // out->tile: the caller's head group
     if (r < total) {
