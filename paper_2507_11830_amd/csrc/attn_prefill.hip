@@ -70,7 +70,7 @@ static int cut_slots(int batch, int total_q, int max_q_len, int max_kv_len, int 
   const int cols = (group & (group - 1)) == 0 ? (group < 32 ? group : 32) : 1;  // heads in the column dimension
   const long rows = (long)total_q * num_q_heads, groups = num_q_heads / cols;
   const long items = rows / 256 + ((long)batch * groups + 1) / 2, most = rows / 256 + (long)batch * groups;
-  if (most > (1 << 20)) return 0;
+  if (most > (1 << 20) || !cut_countable(max_q_len, 256 / cols, max_kv_len)) return 0;
   if (g_cut_mode == 0) {
     // Mixed batches: their chunk is short next to what a launch costs (2048 tokens: 64.2 us against 63.7).
     if (mixed_route_cap(batch, total_q, max_q_len, num_q_heads, num_kv_heads) > 0) return 0;

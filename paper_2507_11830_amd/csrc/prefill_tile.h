@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "attn_tile.h"
+#include "cut_plan.h"
 
 namespace sp {
 
@@ -97,8 +98,6 @@ constexpr bool kScaledQSwitch = false;
 // up to 3484 keys 58 us, cut 63; 258 of 2048 keys 60 and 68; 253 of up to 4887 keys 99 and 87; 286 of up to 3245 101 and 82).
 constexpr int kCutMostItems = 448, kCutFewItems = 8, kCutKeys = 2048, kCutNoPrefixItems = 240, kCutNoPrefixKeys = 3072;
 constexpr int kSmallGrid = 576;  // 128-column workgroups up to which they are the form of a launch that is not cut
-constexpr int kMostExtraPieces = 205;
-constexpr int kMostCutSlots = 416;  // pieces are at most 2 * 256 / 1.25 (ranked_item), rounded up
 
 // What the merge of a cut work item has to know; one per partial slot.
 struct CutEntry {
@@ -129,10 +128,6 @@ struct PrefillArgs {
   CutEntry *cut_tab;
   int32_t *cut_used;  // number of slots in use
 };
-
-// Split forms of the kernel cut a range into as many pieces at most.
-constexpr int kMaxCutPieces = 16;
-constexpr int kMinCutTiles = 8;     // key tiles that are never cut further
 
 // Inclusive prefix sum over the 64 lanes (gfx9 DPP: shifts inside rows of 16, then the two row
 // broadcasts); lane 63 ends up with the total.
@@ -173,21 +168,11 @@ __device__ __forceinline__ int wave_max_i(int x) {
 // sequence per lane and slot: batches of up to 64 * kRankSlots sequences.  The search is a chain
 // of dependent cross-lane operations in a single wave (about 0.2 us per probe), which is why the
 // probes are few and DPP, not LDS permutes, carries them.
-constexpr int kRankSlots = 4;
-
 struct RankedItem {
   int seq, tile;
   int q0, q_len, ctx;  // the sequence's entries of the length arrays, so that nobody has to load them again
   int piece, pieces;   // CUT: which piece of the item's key range, of how many
 };
-
-// first query tile of a sequence (c cached and q new keys, nt tiles) that sees at least `keys` keys; nt if none does
-__device__ __forceinline__ int first_tile_ge(int c, int q, int nt, int keys, int tpt_shift) {
-  if (nt == 0 || c + q < keys) return nt;
-  const int d = max(keys - c, 0);
-  const int j0 = ((d + (1 << tpt_shift) - 1) >> tpt_shift) - 1;
-  return min(max(j0, 0), nt - 1);
-}
 
 // CUT: items longer than `limit` key tiles are cut into ceil(tiles / limit) equal pieces, and the pieces come
 // before all uncut items in the order.  limit is 5/4 of what a CU's equal share of the launch's key tiles is: an item
@@ -217,57 +202,8 @@ __device__ __forceinline__ bool ranked_item(const PrefillArgs &a, int tpt_shift,
   out->pieces = 1;
   int wsh = a.rank_shift;
   if (CUT) {
-    // key tiles of the whole launch and of its longest item
-    int w = 0, longest = 0;
-#pragma unroll
-    for (int u = 0; u < kRankSlots; ++u)
-      if (u < nslot && nt[u] > 0) {
-        const float keys = (float)nt[u] * (float)c[u] + (float)tpt * 0.5f * (float)nt[u] * (float)(nt[u] - 1) + (float)q[u];
-        w += (int)fminf(keys * (1.0f / 64), 0x1p22f) + 1;  // 256 sequences of at most 2^22 fit the sum
-        longest = max(longest, (c[u] + q[u] + 63) >> 6);
-      }
-    w = wave_total(w);
-    longest = wave_max_i(longest);
-    const int base = max((int)((float)w * (float)a.n_hgroups * (1.25f / 256)) + 1, max(kMinCutTiles, (longest + kMaxCutPieces - 1) / kMaxCutPieces));
-    int limit = base;
-    int items = 0;
-#pragma unroll
-    for (int u = 0; u < kRankSlots; ++u) items += nt[u];
-    bool settled = wave_total(items) * a.n_hgroups > 256;
     int p[kRankSlots], total;  // pieces of cut items
-    for (;;) {
-      int wgs = 0;
-      total = 0;
-#pragma unroll
-      for (int u = 0; u < kRankSlots; ++u) {
-        p[u] = 0;
-        if (u >= nslot) continue;
-        wgs += nt[u];
-        // an item of t tiles has one piece for every n >= 0 with t > n * limit
-        for (int n = 1; n * limit < longest; ++n) {
-          const int more = nt[u] - first_tile_ge(c[u], q[u], nt[u], 64 * n * limit + 1, tpt_shift);
-          p[u] += (n == 1 ? 2 : 1) * more;
-          wgs += more;
-        }
-        total += p[u];
-      }
-      total = wave_total(total);
-      if (total * a.n_hgroups > a.cut_slots) {  // never, by the bound above; a limit of `longest` cuts nothing
-        limit *= 2;
-        settled = true;
-        continue;
-      }
-      if (settled || wave_total(wgs) * a.n_hgroups <= 256) break;
-      // One round of workgroups, with pieces up to 1.2 times as long, before a second round of a few (6 chunks at 8q/1kv,
-      // 114 items: 66 -> 55 us; 8 at 16q/2kv, 144 items: 62 -> 55.5; 2 at 32q/4kv, 206 items: 134 -> 129; where the second
-      // round is full of short items it had been the better one: 28 at 8q/1kv, 118 items: 57 -> 60; up to 1 us elsewhere).
-      if (5 * limit >= 6 * base) {
-        limit = base;
-        settled = true;
-      } else {
-        limit += max(1, base / 10);
-      }
-    }
+    const int limit = cut_limit(c, q, nt, nslot, tpt_shift, a.n_hgroups, a.cut_slots, (int)gridDim.x, wave_total, wave_max_i, p, &total);
     if (r == 0 && out->tile == 0 && threadIdx.x == 0) *a.cut_used = total * a.n_hgroups;  // out->tile: the caller's head group
     if (r < total) {
       int k = r, at = -1;
@@ -1214,12 +1150,10 @@ inline int prefill_grid(PrefillArgs &a, int cols, int batch, int max_q_len, dim3
   *grid = dim3((unsigned)gx, (unsigned)a.ntiles_x, (unsigned)a.kv_splits);
   if (a.ranked) {
     // Ranked workgroups take items by linear id, so the launch only needs as many workgroups as
-    // there can be items: every sequence has at most q_len / tpt + 1 query tiles.  (The grid of
+    // there can be items (ranked_workgroups).  (The grid of
     // the static order is batch x tiles of the LONGEST chunk; in a ragged batch most of it is
     // empty, and an empty workgroup still holds a CU for a microsecond.)
-    // CUT: the cut items add their further pieces, fewer than total tiles / limit <= 256 / 1.25.
-    const long items = (long)a.total_q / tpt + batch;
-    const long wgs = items * a.n_hgroups * a.kv_splits + (a.cut_slots < kMostExtraPieces ? a.cut_slots : kMostExtraPieces);
+    const long wgs = ranked_workgroups(a.total_q, tpt, batch, a.n_hgroups, a.kv_splits, a.cut_slots);
     if (wgs > 0x7fffffffL) a.ranked = 0;  // workgroups are numbered in 32 bits
     else *grid = dim3((unsigned)wgs, 1, 1);
   }

@@ -1,0 +1,88 @@
+"""The prefill form that cuts long work items, on the CPU: whatever the lengths are, its search deals out no more
+workgroups than the host launches and no more partials than the workspace holds, and counts its pieces exactly."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2507_11830_amd as sp
+from conftest import ROOT
+
+SLOTS = 416
+SHARDS = [(2, 1), (4, 1), (8, 1), (16, 2), (32, 8), (12, 3), (8, 8)]
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("cut_plan") / "cut_plan.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-Wno-unknown-pragmas",
+                    "-I", os.path.join(ROOT, "paper_2507_11830_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "cut_plan_host.cpp"), "-o", so], check=True)
+    L = ctypes.CDLL(so)
+    L.launched_workgroups.argtypes = [ctypes.c_long] + [ctypes.c_int] * 4
+
+    def run(hq, hkv, ctx, new, slots=SLOTS):
+        """(workgroups needed, launched, partials needed, partials counted, most pieces of an item)"""
+        ctx, new = np.array(ctx, np.int32), np.array(new, np.int32)
+        group = hq // hkv
+        cols = group if group & (group - 1) == 0 else 1
+        tpt, hgroups = 256 // cols, hq // cols
+        launched = L.launched_workgroups(int(new.sum()), tpt, len(new), hgroups, slots)
+        total = ctypes.c_int(-1)
+        limit = L.limit_of(len(new), ctx.ctypes.data_as(ctypes.c_void_p), new.ctypes.data_as(ctypes.c_void_p),
+                           tpt.bit_length() - 1, hgroups, slots, launched, ctypes.byref(total))
+        pieces = []
+        for c, n in zip(ctx.astype(np.int64), new.astype(np.int64)):
+            keys = c + np.minimum(n, tpt * np.arange(1, -(-n // tpt) + 1))
+            pieces.append(-(-(-(-keys // 64)) // limit))
+        pieces = np.concatenate(pieces)
+        return pieces.sum() * hgroups, launched, pieces[pieces > 1].sum() * hgroups, total.value * hgroups, pieces.max()
+
+    return run
+
+
+def check(got):
+    needed, launched, partials, counted, most = got
+    assert needed <= launched, f"{needed} workgroups dealt out, {launched} launched"
+    assert partials == counted and partials <= SLOTS and most <= 16
+
+
+@pytest.mark.parametrize("hq,hkv", SHARDS)
+def test_batches_of_a_serving_engine(plan, hq, hkv):
+    rng = np.random.default_rng(hq * 100 + hkv)
+    for i in range(400):
+        n = int(rng.integers(1, 257)) if i % 2 else int(rng.integers(1, 9))
+        new = rng.integers(0, int(np.exp(rng.uniform(1, 8))) + 1, n)
+        new[rng.integers(n)] += 1
+        ctx = (np.exp(rng.uniform(0, np.log(1.3e5), n)) * (rng.random(n) < rng.choice([0.1, 0.9]))).astype(int)
+        check(plan(hq, hkv, ctx, new))
+
+
+# one sequence whose key tiles are more than the estimate can hold, alone and next to short ones
+@pytest.mark.parametrize("hq,hkv", SHARDS)
+@pytest.mark.parametrize("ctx", [1_300_000, 1_750_000, 3_500_000, 8_000_000, 16_700_000])
+@pytest.mark.parametrize("new", [512, 4096, 10000])
+def test_very_long_contexts(plan, hq, hkv, ctx, new):
+    check(plan(hq, hkv, [ctx], [new]))
+    check(plan(hq, hkv, [700, ctx, 0, 30000], [64, new, 900, 1]))
+
+
+def test_few_slots_and_wrong_hints(plan):
+    """Fewer slots than pieces, or fewer workgroups than items: nothing is cut then rather than dropped."""
+    for slots in (0, 1, 7, 60):
+        needed, launched, partials, counted, _ = plan(8, 1, [9000, 100, 5000], [300, 40, 64], slots)
+        assert partials == counted <= slots and needed <= launched
+
+
+@pytest.mark.parametrize("hq,hkv,new,ctx", [(2, 1, 40000, 1_300_000), (8, 1, 10000, 1_750_000), (16, 2, 5000, 3_500_000)])
+def test_such_contexts_keep_the_form_that_cuts_by_the_hints(hq, hkv, new, ctx):
+    """... and the host does not ask for the cut form's workspace."""
+    size = lambda: sp.sp_attn_prefill_workspace_size(1, new, new, ctx + new, hq, hkv, 128)
+    auto = size()
+    try:
+        sp.sp_debug_set_tuning("prefill_cut", 1)
+        assert auto == size()
+    finally:
+        sp.sp_debug_set_tuning("prefill_cut", 0)
