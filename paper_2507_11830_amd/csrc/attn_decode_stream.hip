@@ -242,7 +242,7 @@ int plan_decode_stream(DecodeArgs &a, int batch, int max_q, int tiles, int max_l
     wgs = dim3((unsigned)want);
     max_pieces = (int)((max_len + 31) / 32 / least + 2);
     if (max_pieces > want) max_pieces = (int)want;
-    a.inv_wgs = (unsigned)((0x100000000ull + want - 1) / want);
+    a.inv_wgs = share_inverse(want);
     a.row_tab = (int32_t *)workspace;
     a.part_o = (float *)((char *)workspace + tab);
     a.part_ml = a.part_o + (size_t)(rows + want) * a.cols * head_dim;

@@ -23,7 +23,7 @@ struct DecodeArgs {
   // runs; partials [slot][cols][D], cols = query tokens x geff; equal runs: per row its first slot and number of slots
   int batch, cols, row_splits, hg_per_kv, q_max;
   int32_t *row_tab;
-  unsigned inv_wgs;  // 2^32 / workgroups, rounded up
+  unsigned inv_wgs;  // share_inverse of the number of workgroups
   float sl2e;
   float tau;  // lazy-rescale threshold in raw score units (8 / sl2e)
 };

@@ -2,13 +2,11 @@
 // by the files that launch it: attn_decode_stream.hip and attn_mixed.hip.
 #pragma once
 #include "decode_block.h"
+#include "share_plan.h"
 
 namespace sp {
 
-constexpr int kWaves = 4;          // waves per workgroup
 constexpr int kMaxSeqs = kMaxShareSeqs;
-constexpr int kRowCost = 8;        // blocks that a segment's fixed cost amounts to (64-sequence batch: 4 blocks 34.5 us, 8 and 12 33.5)
-constexpr int kMinShare = 12;      // blocks per workgroup below which a further cut costs more than it gives
 
 typedef __attribute__((address_space(3))) int32_t lds_int;
 
@@ -329,8 +327,7 @@ __device__ __forceinline__ void decode_share(const DecodeArgs &a, lds_char *smem
     s_len[s] = len;
   }
   wave_lds_fence();
-  int share = (int)(((unsigned long long)(unsigned)total * a.inv_wgs) >> 32) + 1;  // >= total / workgroups
-  share = (max(share, kMinShare + kRowCost) + kWaves - 1) & -kWaves;
+  const int share = share_blocks(total, a.inv_wgs);
   const int lo = wg * share, hi = min(total, lo + share);
   if (lo >= hi) return;
   auto uni = [&](lds_int *p) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*p); };
@@ -359,7 +356,7 @@ __device__ __forceinline__ void decode_share(const DecodeArgs &a, lds_char *smem
     } else if (p1 > p0) {
       const bool whole = p0 == 0 && p1 == v - kRowCost;
       if (p0 == 0 && threadIdx.x == 0) {  // the row's first partial slot and its number of partials
-        const uint32_t pieces = whole ? 1 : (uint32_t)((last - 1) / share - wg + 1);
+        const uint32_t pieces = whole ? 1 : (uint32_t)share_pieces(last, share, wg);
         *reinterpret_cast<u32x2 *>(a.row_tab + 2 * (long)row) = (u32x2){(uint32_t)(wg + row), pieces};
       }
       row_segment<D, APPEND, MQ, NT>(a, smem, lane, w, seq, hg, L, ctx, tok, p0, p1, load_pages(a, seq, p0, 0, w, lane), whole, wg + row);

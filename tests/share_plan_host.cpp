@@ -1,0 +1,9 @@
+// How the equal-share decode deals rows to workgroups (csrc/share_plan.h), for the CPU tests.
+#include "share_plan.h"
+
+extern "C" {
+
+int share_of(int total, long wgs) { return sp::share_blocks(total, sp::share_inverse(wgs)); }
+int pieces_of(int last, int share, int wg) { return sp::share_pieces(last, share, wg); }
+
+}
