@@ -925,6 +925,10 @@ int launch_decode(const sp_cache_desc &c, const void *k_new, const void *v_new, 
     // every sequence is empty: the combine kernel alone writes the zero rows
     return launch_combine(nullptr, nullptr, out, (long)batch * num_q_heads, 1, c.head_dim, stream);
   }
+  // Planned within the size that the caller was asked for, also where there is more: the division of the keys, and with it
+  // the result's last bits, then follow from the shape alone (sp_attn_decode_static gives those of sp_attn_decode).
+  const size_t asked = decode_workspace_bytes(batch, max_seq_len, num_q_heads, c.head_dim);
+  if (workspace_bytes > asked) workspace_bytes = asked;
   if (stream_allowed()) {
     a.out = (char *)out;
     const int rc = launch_decode_stream(a, batch, 1, 1, max_seq_len, c.head_dim, workspace, workspace_bytes, g_form, stream);

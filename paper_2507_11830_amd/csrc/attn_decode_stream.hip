@@ -225,8 +225,13 @@ int plan_decode_stream(DecodeArgs &a, int batch, int max_q, int tiles, int max_l
   const size_t tab = (size_t)(rows * 8 + 15) / 16 * 16;
   const long least = kMinShare + kRowCost;
   const long useful = (rows * ((max_len + 31) / 32 + kRowCost) + least - 1) / least;
-  const long want = resident < useful ? resident : useful;
-  if (splits == 0 && (batch > kMaxSeqs || ws < tab + (rows + want) * slot_bytes)) {
+  long want = resident < useful ? resident : useful;
+  // Where the room is short, up to a quarter of the workgroups less: what sp_attn_decode_workspace_size returns follows the
+  // one-wave splits and is a few slots short of the full number at 16 heads per KV head of 64 (29 sequences of up to 18214
+  // keys at 16q/1kv: 492 of 512 fit).
+  const long fit = ws < tab ? 0 : (long)((ws - tab) / slot_bytes) - rows;
+  if (fit < want && 4 * fit >= 3 * want) want = fit;
+  if (splits == 0 && (batch > kMaxSeqs || fit < want)) {
     if (max_len > 1024) return 1;
     chunk = 1024;
     splits = 1;

@@ -66,3 +66,33 @@ def test_static_scratch_decode_refuses_shapes_beyond_its_array():
     with pytest.raises(sp.SpError) as e:
         sp.sp_attn_decode_static(g.cache, q, q, dev_i32(np.ones(4096)), dev_i32(np.zeros((4096, 1024))), 16384, 0.1)
     assert e.value.status == sp.SP_ERR_WORKSPACE
+
+
+# shapes whose partials fill the asked-for workspace to a few slots, or pass it, in the forms that a larger one would allow
+@pytest.mark.parametrize("batch,longest,Hq,Hkv,d", [(320, 846, 32, 8, 128), (160, 846, 64, 8, 128), (29, 18214, 16, 1, 64), (48, 6000, 32, 2, 64)])
+def test_static_scratch_and_workspaces_of_any_size_give_the_same_bits(batch, longest, Hq, Hkv, d):
+    import torch
+    import paper_2507_11830_amd as sp
+
+    gen = torch.Generator(device="cuda").manual_seed(205)
+    rng = np.random.default_rng(205)
+    lens = rng.integers(1, longest + 1, batch)
+    lens[0] = longest
+    # a cache of 256 pages that the sequences share: only the addresses are of interest here
+    cache = sp.KVCache(*(torch.randn((256, Hkv, 16, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2)))
+    bt, sl = dev_i32(rng.integers(0, 256, (batch, -(-longest // 16)))), dev_i32(lens)
+    q = torch.randn((batch, Hq, d), generator=gen, device="cuda").to(torch.bfloat16)
+    size = sp.sp_attn_decode_workspace_size(batch, longest, Hq, d)
+    assert size <= 16 << 20
+    outs = []
+    for ws_bytes in (size, 2 * size, 64 << 20, None):
+        out = torch.full_like(q, float("nan"))
+        if ws_bytes is None:
+            sp.sp_attn_decode_static(cache, q, out, sl, bt, longest, d ** -0.5)
+        else:
+            sp.sp_attn_decode(cache, q, out, sl, bt, longest, d ** -0.5, torch.empty(ws_bytes, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        outs.append(bits_of(out))
+    assert np.isfinite(W.bf16_bits_to_f64(outs[0])).all()
+    for got in outs[1:]:
+        assert np.array_equal(got, outs[0])
