@@ -39,16 +39,6 @@ void set_prefill_short_chunk(int mode) { g_short_chunk_mode = mode; }
 void set_prefill_split(int mode) { g_split_mode = mode; }
 void set_prefill_kv_splits(int n) { g_kv_splits = n; }
 
-constexpr int kMaxKvSplits = 16;
-constexpr long kMaxPartialSlots = 1L << 17;  // (row, split) pairs the workspace is ever sized for
-
-// Largest number of key-range pieces a batch of `rows` (token, head) rows may be cut into.
-static int kv_split_cap(long rows) {
-  if (rows <= 0) return 1;
-  long cap = kMaxPartialSlots / rows;
-  return (int)(cap < 1 ? 1 : cap > kMaxKvSplits ? kMaxKvSplits : cap);
-}
-
 // Mixed batch?  Decided from the host-side hints alone: chunks too long for the short-chunk path
 // exist (max_q_len), and the tokens besides the longest chunk are so few that at least one other
 // sequence must be short — those sequences are then routed to the split kernel (which reads a
@@ -65,20 +55,9 @@ static int mixed_route_cap(int batch, int total_q, int max_q_len, int num_q_head
 
 // Slots for partials of the CUT form (0: not taken), from the host-side hints alone.
 static int cut_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads) {
-  if (g_cut_mode == 1 || batch <= 0 || batch > 64 * kRankSlots || total_q <= 0 || max_kv_len > (1 << 24)) return 0;
-  const int group = num_q_heads / num_kv_heads;
-  const int cols = (group & (group - 1)) == 0 ? (group < 32 ? group : 32) : 1;  // heads in the column dimension
-  const long rows = (long)total_q * num_q_heads, groups = num_q_heads / cols;
-  const long items = rows / 256 + ((long)batch * groups + 1) / 2, most = rows / 256 + (long)batch * groups;
-  if (most > (1 << 20) || !cut_countable(max_q_len, 256 / cols, max_kv_len)) return 0;
-  if (g_cut_mode == 0) {
-    // Mixed batches: their chunk is short next to what a launch costs (2048 tokens: 64.2 us against 63.7).
-    if (mixed_route_cap(batch, total_q, max_q_len, num_q_heads, num_kv_heads) > 0) return 0;
-    if (items > kCutMostItems || max_kv_len < (items > kCutFewItems ? kCutKeys : 2 * kCutKeys)) return 0;
-    if (max_kv_len <= max_q_len && (items < kCutNoPrefixItems || max_kv_len < kCutNoPrefixKeys)) return 0;
-  }
-  const long by_len = most * (g_cut_mode == 2 ? kMaxCutPieces : (max_kv_len + 64 * kMinCutTiles - 1) / (64 * kMinCutTiles));
-  return (int)(by_len < kMostCutSlots ? by_len : kMostCutSlots);
+  // Mixed batches: their chunk is short next to what a launch costs (2048 tokens: 64.2 us against 63.7).
+  if (g_cut_mode == 1 || (g_cut_mode == 0 && mixed_route_cap(batch, total_q, max_q_len, num_q_heads, num_kv_heads) > 0)) return 0;
+  return cut_form_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, num_kv_heads, g_cut_mode == 2);
 }
 
 static size_t cut_bytes(int slots, int head_dim) {
@@ -163,28 +142,18 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
   a.sl2e = scale * 1.44269504088896340736f;
   a.tau = 8.0f / a.sl2e;
 
-  // ---- shape of the launch, from host-side counts only.  wg128 estimates the 128-column
-  // workgroups that find work (rows / 128 plus half a partial tile per sequence and head group).
+  // ---- shape of the launch, from host-side counts only
   const long rows = (long)total_q * num_q_heads;
-  const long wg128 = rows / 128 + ((long)batch * a.n_hgroups + 1) / 2;
-  // Up to about one 256-column workgroup per CU: let the two wave groups split the key range of
-  // 128 columns instead (halves the critical path of the longest work item; measured faster up
-  // to that grid size, slower beyond it because every K/V tile is then staged for half the
-  // columns).
-  const bool small_grid = g_split_mode == 0 ? wg128 <= kSmallGrid : g_split_mode == 2;
-  // How many pieces the key range of a query tile is cut into (1 = none): only when even the
-  // 128-column workgroups leave most CUs idle and the key ranges are long, and bounded by what
-  // the caller's workspace holds.  A piece's partial costs about as much HBM time as 500 keys
-  // cost matrix time, so pieces stay around 1500 keys or longer.
+  const long wg128 = estimate_wg128(rows, batch, a.n_hgroups);
+  const bool small_grid = g_split_mode == 0 ? is_small_grid(wg128) : g_split_mode == 2;
+  // Pieces of the key ranges, bounded by what the caller's workspace holds.
   const size_t slot_bytes = (size_t)(c.head_dim + 2) * sizeof(float);
   int kvs = 1;
   if (workspace && rows > 0) {
     if (g_kv_splits > 0) {
       kvs = g_kv_splits;
     } else if (small_grid) {
-      const long by_grid = 256 / (wg128 > 0 ? wg128 : 1);
-      const long by_len = (long)max_kv_len / 1536;
-      kvs = (int)(by_grid < by_len ? by_grid : by_len);
+      kvs = kv_pieces(wg128, max_kv_len);
     }
     const int cap = kv_split_cap(rows);
     if (kvs > cap) kvs = cap;

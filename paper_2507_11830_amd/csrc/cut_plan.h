@@ -31,10 +31,92 @@ SP_HD int first_tile_ge(int c, int q, int nt, int keys, int tpt_shift) {
   return imin(imax(j0, 0), nt - 1);
 }
 
+constexpr int kMaxKvSplits = 16;
+constexpr long kMaxPartialSlots = 1L << 17;  // (row, split) pairs the workspace is ever sized for
+
+// Largest number of key-range pieces a batch of `rows` (token, head) rows may be cut into.
+inline int kv_split_cap(long rows) {
+  if (rows <= 0) return 1;
+  long cap = kMaxPartialSlots / rows;
+  return (int)(cap < 1 ? 1 : cap > kMaxKvSplits ? kMaxKvSplits : cap);
+}
+
+// Up to about one 256-column workgroup per CU: let the two wave groups split the key range of
+// 128 columns instead (halves the critical path of the longest work item; measured faster up
+// to that grid size, slower beyond it because every K/V tile is then staged for half the
+// columns).
+constexpr int kSmallGrid = 576;  // 128-column workgroups
+inline bool is_small_grid(long wg128) { return wg128 <= kSmallGrid; }
+
+// How many pieces the key range of a query tile of a small grid is cut into (1 = none): only when even the
+// 128-column workgroups leave most CUs idle and the key ranges are long.  A piece's partial costs about as much HBM time
+// as 500 keys cost matrix time, so pieces stay around 1500 keys or longer.
+inline int kv_pieces(long wg128, long max_kv_len) {
+  const long by_grid = 256 / (wg128 > 0 ? wg128 : 1);
+  const long by_len = max_kv_len / 1536;
+  return (int)(by_grid < by_len ? by_grid : by_len);
+}
+
+// 128-column workgroups that find work, estimated: rows / 128 plus half a partial tile per sequence and head group.
+inline long estimate_wg128(long rows, int batch, long n_hgroups) { return rows / 128 + ((long)batch * n_hgroups + 1) / 2; }
+
+// Whether a batch on cached prefixes takes the form, from the hints: batch sequences of `columns` query columns (tokens x
+// heads in the column dimension) per head group on average, `streams` head groups of all sequences, keys up to
+// max_kv_len.  narrow: the launch has 128-column workgroups otherwise, in kv_pieces pieces each (else whole 256-column ones).
+// Times are compared in key tiles of a workgroup.  The lengths are not known here: a sequence is taken to be 0.6 of the
+// longest (one alone: all of it), and what a whole launch waits for beyond the mean load of a CU to be 0.2 and 0.4 of its
+// longest item; the form itself costs a merge and the search, 4 and 8 tiles.  The numbers are those that leave the least
+// behind on 420 batches (equal, uniform, cubed and lognormal lengths, 1..200 sequences, 40..8192 columns, up to 60000
+// keys, nine head shards; both forms timed): 14.4 % of the time is gained over never cutting, 14.7 % with hindsight; 20 batches lose
+// more than 3 %, 8 % on average, 20 % at most (5 chunks of up to 741 tokens at 16q/2kv).  Both sides of it:
+//   1 x 64 tokens on 20000 keys, 8q/1kv: 30.4 us in 13 pieces of 128 columns, 39.6 cut; on 5500 keys 28.4 and 21.9 (an item
+//   has kMaxCutPieces at most, each walked by one workgroup, where two wave groups share the narrow form's);
+//   64 x 37 tokens of up to 6000 keys, 12q/3kv (columns for 1.2 tiles of 256): 92.6 and 124.5;
+//   32 chunks of 512 tokens on up to 8192 keys: 164 whole, 106 cut; 549 items, longest 484 tiles: 518 and 359; 600 items, longest
+//   27 tiles: 61.6 and 69 (nothing to gain: all items are short next to what a CU does).
+inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, bool narrow, int kv_pieces) {
+  const double tiles = (double)((max_kv_len + 63) / 64), mean = batch == 1 ? 1.0 : 0.6;
+  const double share = streams * (double)(long)((columns + 255.99) / 256) * tiles * mean / kCutShare;
+  double cut = 1.25 * share;
+  if (cut < tiles / kMaxCutPieces) cut = tiles / kMaxCutPieces;
+  if (cut < kMinCutTiles) cut = kMinCutTiles;
+  const double longest = narrow ? tiles / (2 * kv_pieces) : tiles;
+  const double load = narrow ? 1.1 * streams * (double)(long)((columns + 127.99) / 128) * tiles * mean / (2 * kCutShare) + 0.2 * longest
+                             : share + 0.4 * longest;
+  return cut + (narrow ? 4 : 8) < (load > longest ? load : longest);
+}
+
+// Batches without cached prefixes hold items of all lengths and few long ones; the 128-column form or the plain order is as
+// good up to this many items or keys (201 items of up to 3484 keys 58 us, cut 63; 258 of 2048 keys 60 and 68; 253 of up to
+// 4887 keys 99 and 87; 286 of up to 3245 101 and 82), and beyond the last number heaviest first evens them out alone.
+constexpr int kCutNoPrefixItems = 240, kCutNoPrefixMost = 448, kCutNoPrefixKeys = 3072;
+
 // Whether the key tiles of a sequence of up to max_q_len new and max_kv_len visible keys stay within what cut_limit's
 // sum can hold.  Beyond that its limit is too small: it cuts into more pieces than it should.
 inline bool cut_countable(long max_q_len, int tpt, long max_kv_len) {
   return (max_q_len + tpt - 1) / tpt * (max_kv_len / 64 + 1) <= kMostSeqTiles;
+}
+
+// Slots for partials of the form (0: not taken), from the hints; forced: wherever it can be computed.
+inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads, bool forced) {
+  if (batch <= 0 || batch > 64 * kRankSlots || total_q <= 0 || max_kv_len > (1 << 24)) return 0;
+  const int group = num_q_heads / num_kv_heads;
+  const int cols = (group & (group - 1)) == 0 ? (group < 32 ? group : 32) : 1;  // heads in the column dimension
+  const long rows = (long)total_q * num_q_heads, streams = (long)batch * (num_q_heads / cols);
+  const long items = rows / 256 + (streams + 1) / 2, most = rows / 256 + streams;
+  if (most > (1 << 20) || !cut_countable(max_q_len, 256 / cols, max_kv_len)) return 0;
+  if (!forced) {
+    if (max_kv_len <= max_q_len) {
+      if (items < kCutNoPrefixItems || items > kCutNoPrefixMost || max_kv_len < kCutNoPrefixKeys) return 0;
+    } else {
+      const long wg128 = estimate_wg128(rows, batch, num_q_heads / cols);
+      const int by_hints = kv_pieces(wg128, max_kv_len), cap = kv_split_cap(rows);
+      const int pieces = by_hints < 1 ? 1 : by_hints < cap ? by_hints : cap;
+      if (!cut_pays(batch, streams, (double)total_q * cols / batch, max_kv_len, is_small_grid(wg128), pieces)) return 0;
+    }
+  }
+  const long by_len = most * (forced ? kMaxCutPieces : (max_kv_len + 64 * kMinCutTiles - 1) / (64 * kMinCutTiles));
+  return (int)(by_len < kMostCutSlots ? by_len : kMostCutSlots);
 }
 
 // Workgroups of a ranked launch: every sequence has at most q_len / tpt + 1 query tiles, and the cut items add their

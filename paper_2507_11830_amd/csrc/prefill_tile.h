@@ -88,17 +88,6 @@ constexpr bool kScaledQSwitch = true;
 constexpr bool kScaledQSwitch = false;
 #endif
 
-// The CUT form: launches of up to kCutMostItems 256-column items (beyond that the heaviest-first order alone evens out the
-// load: 846 items of up to 4102 keys 142 us whole, 151 cut; 441 of up to 8704 keys 163 whole, 103 cut) with key
-// ranges of at least kCutKeys (shorter ones are not worth the 4-6 us of the combine pass: 82 items of up to 1100 keys 28 us
-// whole, 37 cut; 11 items of up to 5749 keys 32 us as pieces of 128 columns, 23 cut; twice as long for the very few items
-// that pieces of 128 columns serve nearly as well).  What it costs a batch of equal lengths: 391 items of up
-// to 4318 keys 158 us whole, 162 with nothing cut.  Without cached prefixes a launch holds items of all lengths and few
-// long ones, and the 128-column form or the plain order is as good up to kCutNoPrefixItems or kCutNoPrefixKeys (201 items of
-// up to 3484 keys 58 us, cut 63; 258 of 2048 keys 60 and 68; 253 of up to 4887 keys 99 and 87; 286 of up to 3245 101 and 82).
-constexpr int kCutMostItems = 448, kCutFewItems = 8, kCutKeys = 2048, kCutNoPrefixItems = 240, kCutNoPrefixKeys = 3072;
-constexpr int kSmallGrid = 576;  // 128-column workgroups up to which they are the form of a launch that is not cut
-
 // What the merge of a cut work item has to know; one per partial slot.
 struct CutEntry {
   int32_t q0, q_len, tile, hg;

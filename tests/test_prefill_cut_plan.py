@@ -15,13 +15,19 @@ SHARDS = [(2, 1), (4, 1), (8, 1), (16, 2), (32, 8), (12, 3), (8, 8)]
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def library(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("cut_plan") / "cut_plan.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-Wno-unknown-pragmas",
                     "-I", os.path.join(ROOT, "paper_2507_11830_amd", "csrc"),
                     os.path.join(ROOT, "tests", "cut_plan_host.cpp"), "-o", so], check=True)
     L = ctypes.CDLL(so)
     L.launched_workgroups.argtypes = [ctypes.c_long] + [ctypes.c_int] * 4
+    return L
+
+
+@pytest.fixture(scope="module")
+def plan(library):
+    L = library
 
     def run(hq, hkv, ctx, new, slots=SLOTS):
         """(workgroups needed, launched, partials needed, partials counted, most pieces of an item)"""
@@ -86,3 +92,22 @@ def test_such_contexts_keep_the_form_that_cuts_by_the_hints(hq, hkv, new, ctx):
         assert auto == size()
     finally:
         sp.sp_debug_set_tuning("prefill_cut", 0)
+
+
+S70, F8, W64 = (8, 1, 128), (32, 8, 128), (16, 2, 64)
+
+
+@pytest.mark.parametrize("batch,tokens,mq,mkv,heads,cut", [
+    # few query rows: pieces of 128 columns are shorter from about 12000 keys on
+    (1, 64, 64, 5564, S70, True), (1, 64, 64, 20064, S70, False), (1, 64, 64, 131136, S70, False),
+    (1, 256, 256, 5500, W64, True), (1, 256, 256, 100256, S70, False), (4, 236, 59, 41558, S70, False),
+    # ... and the same from about 24 query tiles on
+    (1, 1024, 1024, 33024, S70, True), (4, 512, 128, 100128, F8, True),
+    # chunks that leave most of a 256-column tile empty
+    (64, 320, 5, 12005, W64, False), (64, 2368, 37, 6000, (12, 3, 64), False), (32, 1536, 48, 12048, (6, 2, 128), False),
+    # many query tiles: what counts is the longest one against a CU's share
+    (32, 13619, 512, 8704, S70, True), (33, 14100, 512, 8704, S70, True), (76, 9272, 122, 30976, (12, 3, 64), True),
+    (75, 4240, 110, 1700, S70, False), (134, 12000, 110, 1710, S70, False), (138, 40000, 400, 3200, S70, False),
+])
+def test_which_batches_take_the_form(library, batch, tokens, mq, mkv, heads, cut):
+    assert (library.form_slots(batch, tokens, mq, mkv, heads[0], heads[1]) > 0) == cut
