@@ -91,6 +91,9 @@ inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, b
 // 4887 keys 99 and 87; 286 of up to 3245 101 and 82), and beyond the last number heaviest first evens them out alone.
 constexpr int kCutNoPrefixItems = 240, kCutNoPrefixMost = 448, kCutNoPrefixKeys = 3072;
 
+// Up to this many items on fewer keys the pieces of 128 columns serve nearly as well, and the form is not worth its workspace.
+constexpr int kCutFewItems = 8, kCutFewKeys = 4096;
+
 // Whether the key tiles of a sequence of up to max_q_len new and max_kv_len visible keys stay within what cut_limit's
 // sum can hold.  Beyond that its limit is too small: it cuts into more pieces than it should.
 inline bool cut_countable(long max_q_len, int tpt, long max_kv_len) {
@@ -109,6 +112,7 @@ inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len,
     if (max_kv_len <= max_q_len) {
       if (items < kCutNoPrefixItems || items > kCutNoPrefixMost || max_kv_len < kCutNoPrefixKeys) return 0;
     } else {
+      if (items <= kCutFewItems && max_kv_len < kCutFewKeys) return 0;
       const long wg128 = estimate_wg128(rows, batch, num_q_heads / cols);
       const int by_hints = kv_pieces(wg128, max_kv_len), cap = kv_split_cap(rows);
       const int pieces = by_hints < 1 ? 1 : by_hints < cap ? by_hints : cap;
