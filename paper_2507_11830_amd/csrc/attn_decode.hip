@@ -256,14 +256,13 @@ __global__ __launch_bounds__(64, NT > 1 ? 1 : 2) void decode_split_kernel(Decode
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const char *qrow = a.q + row_col[nt] * (D * 2);
+    if (col_valid[nt]) {  // one branch around all of them: with a branch per load the launch takes 2 to 4 % longer
 #pragma unroll
-    for (int s = 0; s < G::kDSteps; ++s) {
-      if (col_valid[nt]) {
-        qreg[nt][s] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * s + 16 * half);
-      } else {
-        u32x4 z = {0, 0, 0, 0};
-        qreg[nt][s] = *reinterpret_cast<bf16x8 *>(&z);
-      }
+      for (int s = 0; s < G::kDSteps; ++s) qreg[nt][s] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * s + 16 * half);
+    } else {
+      u32x4 z = {0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < G::kDSteps; ++s) qreg[nt][s] = *reinterpret_cast<bf16x8 *>(&z);
     }
   }
   // this step's new K/V row, one 16-byte chunk per lane (64 / CPR copies of the row per wave);
@@ -418,11 +417,15 @@ __global__ __launch_bounds__(64, NT > 1 ? 1 : 2) void decode_split_kernel(Decode
       // range take the chunk's last row: finite, and masked.  At most two blocks of a sequence
       // reach into its chunk, so the extra round trip is paid once or twice per sequence.
       const int tok0 = a.cu_q[seq];
-      const int c = lane % CPR;
+      // Computed anew for every block: hoisted out of the loop, the offsets of a rare block would hold 16 registers (with two
+      // column tiles the kernel then keeps others in scratch memory, and reloads them for every block).
+      int ln = lane;
+      asm("" : "+v"(ln));
+      const int c = ln % CPR;
       const bool writer = head0 % a.group == 0;
 #pragma unroll
       for (int j = 0; j < 32 * CPR / 64; ++j) {
-        const int row = j * (64 / CPR) + lane / CPR;
+        const int row = j * (64 / CPR) + ln / CPR;
         const int pos = base + row;
         // page of this position, from the lane that holds it: taken by all lanes, outside the
         // branch (a cross-lane read must not depend on which lanes the branch leaves active)

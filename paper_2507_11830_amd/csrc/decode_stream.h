@@ -184,11 +184,15 @@ __device__ __forceinline__ void row_segment(const DecodeArgs &a, lds_char *smem,
       // Rows of this block at positions >= ctx are not in the cache yet: every lane fetches its 16-byte
       // pieces of the new rows, patches the block in LDS and, for positions of the row, stores them to their
       // pages.  Rows past the end take the chunk's last row.
-      const int c = lane % CPR;
+      // Computed anew for every block: hoisted out of the loop, the offsets of a rare block would hold 16 registers (with two
+      // column tiles the kernel then keeps others in scratch memory, and reloads them for every block).
+      int ln = lane;
+      asm("" : "+v"(ln));
+      const int c = ln % CPR;
       const int pages_i = i + 1 < nb && ((i + 1) & 31) == 0 ? pages_before : pages;  // block i + 1 may have moved on to its 32 page ids
 #pragma unroll
       for (int j = 0; j < 32 * CPR / 64; ++j) {
-        const int row = j * (64 / CPR) + lane / CPR;
+        const int row = j * (64 / CPR) + ln / CPR;
         const int pos = base + row;
         const int pg = __shfl(pages_i, 2 * (i & 31) + (row >> 4));  // by all lanes: a cross-lane read must not sit in the branch
         if (pos >= ctx) {
