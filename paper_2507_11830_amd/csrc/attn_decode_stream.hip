@@ -199,10 +199,6 @@ int plan_decode_stream(DecodeArgs &a, int batch, int max_q, int tiles, int max_l
   const long rows = (long)batch * a.n_hgroups;
   const bool mq = a.cu_q != nullptr;
   if (rows > 65535) return 1;
-  // Single tokens on little data (up to 32 MB of K at most) and middling lengths: one wave per 128 keys writes its
-  // partial without the merge's barriers, and its combine pass is not long yet (16 sequences of
-  // 512..8192 keys at 8q/1kv: 13.0 us against 13.8; from 32 such sequences on, 20.8 against 19.4).
-  if (form == 0 && !mq && max_len > 512 && max_len <= 8192 && rows * max_len * head_dim <= 8192L * 16 * 128) return 1;
   a.batch = batch;
   a.hg_per_kv = a.group / a.geff;
   a.q_max = max_q;
@@ -221,6 +217,7 @@ int plan_decode_stream(DecodeArgs &a, int batch, int max_q, int tiles, int max_l
   while (chunk <= 1024 && rows * ((max_len + chunk - 1) / chunk) > resident && (max_len > 512 || form != 0)) chunk += 128;
   long splits = (max_len + chunk - 1) / chunk;
   if (chunk > 1024 || form == 2 || (splits > 1 && ws < rows * splits * slot_bytes)) splits = 0;
+  if (form == 0 && !mq && one_wave_pays(rows, a.geff, max_len, head_dim, splits, resident)) return 1;
   // Equal shares: a partial slot per (workgroup, row) pair along the concatenated rows, and the table of rows.
   const size_t tab = (size_t)(rows * 8 + 15) / 16 * 16;
   const long least = kMinShare + kRowCost;

@@ -17,6 +17,7 @@ def plan(tmp_path_factory):
                     os.path.join(ROOT, "tests", "share_plan_host.cpp"), "-o", so], check=True)
     L = ctypes.CDLL(so)
     L.share_of.argtypes = [ctypes.c_int, ctypes.c_long]
+    L.one_wave.argtypes = [ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_long]
     return L
 
 
@@ -37,3 +38,17 @@ def test_rows_count_partials_of_launched_workgroups_only(plan, wgs, lens):
     for end, n in zip(ends, lens):
         first_wg = (int(end) - (n + 31) // 32) // share  # of the row's first key block
         assert first_wg + plan.pieces_of(int(end), share, first_wg) <= wgs
+
+
+@pytest.mark.parametrize("rows,geff,longest,d,splits,wave", [
+    # many rows of a single short split, and of a few with one head per KV head
+    (1024, 1, 128, 128, 1, True), (3752, 1, 121, 128, 1, True), (2048, 5, 66, 128, 1, True), (704, 4, 109, 128, 1, False),
+    (2676, 1, 95, 64, 1, True), (1024, 8, 128, 64, 1, False), (1024, 1, 300, 128, 1, True), (1024, 4, 300, 128, 1, False),
+    (1024, 1, 512, 128, 1, False), (128, 8, 100, 128, 1, False),
+    # little data against shares and rounds that are not full
+    (300, 8, 600, 128, 0, True), (200, 4, 1500, 64, 2, True), (256, 8, 900, 128, 1, False), (256, 4, 1500, 64, 2, False),
+    (512, 8, 600, 128, 0, False), (384, 1, 900, 128, 0, True), (512, 2, 1849, 64, 0, True), (1024, 4, 1500, 128, 0, False),
+    (16, 8, 8192, 128, 16, True), (64, 8, 8192, 128, 0, False), (2, 8, 16384, 128, 64, False),
+])
+def test_which_batches_stay_with_one_wave_splits(plan, rows, geff, longest, d, splits, wave):
+    assert plan.one_wave(rows, geff, longest, d, splits) == wave
