@@ -64,18 +64,19 @@ inline long estimate_wg128(long rows, int batch, long n_hgroups) { return rows /
 // heads in the column dimension) per head group on average, `streams` head groups of all sequences, keys up to
 // max_kv_len.  narrow: the launch has 128-column workgroups otherwise, in kv_pieces pieces each (else whole 256-column ones).
 // Times are compared in key tiles of a workgroup.  The lengths are not known here: a sequence is taken to be 0.6 of the
-// longest (one alone: all of it), and what a whole launch waits for beyond the mean load of a CU to be 0.2 and 0.4 of its
-// longest item; the form itself costs a merge and the search, 4 and 8 tiles.  The numbers are those that leave the least
-// behind on 420 batches (equal, uniform, cubed and lognormal lengths, 1..200 sequences, 40..8192 columns, up to 60000
-// keys, nine head shards; both forms timed): 14.4 % of the time is gained over never cutting, 14.7 % with hindsight; 20 batches lose
-// more than 3 %, 8 % on average, 20 % at most (5 chunks of up to 741 tokens at 16q/2kv).  Both sides of it:
+// longest (narrow) or 0.4 (one alone: all of it), and what a whole launch waits for beyond the mean load of a CU to be 0.2 or
+// 0.4 of its longest item; the form itself costs a merge and the search, 4 tiles more than the pieces of the narrow form
+// and 20 in place of whole items (5-8 us even where the device finds nothing to cut).  The numbers are those that leave the
+// least behind on 430 batches (equal, uniform, cubed and lognormal lengths, 1..200 sequences, 40..8192 columns, up to
+// 60000 keys, nine head shards; both forms timed): 12.8 % of the time is gained over never cutting, 20 batches lose more than 3 %, 9 % on
+// average and 26 % at most (5 chunks of up to 741 tokens at 16q/2kv).  Both sides of it:
 //   1 x 64 tokens on 20000 keys, 8q/1kv: 30.4 us in 13 pieces of 128 columns, 39.6 cut; on 5500 keys 28.4 and 21.9 (an item
 //   has kMaxCutPieces at most, each walked by one workgroup, where two wave groups share the narrow form's);
 //   64 x 37 tokens of up to 6000 keys, 12q/3kv (columns for 1.2 tiles of 256): 92.6 and 124.5;
 //   32 chunks of 512 tokens on up to 8192 keys: 164 whole, 106 cut; 549 items, longest 484 tiles: 518 and 359; 600 items, longest
 //   27 tiles: 61.6 and 69 (nothing to gain: all items are short next to what a CU does).
 inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, bool narrow, int kv_pieces) {
-  const double tiles = (double)((max_kv_len + 63) / 64), mean = batch == 1 ? 1.0 : 0.6;
+  const double tiles = (double)((max_kv_len + 63) / 64), mean = batch == 1 ? 1.0 : narrow ? 0.6 : 0.4;
   const double share = streams * (double)(long)((columns + 255.99) / 256) * tiles * mean / kCutShare;
   double cut = 1.25 * share;
   if (cut < tiles / kMaxCutPieces) cut = tiles / kMaxCutPieces;
@@ -83,7 +84,7 @@ inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, b
   const double longest = narrow ? tiles / (2 * kv_pieces) : tiles;
   const double load = narrow ? 1.1 * streams * (double)(long)((columns + 127.99) / 128) * tiles * mean / (2 * kCutShare) + 0.2 * longest
                              : share + 0.4 * longest;
-  return cut + (narrow ? 4 : 8) < (load > longest ? load : longest);
+  return cut + (narrow ? 4 : 20) < (load > longest ? load : longest);
 }
 
 // Batches without cached prefixes hold items of all lengths and few long ones; the 128-column form or the plain order is as

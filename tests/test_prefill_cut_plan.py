@@ -107,6 +107,7 @@ S70, F8, W64 = (8, 1, 128), (32, 8, 128), (16, 2, 64)
     (64, 320, 5, 12005, W64, False), (64, 2368, 37, 6000, (12, 3, 64), False), (32, 1536, 48, 12048, (6, 2, 128), False),
     # many query tiles: what counts is the longest one against a CU's share
     (32, 13619, 512, 8704, S70, True), (33, 14100, 512, 8704, S70, True), (76, 9272, 122, 30976, (12, 3, 64), True),
+    (24, 12288, 512, 4312, S70, False), (3, 3072, 1024, 4324, F8, False),  # of one length: up to 5 % slower cut
     (75, 4240, 110, 1700, S70, False), (134, 12000, 110, 1710, S70, False), (138, 40000, 400, 3200, S70, False),
 ])
 def test_which_batches_take_the_form(library, batch, tokens, mq, mkv, heads, cut):
