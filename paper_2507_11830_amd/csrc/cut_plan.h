@@ -87,10 +87,17 @@ inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, b
   return cut + (narrow ? 4 : 20) < (load > longest ? load : longest);
 }
 
-// Batches without cached prefixes hold items of all lengths and few long ones; the 128-column form or the plain order is as
-// good up to this many items or keys (201 items of up to 3484 keys 58 us, cut 63; 258 of 2048 keys 60 and 68; 253 of up to
-// 4887 keys 99 and 87; 286 of up to 3245 101 and 82), and beyond the last number heaviest first evens them out alone.
-constexpr int kCutNoPrefixItems = 240, kCutNoPrefixMost = 448, kCutNoPrefixKeys = 3072;
+// Whether a batch without cached prefixes takes it: its items are of all lengths already, so that few are long next to a CU's
+// share.  Not below kCutNoPrefixItems or kCutNoPrefixKeys (201 items of up to 3484 keys 58 us, cut 63; 258 of 2048 60 and 68), not
+// where the 128-column form serves sequences of one length (257 items, 4097 tokens at 16q/2kv d 64: 52 and 64; of
+// different lengths 99 and 87), and beyond 390 items, where heaviest first evens them out alone, only for different lengths
+// (412 items, 4 x 3281 at 8q/1kv: 102 and 108; filled 0.45 of the longest, 431 items: 305 and 198).  In between: 9 to 36 % faster.
+constexpr int kCutNoPrefixItems = 240, kCutNoPrefixEvenMost = 390, kCutNoPrefixMost = 448, kCutNoPrefixKeys = 3072;
+inline bool cut_pays_no_prefix(long items, int batch, long total_q, long max_q_len, long max_kv_len, bool narrow) {
+  if (items < kCutNoPrefixItems || items > kCutNoPrefixMost || max_kv_len < kCutNoPrefixKeys) return false;
+  const long full = batch * max_q_len;
+  return narrow ? 20 * total_q < 19 * full : items <= kCutNoPrefixEvenMost || 10 * total_q < 9 * full;
+}
 
 // Up to this many items on fewer keys the pieces of 128 columns serve nearly as well, and the form is not worth its workspace.
 constexpr int kCutFewItems = 8, kCutFewKeys = 4096;
@@ -110,11 +117,11 @@ inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len,
   const long items = rows / 256 + (streams + 1) / 2, most = rows / 256 + streams;
   if (most > (1 << 20) || !cut_countable(max_q_len, 256 / cols, max_kv_len)) return 0;
   if (!forced) {
+    const long wg128 = estimate_wg128(rows, batch, num_q_heads / cols);
     if (max_kv_len <= max_q_len) {
-      if (items < kCutNoPrefixItems || items > kCutNoPrefixMost || max_kv_len < kCutNoPrefixKeys) return 0;
+      if (!cut_pays_no_prefix(items, batch, total_q, max_q_len, max_kv_len, is_small_grid(wg128))) return 0;
     } else {
       if (items <= kCutFewItems && max_kv_len < kCutFewKeys) return 0;
-      const long wg128 = estimate_wg128(rows, batch, num_q_heads / cols);
       const int by_hints = kv_pieces(wg128, max_kv_len), cap = kv_split_cap(rows);
       const int pieces = by_hints < 1 ? 1 : by_hints < cap ? by_hints : cap;
       if (!cut_pays(batch, streams, (double)total_q * cols / batch, max_kv_len, is_small_grid(wg128), pieces)) return 0;

@@ -109,6 +109,9 @@ S70, F8, W64 = (8, 1, 128), (32, 8, 128), (16, 2, 64)
     (32, 13619, 512, 8704, S70, True), (33, 14100, 512, 8704, S70, True), (76, 9272, 122, 30976, (12, 3, 64), True),
     (24, 12288, 512, 4312, S70, False), (3, 3072, 1024, 4324, F8, False),  # of one length: up to 5 % slower cut
     (75, 4240, 110, 1700, S70, False), (134, 12000, 110, 1710, S70, False), (138, 40000, 400, 3200, S70, False),
+    # without prefixes: one length, different lengths, on small grids and on full ones
+    (1, 4097, 4097, 4097, W64, False), (1, 8183, 8183, 8183, S70, False), (2, 8200, 4887, 4887, S70, True),
+    (1, 9560, 9560, 9560, S70, True), (4, 13124, 3281, 3281, S70, False), (2, 12704, 8250, 8250, S70, True),
 ])
 def test_which_batches_take_the_form(library, batch, tokens, mq, mkv, heads, cut):
     assert (library.form_slots(batch, tokens, mq, mkv, heads[0], heads[1]) > 0) == cut
