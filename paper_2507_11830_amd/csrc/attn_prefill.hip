@@ -185,9 +185,11 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
   // 0.9 of the batch's longest: the XCDs with the longer ones finish last.  8 sequences of up to 7473 tokens, 8q/1kv
   // d 128, filled 0.62: 646 us, ranked 336; 8 of up to 1868, 16q/2kv d 64, 0.73: 75 and 53; 8 of up to 2853, 12q/3kv d 64,
   // 0.75: 94 and 87; filled 0.94 and more: 2 to 9 % slower ranked (the search, and K/V tiles from other XCDs' L2s).
-  // Below 512 tokens the search's microsecond shows (35.6 us, ranked 38.2).
+  // Below 512 tokens the search's microsecond shows (35.6 us, ranked 38.2), and where the longest sequences together give
+  // an XCD no more workgroups than its 32 CUs there is nothing to even out (8 of up to 985 at 2q/1kv d 64: 14.7 and 15.6).
   const long streams = (long)batch * a.n_hgroups;
-  const bool uneven = a.n_hgroups % 8 != 0 && streams % 8 == 0 && max_q_len >= 512 && 10L * total_q < 9L * batch * max_q_len;
+  const bool uneven = a.n_hgroups % 8 != 0 && streams % 8 == 0 && max_q_len >= 512 && 10L * total_q < 9L * batch * max_q_len &&
+                      streams / 8 * (((long)max_q_len << a.gshift) / 128) > 32;
   a.ranked = can_rank && (g_order_mode == 0 ? batch >= 2 && (max_kv_len > max_q_len || uneven) : g_order_mode == 2);
   a.rank_shift = 6;
   while (a.rank_shift < 24 && (max_kv_len >> a.rank_shift) > 63) ++a.rank_shift;
