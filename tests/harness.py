@@ -28,6 +28,37 @@ def bits_of(t) -> np.ndarray:
     return t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
 
 
+def kernel_launches(call):
+    """(grid, block) of the kernels that a call of the library enqueues, read from a capture of it (which is not run).  The
+    call has been made once before."""
+    import ctypes
+
+    import torch
+
+    class NodeParams(ctypes.Structure):  # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("smem", ctypes.c_uint)]
+
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            call()
+    torch.cuda.current_stream().wait_stream(side)
+    with open("/proc/self/maps") as f:  # the runtime that is loaded
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    found = []
+    for node in nodes:
+        p = NodeParams()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0  # the library enqueues kernels only
+        found.append((tuple(p.grid), tuple(p.block)))
+    return found
+
+
 class GpuRunner:
     """Owns the device cache of a workload and feeds steps to the library."""
 

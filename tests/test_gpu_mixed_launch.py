@@ -3,7 +3,7 @@ workgroups, more decoding sequences than one per lane, rows in many shares, and 
 import numpy as np
 import pytest
 
-from harness import TOL, GpuRunner, OracleRunner, bits_of, dev_i32, report_err, to_dev
+from harness import TOL, GpuRunner, OracleRunner, bits_of, dev_i32, kernel_launches, report_err, to_dev
 from test_gpu_parity import custom_workload, run_chunk_steps, run_full_compare
 
 pytestmark = pytest.mark.gpu
@@ -17,7 +17,7 @@ CASES = {
     "most-sequences": (8, 2, 64, [1] * 255 + [200], list(RNG.integers(0, 300, 256))),
     "long-rows": (8, 1, 128, [1, 90, 4], [20000, 77, 9000]),
     "no-keys-before": (8, 1, 64, [1, 0, 500, 1, 0, 2], [0, 40, 60, 0, 0, 0]),
-    "odd-group": (6, 2, 128, [1, 200, 33, 1], [800, 100, 2000, 31]),
+    "odd-group": (6, 2, 128, [1, 200, 20, 1], [800, 100, 2000, 31]),  # the halves have 6 and 2 head groups; 20 tokens are too many for the decode half
 }
 
 
@@ -28,6 +28,28 @@ def test_mixed_launch(case):
     w = custom_workload(f"mixed-launch-{case}", ctx + new, ctx, Hq, Hkv, d, "prefill", seed=311)
     run_full_compare(w, check_cache=False)
     run_chunk_steps(w)
+    # one launch of both halves, then the merge over the decode half's rows
+    found = launches(w, new, ctx)
+    assert [block[0] for _, block in found][:1] == [512] and len(found) == 2, found
+    assert found[1][0][:2] == (32 // min(Hq // Hkv, 32) * (Hq // Hkv), w.batch * Hkv), found
+
+
+def launches(w, new, ctx):
+    import torch
+
+    import paper_2507_11830_amd as sp
+
+    g = GpuRunner(w)
+    for st in w.steps():
+        g.append(st)
+    q, cu, cx = to_dev(st.q), dev_i32(st.cu_new), dev_i32(st.ctx_lens)
+    mq, mkv = int(new.max()), int((new + ctx).max())
+    ws = torch.empty(sp.sp_attn_prefill_workspace_size(w.batch, q.shape[0], mq, mkv, w.Hq, w.Hkv, w.d), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(q)
+    call = lambda: sp.sp_attn_prefill(g.cache, q, out, cu, cx, g.bt, mq, mkv, float(w.scale), workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    return kernel_launches(call)
 
 
 def test_mixed_launch_in_a_graph():
