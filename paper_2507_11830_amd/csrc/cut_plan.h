@@ -127,7 +127,9 @@ inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len,
       if (!cut_pays(batch, streams, (double)total_q * cols / batch, max_kv_len, is_small_grid(wg128), pieces)) return 0;
     }
   }
-  const long by_len = most * (forced ? kMaxCutPieces : (max_kv_len + 64 * kMinCutTiles - 1) / (64 * kMinCutTiles));
+  // an item has ceil(tiles / kMinCutTiles) pieces at most, and kMaxCutPieces
+  const long by_tiles = (max_kv_len + 64 * kMinCutTiles - 1) / (64 * kMinCutTiles);
+  const long by_len = most * (forced || by_tiles > kMaxCutPieces ? kMaxCutPieces : by_tiles);
   return (int)(by_len < kMostCutSlots ? by_len : kMostCutSlots);
 }
 

@@ -75,6 +75,22 @@ def test_very_long_contexts(plan, hq, hkv, ctx, new):
     check(plan(hq, hkv, [700, ctx, 0, 30000], [64, new, 900, 1]))
 
 
+@pytest.mark.parametrize("batch,tokens,mq,mkv,heads", [(1, 64, 64, 5564, (8, 1)), (2, 96, 60, 9000, (8, 1)), (1, 512, 512, 33280, (16, 2)), (4, 512, 128, 100128, (32, 8))])
+def test_slots_are_what_the_pieces_need(library, plan, batch, tokens, mq, mkv, heads):
+    """No more slots than kMaxCutPieces of every item there may be, and enough for the search on any lengths of these hints."""
+    slots = library.form_slots(batch, tokens, mq, mkv, *heads)
+    items = tokens * heads[0] // 256 + batch * heads[1]
+    assert 0 < slots <= min(SLOTS, 16 * items)
+    rng = np.random.default_rng(mkv)
+    for _ in range(50):
+        new = rng.multinomial(tokens - batch, [1 / batch] * batch) + 1 if batch > 1 else np.array([tokens])
+        new = np.minimum(new, mq)
+        ctx = rng.integers(0, mkv - new + 1)
+        ctx[rng.integers(batch)] = mkv - mq
+        unlimited, limited = plan(*heads, ctx, new, SLOTS), plan(*heads, ctx, new, slots)
+        assert unlimited[2] == limited[2] <= slots and unlimited[0] == limited[0] <= limited[1]
+
+
 def test_few_slots_and_wrong_hints(plan):
     """Fewer slots than pieces, or fewer workgroups than items: nothing is cut then rather than dropped."""
     for slots in (0, 1, 7, 60):
