@@ -10,18 +10,6 @@ constexpr int kMaxSeqs = kMaxShareSeqs;
 
 typedef __attribute__((address_space(3))) int32_t lds_int;
 
-// Inclusive prefix sum over the 64 lanes (gfx9 DPP: shifts inside rows of 16, then the two row
-// broadcasts).
-__device__ __forceinline__ int scan_incl(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
-  return x;
-}
-
 // Page ids of the blocks i0 .. i0 + 31 of wave w in a segment that begins at the row's block p0: two per block,
 // one per lane; -1 past the table row.  Bad metadata must not become a wild access: loads go through the clamped
 // id, the fused-append stores through the raw one and are skipped when it lies outside the pool (the
@@ -325,7 +313,7 @@ __device__ __forceinline__ void decode_share(const DecodeArgs &a, lds_char *smem
       }
       wt = weight(len, qn);
     }
-    const int end = total + scan_incl(wt * a.n_hgroups);
+    const int end = total + wave_scan_incl(wt * a.n_hgroups);
     total = __builtin_amdgcn_readlane(end, 63);
     s_end[s] = end;
     s_len[s] = len;
