@@ -39,8 +39,8 @@ PEAK_HBM_GBPS = 8000.0      # MI355X HBM3E, published
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this file, scaled by
 # what the same counters read for the 1 GiB copy of `--workload copy` (FETCH_SIZE x2.000,
 # WRITE_SIZE x1.000); figures and commands in profiles/pmc_hbm_traffic_and_mfma.md.
-TRAFFIC_PREFILL_C5A = int(359105.0 * 1024 * 2.0 + 65852.2 * 1024)
-TRAFFIC_DECODE_C3 = int((68028.5 + 3678.5) * 1024 * 2.0 + (3889.6 + 128.0) * 1024)
+TRAFFIC_PREFILL_C5A = int(340519.1 * 1024 * 2.0 + 65864.8 * 1024)
+TRAFFIC_DECODE_C3 = int((67725.9 + 688.0) * 1024 * 2.0 + (1202.2 + 122.0) * 1024)
 
 
 def _dev_bf16(u16):
@@ -690,7 +690,7 @@ def main():
                      "median": long_job.flops / t_pre["median"] / 1e9, "best": long_job.flops / t_pre["min"] / 1e9},
         "roofline_decode": {"bound": "hbm", "achieved": gbps, "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                             "frac": gbps / PEAK_HBM_GBPS, "traffic": TRAFFIC_DECODE_C3,
-                            "kernel": "decode_split_kernel + combine_kernel", "workload": "C3 cold",
+                            "kernel": "decode_stream_kernel + combine_rows_kernel", "workload": "C3 cold",
                             "algorithmic_bytes": dec.bytes,
                             "median": dec.bytes / t_dec["median"] / 1e6, "best": dec.bytes / t_dec["min"] / 1e6},
         "decode_warm": {"ms": warm, "GBps": dec.bytes / warm["mean"] / 1e6,

@@ -106,10 +106,10 @@ int sp_kv_append(const sp_cache_desc *cache, const void *k_new, const void *v_ne
  *                   sp_attn_prefill_workspace_size(...) bytes the library may cut long key
  *                   ranges into pieces computed by separate workgroups and merged by a
  *                   log-sum-exp combine pass, which it does for batches of few query tokens on
- *                   long cached prefixes, and for batches of a few hundred 256-row query tiles
- *                   whose key ranges may differ a lot (only the ranges that the lengths on the
- *                   device show to be long are cut then); with NULL / 0 (or less than that) it
- *                   uses fewer pieces or none.  The result is the same up to fp32 summation order.
+ *                   long cached prefixes, and for batches where the hints let it expect a few
+ *                   256-row query tiles with key ranges much longer than the others (only the
+ *                   ranges that the lengths on the device show to be long are cut then); with
+ *                   NULL / 0 (or less than that) it uses fewer pieces or none.  The result is the same up to fp32 summation order.
  *                   Batches whose chunks are all a few tokens long (max_q_len times the query
  *                   heads per KV head <= 32, for some shapes <= 64: the verification step of
  *                   speculative decoding) are served, when the workspace allows, by the decode
@@ -148,7 +148,8 @@ int sp_attn_prefill(const sp_cache_desc *cache, const void *q, void *out,
  *                   a sequence with seq_lens[s] == 0 gets an all-zero output row
  *   max_seq_len     host hint: >= max seq_lens[s] (sizes the split grid and the workspace)
  *   workspace       device scratch of at least sp_attn_decode_workspace_size(...) bytes for
- *                   the per-split partial results; contents need no initialisation
+ *                   the per-split partial results; contents need no initialisation, and more
+ *                   than that changes nothing
  */
 int sp_attn_decode(const sp_cache_desc *cache, const void *q, void *out,
                    const int32_t *seq_lens, const int32_t *block_table, int32_t batch,
@@ -305,7 +306,9 @@ int sp_debug_validate_hints(const int32_t *cu_seqlens, const int32_t *lens, int3
  *   "prefill_order" which work item (sequence, query tile) a prefill workgroup takes: 0 (built-in
  *                   choice), 1 (by launch index: last query tiles of all sequences first), 2 (the
  *                   workgroup with the r-th launch index takes the r-th heaviest item; batches of
- *                   up to 256 sequences).  Same result bit for bit.
+ *                   up to 256 sequences).  1 and 2 give the same result bit for bit; with 0 long
+ *                   items may also be cut and mixed batches may share a launch, which 1 and 2
+ *                   switch off: the same up to fp32 summation order.
  *   "prefill_short_chunk" 0 (built-in choice: batches of short chunks go to the decode
  *                   kernels when the workspace allows) or 1 (never; always the prefill kernel).
  *                   Changes what sp_attn_prefill_workspace_size returns.

@@ -27,9 +27,9 @@
 //
 // Bound: HBM bandwidth, 4 * head_dim bytes per cached token per KV head; on small batches the chain of memory round
 // trips.  Measured (split + combine, one-wave splits of fixed length before -> here): 64 sequences of 512..8192 keys,
-// 8q/1kv, d 128: 37.5 -> 31.9 us (the key loop moves 157 MB in 20 us; 5 us pass before the first block is there, 3 us
-// in the tail and the merge); 128 sequences of 1024..16384 keys, 32q/8kv (4.9 GB): 803 -> 728 us (6.7 TB/s);
-// 64 x 4 query tokens: 35.4 -> 31.1 us; one sequence of 32900 keys: 12.5 -> 11.6 us; one of 137 keys: 11.2 -> 7.5 us.
+// 8q/1kv, d 128: 37.5 -> 31.5 us (157 MB; a batch of 138 MB, all read once: kernel 25.6 us, 5.4 TB/s with the ramp to the first
+// block and the tail, merge 4.2); 128 sequences of 1024..16384 keys, 32q/8kv (4.9 GB): 808 -> 734 us (6.7 TB/s);
+// 64 x 4 query tokens: 35.5 -> 31.1 us; one sequence of 32900 keys: 12.5 -> 11.6-12.1 us; one of 137 keys: 10 -> 7.3 us.
 #include "decode_stream.h"
 
 namespace sp {
