@@ -229,7 +229,7 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
       if (rc != 1) return rc;
     }
   }
-  int rc = a.cut_slots > 0 ? launch_prefill_cut(a, c.head_dim, batch, max_q_len, stream)
+  int rc = a.cut_slots > 0 ? launch_prefill_cut(a, c.head_dim, batch, max_q_len, cut_merge_groups(batch, total_q, max_kv_len, num_q_heads, a.n_hgroups, g_cut_mode == 2), stream)
            : c.head_dim == 128 ? launch_prefill_d<128>(a, split, batch, max_q_len, stream)
                              : launch_prefill_d<64>(a, split, batch, max_q_len, stream);
   if (rc != SP_OK) return rc;

@@ -17,6 +17,9 @@ namespace sp {
 // where a slot is the first of an item, adds the item's pieces: wave v the channels v * D/4 .. in the lane
 // order of the prefill kernel's accumulators, so that loads are 1 KiB in a row.  The kernel is a chain of
 // memory round trips: one for the table (all of the workgroup's entries together), then one per item and four pieces.
+// (How the workgroups that have work fall on the CUs changes with the launch's width by up to 4 us for small batches, without a
+// rule: 16 items of 7 pieces, one head group, 119 wide 26.2 us, 121 wide 29.8; 6 of 16, 162 wide 26.9, 144 wide 35.8.  The width
+// is that of a piece per kMinCutTiles key tiles, which was the best of those tried on most batches.)
 constexpr int kCombineGroups = 208;
 template <int D>
 __global__ __launch_bounds__(256) void cut_combine_kernel(PrefillArgs a) {
@@ -91,18 +94,18 @@ __global__ __launch_bounds__(256) void cut_combine_kernel(PrefillArgs a) {
 }
 
 template <int D>
-static int launch_cut_d(const PrefillArgs &a, int batch, int max_q_len, hipStream_t stream) {
+static int launch_cut_d(const PrefillArgs &a, int batch, int max_q_len, int groups, hipStream_t stream) {
   static bool set = false;
   int rc = launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 1>, &set, kPrefillSmem<D>, 256, a, batch, max_q_len, stream);
   if (rc != SP_OK) return rc;
-  hipLaunchKernelGGL(cut_combine_kernel<D>, dim3((unsigned)(a.cut_slots < kCombineGroups ? a.cut_slots : kCombineGroups), 8), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(cut_combine_kernel<D>, dim3((unsigned)(groups < kCombineGroups ? groups : kCombineGroups), 8), dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SP_ERR_HIP, "prefill combine launch: %s", hipGetErrorString(e));
   return SP_OK;
 }
 
-int launch_prefill_cut(const PrefillArgs &a, int head_dim, int batch, int max_q_len, hipStream_t stream) {
-  return head_dim == 128 ? launch_cut_d<128>(a, batch, max_q_len, stream) : launch_cut_d<64>(a, batch, max_q_len, stream);
+int launch_prefill_cut(const PrefillArgs &a, int head_dim, int batch, int max_q_len, int groups, hipStream_t stream) {
+  return head_dim == 128 ? launch_cut_d<128>(a, batch, max_q_len, groups, stream) : launch_cut_d<64>(a, batch, max_q_len, groups, stream);
 }
 
 }  // namespace sp

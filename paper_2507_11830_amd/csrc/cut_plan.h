@@ -108,6 +108,9 @@ inline bool cut_countable(long max_q_len, int tpt, long max_kv_len) {
   return (max_q_len + tpt - 1) / tpt * (max_kv_len / 64 + 1) <= kMostSeqTiles;
 }
 
+inline long cut_pieces_by_tiles(int max_kv_len) { return (max_kv_len + 64 * kMinCutTiles - 1) / (64 * kMinCutTiles); }
+inline int cut_cap(long slots) { return (int)(slots < kMostCutSlots ? slots : kMostCutSlots); }
+
 // Slots for partials of the form (0: not taken), from the hints; forced: wherever it can be computed.
 inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads, bool forced) {
   if (batch <= 0 || batch > 64 * kRankSlots || total_q <= 0 || max_kv_len > (1 << 24)) return 0;
@@ -128,9 +131,14 @@ inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len,
     }
   }
   // an item has ceil(tiles / kMinCutTiles) pieces at most, and kMaxCutPieces
-  const long by_tiles = (max_kv_len + 64 * kMinCutTiles - 1) / (64 * kMinCutTiles);
-  const long by_len = most * (forced || by_tiles > kMaxCutPieces ? kMaxCutPieces : by_tiles);
-  return (int)(by_len < kMostCutSlots ? by_len : kMostCutSlots);
+  const long pieces = forced ? kMaxCutPieces : cut_pieces_by_tiles(max_kv_len);
+  return cut_cap(most * (pieces < kMaxCutPieces ? pieces : kMaxCutPieces));
+}
+
+// Workgroups that the merge is wide: slots for a piece per kMinCutTiles key tiles, also where an item has fewer.
+inline int cut_merge_groups(int batch, int total_q, int max_kv_len, int num_q_heads, int n_hgroups, bool forced) {
+  const long most = (long)total_q * num_q_heads / 256 + (long)batch * n_hgroups;
+  return cut_cap(most * (forced ? kMaxCutPieces : cut_pieces_by_tiles(max_kv_len)));
 }
 
 // Workgroups of a ranked launch: every sequence has at most q_len / tpt + 1 query tiles, and the cut items add their

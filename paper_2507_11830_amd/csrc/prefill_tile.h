@@ -1160,8 +1160,8 @@ inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, cons
   return SP_OK;
 }
 
-// attn_prefill_cut.hip: the CUT form and its combine pass.
-int launch_prefill_cut(const PrefillArgs &a, int head_dim, int batch, int max_q_len, hipStream_t stream);
+// attn_prefill_cut.hip: the CUT form and its combine pass, which is `groups` workgroups wide (at least cut_slots, as far as it matters).
+int launch_prefill_cut(const PrefillArgs &a, int head_dim, int batch, int max_q_len, int groups, hipStream_t stream);
 struct DecodeArgs;
 // attn_mixed.hip: ranked prefill workgroups of 128 (split) or 256 columns and `shares` workgroups of the equal-share decode.
 int launch_mixed(const PrefillArgs &a, const DecodeArgs &d, int shares, int pieces, bool split, int head_dim, int batch, int max_q_len, hipStream_t stream);

@@ -7,6 +7,10 @@ int form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_
   return sp::cut_form_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, num_kv_heads, false);
 }
 
+int merge_groups(int batch, int total_q, int max_kv_len, int num_q_heads, int n_hgroups) {
+  return sp::cut_merge_groups(batch, total_q, max_kv_len, num_q_heads, n_hgroups, false);
+}
+
 int launched_workgroups(long total_q, int tpt, int batch, int n_hgroups, int slots) {
   return (int)sp::ranked_workgroups(total_q, tpt, batch, n_hgroups, 1, slots);
 }

@@ -81,6 +81,7 @@ def test_slots_are_what_the_pieces_need(library, plan, batch, tokens, mq, mkv, h
     slots = library.form_slots(batch, tokens, mq, mkv, *heads)
     items = tokens * heads[0] // 256 + batch * heads[1]
     assert 0 < slots <= min(SLOTS, 16 * items)
+    assert slots <= library.merge_groups(batch, tokens, mkv, heads[0], heads[1])  # the merge covers every slot
     rng = np.random.default_rng(mkv)
     for _ in range(50):
         new = rng.multinomial(tokens - batch, [1 / batch] * batch) + 1 if batch > 1 else np.array([tokens])
