@@ -54,10 +54,10 @@ static int mixed_route_cap(int batch, int total_q, int max_q_len, int num_q_head
 }
 
 // Slots for partials of the CUT form (0: not taken), from the host-side hints alone.
-static int cut_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads) {
+static int cut_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads, int head_dim) {
   // Mixed batches: their chunk is short next to what a launch costs (2048 tokens: 64.2 us against 63.7).
   if (g_cut_mode == 1 || (g_cut_mode == 0 && mixed_route_cap(batch, total_q, max_q_len, num_q_heads, num_kv_heads) > 0)) return 0;
-  return cut_form_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, num_kv_heads, g_cut_mode == 2);
+  return cut_form_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, num_kv_heads, head_dim, g_cut_mode == 2);
 }
 
 static size_t cut_bytes(int slots, int head_dim) {
@@ -74,7 +74,7 @@ size_t prefill_workspace_bytes(int batch, int total_q_tokens, int max_q_len, int
                                                                          num_q_heads, num_kv_heads, head_dim);
   if (mixed_route_cap(batch, total_q_tokens, max_q_len, num_q_heads, num_kv_heads) > 0)
     shortq = decode_routed_workspace_bytes(batch, max_kv_len, num_q_heads, num_kv_heads, head_dim);
-  const size_t cut = cut_bytes(cut_slots(batch, total_q_tokens, max_q_len, max_kv_len, num_q_heads, num_kv_heads), head_dim);
+  const size_t cut = cut_bytes(cut_slots(batch, total_q_tokens, max_q_len, max_kv_len, num_q_heads, num_kv_heads, head_dim), head_dim);
   const size_t most = pieces > shortq ? pieces : shortq;
   return cut > most ? cut : most;
 }
@@ -202,7 +202,7 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
   // Batches whose items may be of very different lengths: the CUT form.
   a.cut_slots = 0;
   {
-    const int slots = g_split_mode == 0 && g_kv_splits == 0 && g_order_mode == 0 ? cut_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, c.num_kv_heads) : 0;
+    const int slots = g_split_mode == 0 && g_kv_splits == 0 && g_order_mode == 0 ? cut_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, c.num_kv_heads, c.head_dim) : 0;
     if (slots > 0 && workspace && workspace_bytes >= cut_bytes(slots, c.head_dim)) {
       a.cut_slots = slots;
       a.kv_splits = kvs = 1;

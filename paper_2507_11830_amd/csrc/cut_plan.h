@@ -62,29 +62,33 @@ inline long estimate_wg128(long rows, int batch, long n_hgroups) { return rows /
 
 // Whether a batch on cached prefixes takes the form, from the hints: batch sequences of `columns` query columns (tokens x
 // heads in the column dimension) per head group on average, `streams` head groups of all sequences, keys up to
-// max_kv_len.  narrow: the launch has 128-column workgroups otherwise, in kv_pieces pieces each (else whole 256-column ones).
+// max_kv_len.  narrow: the launch has 128-column workgroups otherwise, in `pieces` pieces each (else whole 256-column ones).
 // Times are compared in key tiles of a workgroup.  The lengths are not known here: a sequence is taken to be 0.6 of the
 // longest (narrow) or 0.4 (one alone: all of it), and what a whole launch waits for beyond the mean load of a CU to be 0.2 or
-// 0.4 of its longest item; the form itself costs a merge and the search, 4 tiles more than the pieces of the narrow form
-// and 20 in place of whole items (5-8 us even where the device finds nothing to cut).  The numbers are those that leave the
-// least behind on 430 batches (equal, uniform, cubed and lognormal lengths, 1..200 sequences, 40..8192 columns, up to
-// 60000 keys, nine head shards; both forms timed): 12.8 % of the time is gained over never cutting, 20 batches lose more than 3 %, 9 % on
-// average and 26 % at most (5 chunks of up to 741 tokens at 16q/2kv).  Both sides of it:
+// 0.4 of its longest item.  Pieces by the hints leave partials of all rows, row_values each, which their merge reads; the
+// form itself costs a merge and the search, 4 tiles in place of the narrow form and 20 in place of whole items (5-8 us even
+// where the device finds nothing to cut).  The numbers are those that leave the least behind on 420 batches (equal, uniform,
+// cubed and lognormal lengths, 1..200 sequences, 40..8192 columns, up to 60000 keys, nine head shards; both forms timed):
+// 13.3 % of the time is gained over never cutting, 24 batches lose more than 3 %, 9 % on average and 25 % at most (5 chunks of
+// up to 741 tokens at 16q/2kv: 216-229 and 269 us).  Without the merge of the pieces by hints it was 12.8 %: 7 x 137 tokens on up
+// to 4660 keys at 16q/2kv 51.2 us in pieces, 30.6 cut; 13 chunks of up to 222 at 6q/2kv 50.3 and 33.0.
+// Both sides of it:
 //   1 x 64 tokens on 20000 keys, 8q/1kv: 30.4 us in 13 pieces of 128 columns, 39.6 cut; on 5500 keys 28.4 and 21.9 (an item
 //   has kMaxCutPieces at most, each walked by one workgroup, where two wave groups share the narrow form's);
 //   64 x 37 tokens of up to 6000 keys, 12q/3kv (columns for 1.2 tiles of 256): 92.6 and 124.5;
 //   32 chunks of 512 tokens on up to 8192 keys: 164 whole, 106 cut; 549 items, longest 484 tiles: 518 and 359; 600 items, longest
 //   27 tiles: 61.6 and 69 (nothing to gain: all items are short next to what a CU does).
-inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, bool narrow, int kv_pieces) {
+inline bool cut_pays(int batch, long streams, double columns, long max_kv_len, bool narrow, int pieces, double row_values) {
   const double tiles = (double)((max_kv_len + 63) / 64), mean = batch == 1 ? 1.0 : narrow ? 0.6 : 0.4;
   const double share = streams * (double)(long)((columns + 255.99) / 256) * tiles * mean / kCutShare;
   double cut = 1.25 * share;
   if (cut < tiles / kMaxCutPieces) cut = tiles / kMaxCutPieces;
   if (cut < kMinCutTiles) cut = kMinCutTiles;
-  const double longest = narrow ? tiles / (2 * kv_pieces) : tiles;
+  const double longest = narrow ? tiles / (2 * pieces) : tiles;
   const double load = narrow ? 1.1 * streams * (double)(long)((columns + 127.99) / 128) * tiles * mean / (2 * kCutShare) + 0.2 * longest
                              : share + 0.4 * longest;
-  return cut + (narrow ? 4 : 20) < (load > longest ? load : longest);
+  const double merge = narrow && pieces > 1 ? 2 + 0.5e-6 * row_values * pieces : 0;
+  return cut + (narrow ? 4 : 20) < (load > longest ? load : longest) + merge;
 }
 
 // Whether a batch without cached prefixes takes it: its items are of all lengths already, so that few are long next to a CU's
@@ -112,7 +116,8 @@ inline long cut_pieces_by_tiles(int max_kv_len) { return (max_kv_len + 64 * kMin
 inline int cut_cap(long slots) { return (int)(slots < kMostCutSlots ? slots : kMostCutSlots); }
 
 // Slots for partials of the form (0: not taken), from the hints; forced: wherever it can be computed.
-inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads, bool forced) {
+inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads, int head_dim,
+                          bool forced) {
   if (batch <= 0 || batch > 64 * kRankSlots || total_q <= 0 || max_kv_len > (1 << 24)) return 0;
   const int group = num_q_heads / num_kv_heads;
   const int cols = (group & (group - 1)) == 0 ? (group < 32 ? group : 32) : 1;  // heads in the column dimension
@@ -127,7 +132,7 @@ inline int cut_form_slots(int batch, int total_q, int max_q_len, int max_kv_len,
       if (items <= kCutFewItems && max_kv_len < kCutFewKeys) return 0;
       const int by_hints = kv_pieces(wg128, max_kv_len), cap = kv_split_cap(rows);
       const int pieces = by_hints < 1 ? 1 : by_hints < cap ? by_hints : cap;
-      if (!cut_pays(batch, streams, (double)total_q * cols / batch, max_kv_len, is_small_grid(wg128), pieces)) return 0;
+      if (!cut_pays(batch, streams, (double)total_q * cols / batch, max_kv_len, is_small_grid(wg128), pieces, (double)rows * head_dim)) return 0;
     }
   }
   // an item has ceil(tiles / kMinCutTiles) pieces at most, and kMaxCutPieces

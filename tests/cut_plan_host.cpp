@@ -3,8 +3,8 @@
 
 extern "C" {
 
-int form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads) {
-  return sp::cut_form_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, num_kv_heads, false);
+int form_slots(int batch, int total_q, int max_q_len, int max_kv_len, int num_q_heads, int num_kv_heads, int head_dim) {
+  return sp::cut_form_slots(batch, total_q, max_q_len, max_kv_len, num_q_heads, num_kv_heads, head_dim, false);
 }
 
 int merge_groups(int batch, int total_q, int max_kv_len, int num_q_heads, int n_hgroups) {

@@ -75,7 +75,7 @@ def test_very_long_contexts(plan, hq, hkv, ctx, new):
     check(plan(hq, hkv, [700, ctx, 0, 30000], [64, new, 900, 1]))
 
 
-@pytest.mark.parametrize("batch,tokens,mq,mkv,heads", [(1, 64, 64, 5564, (8, 1)), (2, 96, 60, 9000, (8, 1)), (1, 512, 512, 33280, (16, 2)), (4, 512, 128, 100128, (32, 8))])
+@pytest.mark.parametrize("batch,tokens,mq,mkv,heads", [(1, 64, 64, 5564, (8, 1, 128)), (2, 96, 60, 9000, (8, 1, 128)), (1, 512, 512, 33280, (16, 2, 64)), (4, 512, 128, 100128, (32, 8, 128))])
 def test_slots_are_what_the_pieces_need(library, plan, batch, tokens, mq, mkv, heads):
     """No more slots than kMaxCutPieces of every item there may be, and enough for the search on any lengths of these hints."""
     slots = library.form_slots(batch, tokens, mq, mkv, *heads)
@@ -88,7 +88,7 @@ def test_slots_are_what_the_pieces_need(library, plan, batch, tokens, mq, mkv, h
         new = np.minimum(new, mq)
         ctx = rng.integers(0, mkv - new + 1)
         ctx[rng.integers(batch)] = mkv - mq
-        unlimited, limited = plan(*heads, ctx, new, SLOTS), plan(*heads, ctx, new, slots)
+        unlimited, limited = plan(*heads[:2], ctx, new, SLOTS), plan(*heads[:2], ctx, new, slots)
         assert unlimited[2] == limited[2] <= slots and unlimited[0] == limited[0] <= limited[1]
 
 
@@ -118,6 +118,8 @@ S70, F8, W64 = (8, 1, 128), (32, 8, 128), (16, 2, 64)
     # few query rows: pieces of 128 columns are shorter from about 12000 keys on
     (1, 64, 64, 5564, S70, True), (1, 64, 64, 4064, S70, False), (1, 64, 64, 20064, S70, False), (1, 64, 64, 131136, S70, False),
     (1, 256, 256, 5500, W64, True), (1, 256, 256, 100256, S70, False), (4, 236, 59, 41558, S70, False),
+    # ... unless the merge of every row's pieces takes longer than that
+    (7, 959, 137, 4660, (16, 2, 128), True),
     # ... and the same from about 24 query tiles on
     (1, 1024, 1024, 33024, S70, True), (4, 512, 128, 100128, F8, True),
     # chunks that leave most of a 256-column tile empty
@@ -131,4 +133,4 @@ S70, F8, W64 = (8, 1, 128), (32, 8, 128), (16, 2, 64)
     (1, 9560, 9560, 9560, S70, True), (4, 13124, 3281, 3281, S70, False), (2, 12704, 8250, 8250, S70, True),
 ])
 def test_which_batches_take_the_form(library, batch, tokens, mq, mkv, heads, cut):
-    assert (library.form_slots(batch, tokens, mq, mkv, heads[0], heads[1]) > 0) == cut
+    assert (library.form_slots(batch, tokens, mq, mkv, *heads) > 0) == cut
