@@ -173,10 +173,7 @@ SP_HD int cut_limit(const int (&c)[N], const int (&q)[N], const int (&nt)[N], in
   longest = most(longest);
   const int base = imax((int)((float)w * (float)n_hgroups * (1.25f / kCutShare)) + 1, imax(kMinCutTiles, (longest + kMaxCutPieces - 1) / kMaxCutPieces));
   int limit = base;
-  int items = 0;
-#pragma unroll
-  for (int u = 0; u < N; ++u) items += nt[u];
-  bool settled = sum(items) * n_hgroups > kCutShare;
+  bool settled = false;
   for (;;) {
     int wgs = 0, total = 0;
 #pragma unroll
@@ -204,8 +201,13 @@ SP_HD int cut_limit(const int (&c)[N], const int (&q)[N], const int (&nt)[N], in
     *total_pieces = total;
     if (settled || wgs * n_hgroups <= kCutShare) break;
     // One round of workgroups, with pieces up to 1.2 times as long, before a second round of a few (6 chunks at 8q/1kv,
-    // 114 items: 66 -> 55 us; 8 at 16q/2kv, 144 items: 62 -> 55.5; 2 at 32q/4kv, 206 items: 134 -> 129; where the second
-    // round is full of short items it had been the better one: 28 at 8q/1kv, 118 items: 57 -> 60; up to 1 us elsewhere).
+    // 114 items: 66 -> 55 us; 8 at 16q/2kv, 144 items: 62 -> 55.5; of 450 batches 18 are 4 to 47 % faster for it; where the second
+    // round is full of short items it is the better one: 28 at 8q/1kv, 118 items: 62 and 59), unless the whole items
+    // alone are more than one round.
+    int items = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) items += nt[u];
+    if (limit == base && sum(items) * n_hgroups > kCutShare) break;
     if (5 * limit >= 6 * base) {
       limit = base;
       settled = true;
