@@ -519,59 +519,58 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // feeds the second group's private K/V stream.  Wave wq brings in page wq of every tile
   // (16 rows = NIW instructions of 1 KiB): lane l of instruction j fills chunk slot l % 16 of
   // line 4j + l / 16 of that page and fetches whichever global chunk the swizzle assigns to
-  // that slot.  Rows past the end of the sequence are redirected to its last valid row (finite
-  // data; their weights are masked to zero).  Page ids are wave-uniform and read from the block
-  // table one period ahead.
-  // Everything a load needs per lane is computed before the loop: the byte offset inside a
-  // (page, kv head) block per instruction, for K and for V (their swizzles differ).  Only the
-  // page that holds the sequence's last key needs other offsets (rows clamped); a stream reaches
-  // it with its last loads and repeats it from then on, so the offsets are switched once, outside
-  // the MFMA sequences, when that page comes up.  A VALU instruction in a matrix phase is not
-  // free: measured with two waves on a SIMD, the second wave gets about five plain VALU
-  // instructions in per 32-cycle MFMA of the first, and the softmax needs nearly all of them.
+  // that slot.  Page ids are wave-uniform and read from the block table one period ahead.
+  // A load instruction's offset field is added on both sides, to the global address and to the LDS address, and
+  // instruction j of a page lies 1024 j further on both: M0 is set once per page, and the lane offsets hold
+  // only what is left, the swizzle (set per instruction, with the page's clamped offsets looked up for K as well, the matrix
+  // phase of the wave that loads was 40 scalar instructions longer: 4 x 2048 tokens 51.8 -> 49.5 us, 1 x 32768 1654 -> 1632).
+  // Rows past the end of the sequence: their scores are masked, so K takes what the page holds; V is
+  // redirected to the last valid row (a weight of 0 does not cover a NaN).  That concerns the pages from the
+  // one with the sequence's last key on, which a stream reaches with its last tile and repeats from then
+  // on: the offsets are switched once, outside the MFMA sequences, when that tile's V comes up.
   constexpr int NSTREAM = SPLIT ? 2 : 1;  // K/V tile streams of the workgroup
   constexpr int NLD = NSTREAM * 2 * NIW;  // load instructions per wave and period
   const int last_kv = kv_end - 1, last_page = last_kv >> 4;
   const int dq = lane >> 4, dslot = lane & 15;
   auto stream_tile = [&](int g, int i) __attribute__((always_inline)) { return t_begin + (SPLIT ? 2 * i + g : i); };  // local tile i of stream g
+  constexpr int VBIAS = (NIW - 1) * 1024;  // keeps the V offsets of clamped rows from going below zero
   auto lane_off = [&](bool is_v, int j, int rip_lim) __attribute__((always_inline)) {  // instruction j of a page load: this lane's source offset
     const int lp = 4 * j + dq;  // line inside the page
     const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
     const int rip = D == 128 ? lp : 2 * lp + (cl >> 3);
     const int chunk = D == 128 ? cl : (cl & 7);
-    return (unsigned)(min(rip, rip_lim) * ROWB + chunk * 16);
+    return (unsigned)(min(rip, rip_lim) * ROWB + chunk * 16 - 1024 * j + (is_v ? VBIAS : 0));
   };
-  unsigned voff[NSTREAM][2][NIW];  // [stream][K, V][instruction]
+  unsigned koff[NIW], voff[NSTREAM][NIW];  // K; V of every stream
+#pragma unroll
+  for (int j = 0; j < NIW; ++j) koff[j] = lane_off(false, j, 15);
 #pragma unroll
   for (int g = 0; g < NSTREAM; ++g)
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, 15);
+  auto clamp_v = [&](int g, int gt) __attribute__((always_inline)) {  // before the loads of V of key tile gt of stream g
+    if (gt < T - 1 || (T - 1) * (KVT / kPage) + wq < last_page) return;
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) voff[g][m][j] = lane_off(m != 0, j, 15);
+    for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, last_kv & 15);
+  };
+  const char *const kpool = a.k_pages + (size_t)kvh * (kPage * ROWB), *const vpool = a.v_pages + (size_t)kvh * (kPage * ROWB) - VBIAS;
+  const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);
   // The inline assembly below makes the compiler treat every later load as possibly clobbered,
   // so block-table reads are vector loads; the value stays in a VGPR until the load that needs
   // it is issued one period later, and only then moves to an SGPR.
   auto page_of = [&](int gt) __attribute__((always_inline)) {  // all lanes read the same entry
     return bt_row[min(min(gt, T - 1) * (KVT / kPage) + wq, last_page)];
   };
-  struct TileLoad {   // wave-uniform description of one page-sized load (NIW instructions)
-    const char *pb;   // start of the (page, kv head) block in the pool
-    unsigned dst0;    // LDS byte address of this wave's part of the tile slot
+  auto page_pos = [&](int pg) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
+    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), a.num_pages - 1) * page_bytes;
   };
-  auto dma_prep = [&](bool is_v, int g, int gt, int pg, int slot) __attribute__((always_inline)) {
-    if (min(gt, T - 1) * (KVT / kPage) + wq >= last_page) {  // uniform: the page with the last key, from now on
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) voff[g][is_v][j] = lane_off(is_v, j, last_kv & 15);
-    }
-    const unsigned page = (unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), a.num_pages - 1);  // no wild loads on bad metadata
-    TileLoad tl;
-    tl.pb = (is_v ? a.v_pages : a.k_pages) + ((size_t)page * a.Hkv + kvh) * (kPage * ROWB);
-    tl.dst0 = (unsigned)(g * REGION + (is_v ? 2 : 0) * TBYTES + slot * TBYTES + wq * (NIW * 1024));
-    return tl;
-  };
-  auto dma_emit = [&](const TileLoad &tl, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of the load
-    const unsigned dst = tl.dst0 + j * 1024;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(tl.pb));
+  const unsigned wave_dst = (unsigned)(wq * (NIW * 1024));
+  auto dma_emit = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
+    static_assert(NIW <= 4, "an offset field holds up to 4095");
+    if (j == 0) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(pb));
+    else if (j == 1) asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(off), "s"(pb));
+    else if (j == 2) asm volatile("global_load_lds_dwordx4 %0, %1 offset:2048" ::"v"(off), "s"(pb));
+    else asm volatile("global_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(off), "s"(pb));
   };
   using std::false_type;
   using std::integral_constant;
@@ -583,21 +582,25 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // instructions are then emitted one at a time, spread over the MFMA sequence: issued back to
   // back by four waves at once they queue up at the CU's one texture address unit, and since a
   // wave issues in order, everything behind them waits too.
-  int pg_k[NSTREAM], pg_v[NSTREAM];  // page ids of the next K and V loads (kept in VGPRs)
-  TileLoad ld[NSTREAM][2];
-  auto issue_prep = [&](int i, auto parc) __attribute__((always_inline)) {  // parc: i & 1 as a compile-time constant
-    constexpr int PAR = decltype(parc)::value;
+  int pg_k[NSTREAM];      // page ids of the next K loads (kept in VGPRs)
+  size_t pos_v[NSTREAM];  // where the pages of the next V loads begin in the pool
+  const char *ld[NSTREAM][2];
+  auto issue_prep = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
     for (int g = 0; g < NSTREAM; ++g) {
-      ld[g][0] = dma_prep(false, g, stream_tile(g, i + 1), pg_k[g], 1 - PAR);
-      ld[g][1] = dma_prep(true, g, stream_tile(g, i), pg_v[g], PAR);
-      pg_v[g] = pg_k[g];
+      const size_t pos = page_pos(pg_k[g]);
+      ld[g][0] = kpool + pos;
+      ld[g][1] = vpool + pos_v[g];
+      pos_v[g] = pos;
       pg_k[g] = page_of(stream_tile(g, i + 2));
     }
   };
-  auto issue_emit = [&](int n) __attribute__((always_inline)) {  // n-th instruction of the period, n < NLD: streams and matrices interleaved
-    const int j = n / (2 * NSTREAM), g = (n / 2) % NSTREAM, m = n & 1;
-    dma_emit(ld[g][m], voff[g][m][j], j);
+  auto slot_dst = [&](int g, int m, int slot) __attribute__((always_inline)) {  // LDS address of this wave's page in a tile slot
+    return (unsigned)(g * REGION + (2 * m + slot) * TBYTES) + wave_dst;
+  };
+  auto issue_emit = [&](int n, int par) __attribute__((always_inline)) {  // n-th instruction of the period, n < NLD: streams and matrices in turn
+    const int j = n % NIW, u = n / NIW, g = u % NSTREAM, m = u / NSTREAM;
+    dma_emit(ld[g][m], slot_dst(g, m, m ? par : 1 - par), m ? voff[g][j] : koff[j], j);
   };
   auto wait_loads = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };  // vmcnt(0) only
 
@@ -693,7 +696,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
       do_mfma(I0 + i, ops[i]);
       if (STAGE && i % GAP == 0 && i / GAP * PER < NLD) {
 #pragma unroll
-        for (int e = 0; e < PER; ++e) issue_emit(i / GAP * PER + e);
+        for (int e = 0; e < PER; ++e) issue_emit(i / GAP * PER + e, KS);
       }
     }
 #ifdef SP_PREFILL_SUM_IN_MATRIX_PHASE
@@ -907,21 +910,25 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // free), so the first period has no load to wait for: a memory latency per workgroup that
   // small grids cannot hide behind other work.
   if (grp == 0) {
+    int pg0[NSTREAM], pg1[NSTREAM];
 #pragma unroll
     for (int g = 0; g < NSTREAM; ++g) {
-      const int gt0 = stream_tile(g, 0), gt1 = stream_tile(g, 1);
-      const int pg0 = page_of(gt0), pg1 = page_of(gt1);
-      TileLoad k0 = dma_prep(false, g, gt0, pg0, 0);
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(k0, voff[g][0][j], j);
-      TileLoad v0 = dma_prep(true, g, gt0, pg0, 0);
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(v0, voff[g][1][j], j);
-      TileLoad k1 = dma_prep(false, g, gt1, pg1, 1);
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(k1, voff[g][0][j], j);
+      pg0[g] = page_of(stream_tile(g, 0));
+      pg1[g] = page_of(stream_tile(g, 1));
       pg_k[g] = page_of(stream_tile(g, 2));
-      pg_v[g] = pg1;
+    }
+#pragma unroll
+    for (int g = 0; g < NSTREAM; ++g) {
+      clamp_v(g, stream_tile(g, 0));
+      const size_t pos0 = page_pos(pg0[g]);
+      pos_v[g] = page_pos(pg1[g]);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos0, slot_dst(g, 0, 0), koff[j], j);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma_emit(vpool + pos0, slot_dst(g, 1, 0), voff[g][j], j);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos_v[g], slot_dst(g, 0, 1), koff[j], j);
+      clamp_v(g, stream_tile(g, 1));
     }
   }
   wait_loads();
@@ -957,11 +964,13 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
         }
 #endif
         if (PREC && precise(t - 1)) pv_residual(integral_constant<int, 1 - PAR>{});  // V(t-1) became visible at the barrier
-        issue_prep(t, parc);
+        issue_prep(t);
         SP_MATRIX_PHASE_BEGIN();
         pv_qk(true_type{}, parc, false_type{});
         SP_MATRIX_PHASE_END();
         softmax(t, false_type{}, PREC && precise(t), integral_constant<bool, kScaledQ && !PREC>{});
+#pragma unroll
+        for (int g = 0; g < NSTREAM; ++g) clamp_v(g, stream_tile(g, t + 1));
         wait_loads();
         __syncthreads();
       };
@@ -1009,6 +1018,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
       for (int t = max(Tl, 1); t < P; ++t) __syncthreads();  // keep the barrier count of the first group
     }
   };
+
   if (precise_wg) tile_loop(true_type{});
   else tile_loop(false_type{});
   SP_TRACE_STAMP(2, 0);
