@@ -429,7 +429,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   const int token = tok0 + (C >> a.gshift);
   const int head = (hg << a.gshift) | (C & gmask);
   const bool valid = token < q_len;
-  const int lim = valid ? ctx + token + 1 : 1;
+  // A column without a query (past the sequence's end) has scores of 0 and is not stored, so it takes any limit: with one of 1 key
+  // its wave went through the mask in every tile instead of the last ones (1 x 5003 tokens, 8q/1kv: 77 -> 65 us).
+  const int lim = valid ? ctx + token + 1 : kv_end;
   const long out_off = ((long)(q0 + token) * a.Hq + head) * (D * 2);
 #pragma unroll
   for (int s = 0; s < G::kDSteps; ++s) {
@@ -474,8 +476,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
     }
   }
   const int wtok_first = tok0 + ((wc * 32) >> a.gshift);
-  const int wtok_last = tok0 + (((wc + 1) * 32 - 1) >> a.gshift);
-  const int wlim_min = wtok_last < q_len ? ctx + wtok_first + 1 : 1;
+  const int wlim_min = min(ctx + wtok_first + 1, kv_end);  // keys that all of the wave's columns see
 
   f32x16 o[G::kDBlocks];
 #pragma unroll
