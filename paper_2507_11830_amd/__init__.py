@@ -3,12 +3,15 @@
 Every step of the hot path (KV append, prefill attention, split decode + combine) runs in the
 HIP kernels behind the C ABI declared in ``include/shiftattn.h``; this module converts torch
 tensors to raw device pointers, passes the current HIP stream and turns negative status codes
-into exceptions.  There is no CPU or PyTorch fallback: if the shared library has not been
+into exceptions.  The step calls do that in a small native module (``csrc/binding.cpp``), the
+others through ctypes.  There is no CPU or PyTorch fallback: if the shared library has not been
 built, importing the binding's functions fails loudly.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
@@ -18,6 +21,8 @@ if os.environ.get("SP_LIB_SANITIZE", "") == "1":
     # the copy whose host code carries ASan + UBSan instrumentation (CPU-only boundary tests; the
     # process must run with the matching sanitizer runtime preloaded)
     LIB_PATH = os.path.join(_HERE, "_build", "san", "libshiftattn_san.so")
+
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 SP_OK = 0
 SP_ERR_NULL = -1
@@ -48,6 +53,30 @@ class sp_cache_desc(ctypes.Structure):
 
 
 _lib = None
+_native = None
+
+
+def _bind(L: ctypes.CDLL):
+    """The native marshalling module, calling into the library L."""
+    global _native
+    if not os.path.exists(BINDING_PATH):
+        raise ImportError(f"{BINDING_PATH} is missing: run `python -m paper_2507_11830_amd.build` (or __graft_entry__.build()) first")
+    import torch
+
+    loader = importlib.machinery.ExtensionFileLoader("_binding", BINDING_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
+    loader.exec_module(module)
+    names = ("sp_kv_append", "sp_attn_prefill", "sp_chunk_step", "sp_attn_decode", "sp_attn_decode_static", "sp_decode_step")
+    module.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, ctypes.ArgumentError,
+                torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.cuda.current_stream)
+    _native = module
+    return module
+
+
+def _calls():
+    if _native is None:
+        lib()
+    return _native
 
 
 def lib() -> ctypes.CDLL:
@@ -98,6 +127,7 @@ def lib() -> ctypes.CDLL:
         L.sp_status_string.restype = ctypes.c_char_p
         L.sp_last_error.restype = ctypes.c_char_p
         L.sp_version.restype = ctypes.c_int
+        _bind(L)
         _lib = L
     return _lib
 
@@ -162,22 +192,14 @@ def sp_version() -> int:
 def sp_kv_append(cache: KVCache, k_new, v_new, cu_seqlens_new, ctx_lens, block_table, stream=None) -> None:
     """k_new, v_new: bf16 [T, Hkv, d] (cuda); cu_seqlens_new [B+1], ctx_lens [B], block_table
     [B, max_pages]: int32 cuda tensors."""
-    batch, max_pages = block_table.shape
-    total = k_new.shape[0]
-    _check(lib().sp_kv_append(ctypes.byref(cache.desc), _ptr(k_new), _ptr(v_new), _ptr(cu_seqlens_new),
-                              _ptr(ctx_lens), _ptr(block_table), batch, max_pages, total, _stream(stream)))
+    _check((_native or _calls()).kv_append(cache, k_new, v_new, cu_seqlens_new, ctx_lens, block_table, stream))
 
 
 def sp_attn_prefill(cache: KVCache, q, out, cu_seqlens_q, ctx_lens, block_table, max_q_len: int,
                     max_kv_len: int, scale: float, causal: int = 1, workspace=None, stream=None) -> None:
     """q, out: bf16 [T, Hq, d] (cuda).  The chunk's own K/V must already be appended."""
-    batch, max_pages = block_table.shape
-    total, num_q_heads = q.shape[0], q.shape[1]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().sp_attn_prefill(ctypes.byref(cache.desc), _ptr(q), _ptr(out), _ptr(cu_seqlens_q),
-                                 _ptr(ctx_lens), _ptr(block_table), batch, max_pages, total, max_q_len,
-                                 max_kv_len, num_q_heads, float(scale), causal, _ptr(workspace), ws_bytes,
-                                 _stream(stream)))
+    _check((_native or _calls()).attn_prefill(cache, q, out, cu_seqlens_q, ctx_lens, block_table, max_q_len, max_kv_len, scale, causal,
+                                              workspace, stream))
 
 
 def sp_attn_decode_workspace_size(batch: int, max_seq_len: int, num_q_heads: int, head_dim: int) -> int:
@@ -193,45 +215,28 @@ def sp_attn_prefill_workspace_size(batch: int, total_q_tokens: int, max_q_len: i
 def sp_attn_decode(cache: KVCache, q, out, seq_lens, block_table, max_seq_len: int, scale: float,
                    workspace, stream=None) -> None:
     """q, out: bf16 [B, Hq, d] (cuda); seq_lens include the current token."""
-    batch, max_pages = block_table.shape
-    num_q_heads = q.shape[1]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().sp_attn_decode(ctypes.byref(cache.desc), _ptr(q), _ptr(out), _ptr(seq_lens),
-                                _ptr(block_table), batch, max_pages, max_seq_len, num_q_heads, float(scale),
-                                _ptr(workspace), ws_bytes, _stream(stream)))
+    _check((_native or _calls()).attn_decode(cache, q, out, seq_lens, block_table, max_seq_len, scale, workspace, stream))
 
 
 def sp_attn_decode_static(cache: KVCache, q, out, seq_lens, block_table, max_seq_len: int, scale: float, stream=None) -> None:
     """sp_attn_decode with the partials in the library's static device array (no workspace, no
     allocation); shapes whose partials exceed 16 MiB are refused."""
-    batch, max_pages = block_table.shape
-    _check(lib().sp_attn_decode_static(ctypes.byref(cache.desc), _ptr(q), _ptr(out), _ptr(seq_lens), _ptr(block_table),
-                                       batch, max_pages, max_seq_len, q.shape[1], float(scale), _stream(stream)))
+    _check((_native or _calls()).attn_decode_static(cache, q, out, seq_lens, block_table, max_seq_len, scale, stream))
 
 
 def sp_decode_step(cache: KVCache, k_new, v_new, q, out, seq_lens, block_table, max_seq_len: int, scale: float,
                    workspace, stream=None) -> None:
     """Fused append + decode: k_new, v_new bf16 [B, Hkv, d] (the new token of every sequence),
     seq_lens include it; the rest as sp_attn_decode."""
-    batch, max_pages = block_table.shape
-    num_q_heads = q.shape[1]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().sp_decode_step(ctypes.byref(cache.desc), _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(out),
-                                _ptr(seq_lens), _ptr(block_table), batch, max_pages, max_seq_len, num_q_heads,
-                                float(scale), _ptr(workspace), ws_bytes, _stream(stream)))
+    _check((_native or _calls()).decode_step(cache, k_new, v_new, q, out, seq_lens, block_table, max_seq_len, scale, workspace, stream))
 
 
 def sp_chunk_step(cache: KVCache, k_new, v_new, q, out, cu_seqlens_q, ctx_lens, block_table, max_q_len: int,
                   max_kv_len: int, scale: float, workspace=None, stream=None) -> None:
     """Fused append + chunk attention: k_new, v_new bf16 [T, Hkv, d] packed like q; the rest as
     sp_attn_prefill."""
-    batch, max_pages = block_table.shape
-    total, num_q_heads = q.shape[0], q.shape[1]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().sp_chunk_step(ctypes.byref(cache.desc), _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(out),
-                               _ptr(cu_seqlens_q), _ptr(ctx_lens), _ptr(block_table), batch, max_pages, total,
-                               max_q_len, max_kv_len, num_q_heads, float(scale), _ptr(workspace), ws_bytes,
-                               _stream(stream)))
+    _check((_native or _calls()).chunk_step(cache, k_new, v_new, q, out, cu_seqlens_q, ctx_lens, block_table, max_q_len, max_kv_len,
+                                            scale, workspace, stream))
 
 
 def sp_debug_validate_metadata(cache: KVCache, seq_lens, block_table) -> None:

@@ -1,5 +1,6 @@
 """Build step: every HIP source under csrc/ compiled for gfx950 with hipcc and linked into
-libshiftattn.so next to this file (in-tree, so it travels with the repo); the benchmark's
+libshiftattn.so next to this file (in-tree, so it travels with the repo), the Python entry points'
+argument marshalling into _binding.so; the benchmark's
 reference kernels under bench_kernels/ go into a shared object of their own, libspceilings.so.
 
 ``python -m paper_2507_11830_amd.build --sanitize-host`` builds a second copy of libshiftattn
@@ -13,6 +14,7 @@ import re
 import shlex
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -22,6 +24,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 BENCH_SRC = os.path.join(HERE, "bench_kernels")
 LIB = os.path.join(HERE, "libshiftattn.so")
 CEIL_LIB = os.path.join(HERE, "libspceilings.so")
+BINDING_LIB = os.path.join(HERE, "_binding.so")
 SAN_LIB = os.path.join(OBJ_DIR, "san", "libshiftattn_san.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -144,8 +147,20 @@ def _link(objs, lib: str, extra_flags=()) -> None:
     os.replace(tmp, lib)
 
 
+def _build_binding() -> None:
+    """The native argument marshalling (plain host code against the CPython C API)."""
+    tmp = BINDING_LIB + f".tmp{os.getpid()}"
+    r = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+                        os.path.join(CSRC, "binding.cpp"), "-o", tmp], capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("g++ failed on binding.cpp")
+    os.replace(tmp, BINDING_LIB)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
+    _build_binding()
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     bench = sorted(glob.glob(os.path.join(BENCH_SRC, "*.hip")))
     with ThreadPoolExecutor(max_workers=min(8, len(srcs) + len(bench))) as ex:
