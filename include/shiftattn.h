@@ -186,8 +186,11 @@ int sp_attn_decode_static(const sp_cache_desc *cache, const void *q, void *out,
  *   same workspace size.
  * Where sp_attn_prefill would take its short-chunk path, the append happens inside the attention
  * kernel (the waves whose key range holds the new positions fetch the rows, use them and store
- * them to their pages): one launch less in a launch-bound step.  Otherwise the call is
- * sp_kv_append + sp_attn_prefill.  Either way the cache afterwards holds the new rows exactly
+ * them to their pages): one launch less in a launch-bound step.  So it does where the hints say
+ * that all sequences are prompts of one length without cached tokens (batch times max_q_len is
+ * total_q_tokens, max_kv_len no larger than max_q_len) and the query heads per KV head are a power
+ * of two of at least 4 (for some shapes 2): the prefill kernel reads their keys from k_new and v_new.
+ * Otherwise the call is sp_kv_append + sp_attn_prefill.  Either way the cache afterwards holds the new rows exactly
  * as sp_kv_append would have written them and `out` equals sp_attn_prefill's on that cache.
  */
 int sp_chunk_step(const sp_cache_desc *cache, const void *k_new, const void *v_new,

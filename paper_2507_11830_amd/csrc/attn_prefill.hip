@@ -91,6 +91,10 @@ static int launch_prefill_d(const PrefillArgs &a, bool split, int batch, int max
   return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0>, &set[2], smem, 256, a, batch, max_q_len, stream);
 }
 
+static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void *v_new, const void *q, void *out, const int32_t *cu_q,
+                          const int32_t *ctx_lens, const int32_t *block_table, int batch, int max_pages, int total_q, int max_q_len,
+                          int max_kv_len, int num_q_heads, float scale, void *workspace, size_t workspace_bytes, hipStream_t stream);
+
 int launch_chunk_step(const sp_cache_desc &c, const void *k_new, const void *v_new, const void *q, void *out,
                       const int32_t *cu_q, const int32_t *ctx_lens, const int32_t *block_table, int batch,
                       int max_pages, int total_q, int max_q_len, int max_kv_len, int num_q_heads, float scale,
@@ -101,10 +105,8 @@ int launch_chunk_step(const sp_cache_desc &c, const void *k_new, const void *v_n
                                  max_q_len, max_kv_len, num_q_heads, scale, workspace, workspace_bytes, stream);
     if (rc != 1) return rc;
   }
-  int rc = launch_kv_append(c, k_new, v_new, cu_q, ctx_lens, block_table, batch, max_pages, total_q, stream);
-  if (rc != SP_OK) return rc;
-  return launch_prefill(c, q, out, cu_q, ctx_lens, block_table, batch, max_pages, total_q, max_q_len, max_kv_len,
-                        num_q_heads, scale, workspace, workspace_bytes, stream);
+  return prefill_chunks(c, k_new, v_new, q, out, cu_q, ctx_lens, block_table, batch, max_pages, total_q, max_q_len, max_kv_len, num_q_heads,
+                        scale, workspace, workspace_bytes, stream);
 }
 
 int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32_t *cu_q,
@@ -118,6 +120,14 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
                                  max_kv_len, num_q_heads, scale, workspace, workspace_bytes, stream);
     if (rc != 1) return rc;
   }
+  return prefill_chunks(c, nullptr, nullptr, q, out, cu_q, ctx_lens, block_table, batch, max_pages, total_q, max_q_len, max_kv_len, num_q_heads,
+                        scale, workspace, workspace_bytes, stream);
+}
+
+// The prefill kernels; k_new / v_new non-NULL: the chunks' rows are appended here.
+static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void *v_new, const void *q, void *out, const int32_t *cu_q,
+                          const int32_t *ctx_lens, const int32_t *block_table, int batch, int max_pages, int total_q, int max_q_len,
+                          int max_kv_len, int num_q_heads, float scale, void *workspace, size_t workspace_bytes, hipStream_t stream) {
   PrefillArgs a;
   a.k_pages = (const char *)c.k_pages;
   a.v_pages = (const char *)c.v_pages;
@@ -214,6 +224,23 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
     }
   }
   const bool split = small_grid || kvs > 1;
+  // Append and prefill in one launch: only where the hints leave no room for cached tokens.  Sequences of max_q_len tokens at
+  // most that together have batch x max_q_len are all that long, and with max_kv_len no larger have no prefix; anywhere else a
+  // sequence may read, as its cached prefix, a page that another one appends in this call, and the append has to come first.  (A
+  // sub-range call may pass hints for more tokens than it has: the kernel finds its prefixes and appends before it reads.)
+  // The heads of a KV head have to share query tiles, of few enough rows that a thread moves two chunks of them.
+  if (k_new) {
+    const int tile = (split ? 128 : 256) >> gshift;
+    if ((group & (group - 1)) == 0 && tile * (c.head_dim / 8) <= kFreshChunks && (long)batch * max_q_len == total_q && max_kv_len <= max_q_len &&
+        kvs == 1 && a.cut_slots == 0 && a.route_cap == 0) {
+      FreshArgs f;
+      static_cast<PrefillArgs &>(f) = a;
+      f.k_new = (const char *)k_new;
+      f.v_new = (const char *)v_new;
+      return launch_prefill_fresh(f, split, c.head_dim, batch, max_q_len, stream);
+    }
+    if (int rc = launch_kv_append(c, k_new, v_new, cu_q, ctx_lens, block_table, batch, max_pages, total_q, stream)) return rc;
+  }
   // Mixed batch: both kinds of workgroups in one launch where the prefill ones take items by rank and the cached keys are
   // up to kMixedBytes, all sequences taken as long as the longest.  Beyond that the decode half alone saturates HBM
   // with all CUs, and starting on a part of them costs more than it hides (0.66 GB of keys: 148 us as two launches, 157 as one;

@@ -118,6 +118,13 @@ struct PrefillArgs {
   int32_t *cut_used;  // number of slots in use
 };
 
+// FreshArgs: the chunks' rows are not in the cache yet.  A workgroup takes the keys of a sequence without cached tokens from
+// the new rows themselves, and appends the rows of its own query tile.
+struct FreshArgs : PrefillArgs {
+  const char *k_new, *v_new;  // bf16 [total_q][Hkv][D]
+};
+constexpr int kFreshChunks = 1024;  // 16-byte chunks of K (and of V) in the rows of a query tile, at most: two per thread
+
 __device__ __forceinline__ int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan_incl(x), 63); }
 // Wave-wide max of non-negative values, wave-uniform (same DPP steps; a lane without a source lane
 // contributes 0).
@@ -327,11 +334,13 @@ __device__ __forceinline__ bool ranked_item(const PrefillArgs &a, int tpt_shift,
 // the device (ranked_item), and only those leave partials, for cut_combine_kernel.
 //
 // Args = MixedArgs (attn_mixed.hip): the launch also holds workgroups of another kernel, behind the prefill ones.
+// Args = FreshArgs (attn_prefill_fresh.hip): the append happens here.
 template <int D, int KVT, int PFD, bool SPLIT, bool PART, int CUT, typename Args = PrefillArgs>
 __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   using G = TileGeom<D>;
   using Z = SwzTile<D>;
   constexpr int COLS = SPLIT ? 128 : 256, KB = KVT / 32;
+  constexpr bool FRESH = std::is_same<Args, FreshArgs>::value;
   constexpr int ROWB = D * 2;               // bytes of one K or V row
   constexpr int TBYTES = KVT * ROWB;        // one tile in LDS
   constexpr int REGION = 4 * TBYTES;        // K[2] at 0 and TBYTES, V[2] at 2 and 3 TBYTES
@@ -348,7 +357,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
 #endif
 
   const int tid = threadIdx.x, lane = tid & 63;
-  if constexpr (!std::is_same<Args, PrefillArgs>::value) {
+  if constexpr (!FRESH && !std::is_same<Args, PrefillArgs>::value) {
     if (blockIdx.x >= a.first_other) {
       a.template run_other<D>(smem, lane);
       return;
@@ -529,10 +538,13 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // redirected to the last valid row (a weight of 0 does not cover a NaN).  That concerns the pages from the
   // one with the sequence's last key on, which a stream reaches with its last tile and repeats from then
   // on: the offsets are switched once, outside the MFMA sequences, when that tile's V comes up.
+  // New rows (FRESH) are no page: they have the stride of a token, and end where the caller's buffer may end, so K is redirected too.
   constexpr int NSTREAM = SPLIT ? 2 : 1;  // K/V tile streams of the workgroup
   constexpr int NLD = NSTREAM * 2 * NIW;  // load instructions per wave and period
   const int last_kv = kv_end - 1, last_page = last_kv >> 4;
   const int dq = lane >> 4, dslot = lane & 15;
+  const bool fresh = FRESH && ctx == 0;  // workgroup-uniform
+  const int row_stride = fresh ? a.Hkv * ROWB : ROWB;
   auto stream_tile = [&](int g, int i) __attribute__((always_inline)) { return t_begin + (SPLIT ? 2 * i + g : i); };  // local tile i of stream g
   constexpr int VBIAS = (NIW - 1) * 1024;  // keeps the V offsets of clamped rows from going below zero
   auto lane_off = [&](bool is_v, int j, int rip_lim) __attribute__((always_inline)) {  // instruction j of a page load: this lane's source offset
@@ -540,11 +552,14 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
     const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
     const int rip = D == 128 ? lp : 2 * lp + (cl >> 3);
     const int chunk = D == 128 ? cl : (cl & 7);
-    return (unsigned)(min(rip, rip_lim) * ROWB + chunk * 16 - 1024 * j + (is_v ? VBIAS : 0));
+    return (unsigned)(min(rip, rip_lim) * row_stride + chunk * 16 - 1024 * j + (is_v || FRESH ? VBIAS : 0));
   };
-  unsigned koff[NIW], voff[NSTREAM][NIW];  // K; V of every stream
+  constexpr int NK = FRESH ? NSTREAM : 1;
+  unsigned koff[NK][NIW], voff[NSTREAM][NIW];  // of every stream; K's are the same for all unless redirected
 #pragma unroll
-  for (int j = 0; j < NIW; ++j) koff[j] = lane_off(false, j, 15);
+  for (int g = 0; g < NK; ++g)
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) koff[g][j] = lane_off(false, j, 15);
 #pragma unroll
   for (int g = 0; g < NSTREAM; ++g)
 #pragma unroll
@@ -554,16 +569,35 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
 #pragma unroll
     for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, last_kv & 15);
   };
-  const char *const kpool = a.k_pages + (size_t)kvh * (kPage * ROWB), *const vpool = a.v_pages + (size_t)kvh * (kPage * ROWB) - VBIAS;
-  const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);
+  auto clamp_k = [&](int g, int gt) __attribute__((always_inline)) {  // the same for K
+    if (!FRESH || gt < T - 1 || (T - 1) * (KVT / kPage) + wq < last_page) return;
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) koff[FRESH ? g : 0][j] = lane_off(false, j, last_kv & 15);
+  };
+  const char *kpool, *vpool;  // this KV head's block of page 0
+  int most_pages = a.num_pages;
+  if constexpr (FRESH) {
+    const size_t first = ((size_t)q0 * a.Hkv + kvh) * ROWB, block = (size_t)kvh * (kPage * ROWB);
+    kpool = (fresh ? a.k_new + first : a.k_pages + block) - VBIAS;
+    vpool = (fresh ? a.v_new + first : a.v_pages + block) - VBIAS;
+    if (fresh) most_pages = 0x7fffffff;
+  } else {
+    kpool = a.k_pages + (size_t)kvh * (kPage * ROWB);
+    vpool = a.v_pages + (size_t)kvh * (kPage * ROWB) - VBIAS;
+  }
+  const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);  // sixteen new rows are as far apart
   // The inline assembly below makes the compiler treat every later load as possibly clobbered,
   // so block-table reads are vector loads; the value stays in a VGPR until the load that needs
   // it is issued one period later, and only then moves to an SGPR.
   auto page_of = [&](int gt) __attribute__((always_inline)) {  // all lanes read the same entry
-    return bt_row[min(min(gt, T - 1) * (KVT / kPage) + wq, last_page)];
+    const int idx = min(min(gt, T - 1) * (KVT / kPage) + wq, last_page);
+    if constexpr (FRESH) {
+      if (fresh) return idx;
+    }
+    return bt_row[idx];
   };
   auto page_pos = [&](int pg) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
-    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), a.num_pages - 1) * page_bytes;
+    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most_pages - 1) * page_bytes;
   };
   const unsigned wave_dst = (unsigned)(wq * (NIW * 1024));
   auto dma_emit = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
@@ -601,7 +635,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   };
   auto issue_emit = [&](int n, int par) __attribute__((always_inline)) {  // n-th instruction of the period, n < NLD: streams and matrices in turn
     const int j = n % NIW, u = n / NIW, g = u % NSTREAM, m = u / NSTREAM;
-    dma_emit(ld[g][m], slot_dst(g, m, m ? par : 1 - par), m ? voff[g][j] : koff[j], j);
+    dma_emit(ld[g][m], slot_dst(g, m, m ? par : 1 - par), m ? voff[g][j] : koff[FRESH ? g : 0][j], j);
   };
   auto wait_loads = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };  // vmcnt(0) only
 
@@ -906,6 +940,25 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
       for (int ks = 0; ks < 2; ++ks) pop[b][ks] = pack8(sacc[b], 8 * ks);
   };
 
+  // FRESH, but the sequence has cached tokens after all (the hints do not rule it out where they are larger than the
+  // batch): the workgroup appends the rows of all the keys it will read before it reads them.  Others may write the same rows at the
+  // same time, with the same bytes.
+  if constexpr (FRESH) {
+    if (!fresh) {
+      constexpr int CPR = ROWB / 16;
+      for (int i = tid; i < (kv_end - ctx) * CPR; i += 512) {
+        const int t = i / CPR, pos = ctx + t;
+        const int page = (pos >> 4) < a.max_pages && pos >= 0 ? bt_row[pos >> 4] : -1;
+        if (page < 0 || page >= a.num_pages) continue;
+        const size_t src = ((size_t)(q0 + t) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
+        const size_t dst = ((size_t)page * a.Hkv + kvh) * (kPage * ROWB) + (pos & 15) * ROWB + (i % CPR) * 16;
+        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.k_new + src);
+        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+      }
+      wait_loads();
+      __syncthreads();
+    }
+  }
   // prologue: K of every stream's first tile must be in LDS before anything is multiplied.  V of
   // that tile and K of the second one are requested in the same round trip (their slots are
   // free), so the first period has no load to wait for: a memory latency per workgroup that
@@ -921,19 +974,50 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
 #pragma unroll
     for (int g = 0; g < NSTREAM; ++g) {
       clamp_v(g, stream_tile(g, 0));
+      clamp_k(g, stream_tile(g, 0));
       const size_t pos0 = page_pos(pg0[g]);
       pos_v[g] = page_pos(pg1[g]);
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos0, slot_dst(g, 0, 0), koff[j], j);
+      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos0, slot_dst(g, 0, 0), koff[FRESH ? g : 0][j], j);
 #pragma unroll
       for (int j = 0; j < NIW; ++j) dma_emit(vpool + pos0, slot_dst(g, 1, 0), voff[g][j], j);
+      clamp_k(g, stream_tile(g, 1));
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos_v[g], slot_dst(g, 0, 1), koff[j], j);
+      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos_v[g], slot_dst(g, 0, 1), koff[FRESH ? g : 0][j], j);
       clamp_v(g, stream_tile(g, 1));
+      clamp_k(g, stream_tile(g, 2));
+    }
+  }
+  // FRESH: the rows of this query tile, on their way from the caller's buffer to their pages; one head group per KV head does
+  // it.  The requests go out behind those of the first tiles and the stores behind the barrier, where nobody waits for them.
+  constexpr int CPR = ROWB / 16;  // 16-byte chunks per row
+  u32x4 knew[2], vnew[2];
+  int page_new[2] = {-1, -1};
+  const int new_chunks = FRESH && fresh && (hg << a.gshift) == kvh * (a.Hq / a.Hkv) ? min(tpt, q_len - tok0) * CPR : 0;
+  if constexpr (FRESH) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = tid + 512 * u;
+      if (i >= new_chunks) continue;
+      const int pos = tok0 + i / CPR;
+      const size_t src = ((size_t)(q0 + pos) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
+      knew[u] = *reinterpret_cast<const u32x4 *>(a.k_new + src);
+      vnew[u] = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+      if ((pos >> 4) < a.max_pages) page_new[u] = bt_row[pos >> 4];
     }
   }
   wait_loads();
   __syncthreads();
+  if constexpr (FRESH) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (page_new[u] >= 0 && page_new[u] < a.num_pages) {  // rows without a page are skipped, as in kv_append_kernel
+        const int i = tid + 512 * u;
+        const size_t dst = ((size_t)page_new[u] * a.Hkv + kvh) * (kPage * ROWB) + ((tok0 + i / CPR) & 15) * ROWB + (i % CPR) * 16;
+        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = knew[u];
+        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = vnew[u];
+      }
+  }
   SP_TRACE_STAMP(1, 0);
 
   // One barrier per key tile.  Inside a tile period the two groups run the same two phases in
@@ -971,7 +1055,10 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
         SP_MATRIX_PHASE_END();
         softmax(t, false_type{}, PREC && precise(t), integral_constant<bool, kScaledQ && !PREC>{});
 #pragma unroll
-        for (int g = 0; g < NSTREAM; ++g) clamp_v(g, stream_tile(g, t + 1));
+        for (int g = 0; g < NSTREAM; ++g) {
+          clamp_v(g, stream_tile(g, t + 1));
+          clamp_k(g, stream_tile(g, t + 2));
+        }
         wait_loads();
         __syncthreads();
       };
@@ -1123,7 +1210,6 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
 #endif
 }
 
-typedef void (*prefill_fn)(PrefillArgs);
 
 constexpr int KVT = 64, PFD = 4;
 template <int D>
@@ -1159,9 +1245,10 @@ inline int grant_smem(const void *fn, bool *done, size_t smem) {
 }
 
 // Launches one prefill kernel instantiation with `cols` query columns per workgroup.
-inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, const PrefillArgs &a0, int batch,
-                      int max_q_len, hipStream_t stream) {
-  PrefillArgs a = a0;
+template <typename Args>
+inline int launch_cfg(void (*fn)(Args), bool *attr_set, size_t smem, int cols, const Args &a0, int batch, int max_q_len,
+                      hipStream_t stream) {
+  Args a = a0;
   dim3 grid;
   if (int rc = prefill_grid(a, cols, batch, max_q_len, &grid)) return rc;
   if (int rc = grant_smem((const void *)fn, attr_set, smem)) return rc;
@@ -1173,6 +1260,8 @@ inline int launch_cfg(prefill_fn fn, bool *attr_set, size_t smem, int cols, cons
 
 // attn_prefill_cut.hip: the CUT form and its combine pass, which is `groups` workgroups wide (at least cut_slots, as far as it matters).
 int launch_prefill_cut(const PrefillArgs &a, int head_dim, int batch, int max_q_len, int groups, hipStream_t stream);
+// attn_prefill_fresh.hip: append and prefill in one launch; split: 128-column workgroups.
+int launch_prefill_fresh(const FreshArgs &a, bool split, int head_dim, int batch, int max_q_len, hipStream_t stream);
 struct DecodeArgs;
 // attn_mixed.hip: ranked prefill workgroups of 128 (split) or 256 columns and `shares` workgroups of the equal-share decode.
 int launch_mixed(const PrefillArgs &a, const DecodeArgs &d, int shares, int pieces, bool split, int head_dim, int batch, int max_q_len, hipStream_t stream);

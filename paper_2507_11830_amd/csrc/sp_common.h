@@ -34,7 +34,7 @@ int launch_prefill(const sp_cache_desc &c, const void *q, void *out, const int32
                    int total_q, int max_q_len, int max_kv_len, int num_q_heads, float scale,
                    void *workspace, size_t workspace_bytes, hipStream_t stream);
 // Append the chunks' K/V rows, then attend (sp_chunk_step): one fused launch where the short-chunk
-// path applies, else launch_kv_append + launch_prefill.
+// path applies or whole prompts of one length come in, else launch_kv_append and the prefill kernels.
 int launch_chunk_step(const sp_cache_desc &c, const void *k_new, const void *v_new, const void *q, void *out,
                       const int32_t *cu_q, const int32_t *ctx_lens, const int32_t *block_table, int batch,
                       int max_pages, int total_q, int max_q_len, int max_kv_len, int num_q_heads, float scale,
