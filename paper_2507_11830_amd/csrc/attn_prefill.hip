@@ -23,7 +23,7 @@
 // cycles a CU is busy, and what limits the kernel beyond that is the clock the chip grants under
 // this load (it is power-limited from the first tile on).
 #include "decode_block.h"
-#include "prefill_tile.h"
+#include "prefill_solo.h"
 
 namespace sp {
 
@@ -88,7 +88,8 @@ static int launch_prefill_d(const PrefillArgs &a, bool split, int batch, int max
   // budget of two workgroups per CU).
   if (a.kv_splits > 1) return launch_cfg(prefill_kernel<D, KVT, PFD, true, true, 0>, &set[0], 2 * smem, 128, a, batch, max_q_len, stream);
   if (split) return launch_cfg(prefill_kernel<D, KVT, PFD, true, false, 0>, &set[1], 2 * smem, 128, a, batch, max_q_len, stream);
-  return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0>, &set[2], smem, 256, a, batch, max_q_len, stream);
+  if constexpr (D == 64) return launch_cfg(prefill_solo_kernel<PrefillArgs>, &set[2], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads);
+  else return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0>, &set[2], smem, 256, a, batch, max_q_len, stream);
 }
 
 static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void *v_new, const void *q, void *out, const int32_t *cu_q,
@@ -230,7 +231,7 @@ static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void 
   // sub-range call may pass hints for more tokens than it has: the kernel finds its prefixes and appends before it reads.)
   // The heads of a KV head have to share query tiles, of few enough rows that a thread moves two chunks of them.
   if (k_new) {
-    const int tile = (split ? 128 : 256) >> gshift;
+    const int tile = (split || c.head_dim == 64 ? 128 : 256) >> gshift;
     if ((group & (group - 1)) == 0 && tile * (c.head_dim / 8) <= kFreshChunks && (long)batch * max_q_len == total_q && max_kv_len <= max_q_len &&
         kvs == 1 && a.cut_slots == 0 && a.route_cap == 0) {
       FreshArgs f;

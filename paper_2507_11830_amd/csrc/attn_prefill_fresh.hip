@@ -8,7 +8,7 @@
 // Measured (append and prefill, 8q/1kv d 128 where not said otherwise): 1 x 128 tokens at 2q/1kv d 64 9.2 -> 6.8 us, 1 x 300
 // 14.7 -> 12.3, 1 x 1500 23.9 -> 22.0, 4 x 2048 51.6 -> 46.1, 1 x 9000 at 16q/2kv d 64 199 -> 193, 4 x 8192 at 32q/8kv 1822 -> 1800.
 // Bound: as attn_prefill.hip; small prompts are a chain of the lengths, the first tiles and the stores.
-#include "prefill_tile.h"
+#include "prefill_solo.h"
 
 namespace sp {
 
@@ -17,7 +17,8 @@ static int launch_fresh_d(const FreshArgs &a, bool split, int batch, int max_q_l
   constexpr size_t smem = kPrefillSmem<D>;
   static bool set[2] = {false, false};
   if (split) return launch_cfg(prefill_kernel<D, KVT, PFD, true, false, 0, FreshArgs>, &set[0], 2 * smem, 128, a, batch, max_q_len, stream);
-  return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0, FreshArgs>, &set[1], smem, 256, a, batch, max_q_len, stream);
+  if constexpr (D == 64) return launch_cfg(prefill_solo_kernel<FreshArgs>, &set[1], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads);
+  else return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0, FreshArgs>, &set[1], smem, 256, a, batch, max_q_len, stream);
 }
 
 int launch_prefill_fresh(const FreshArgs &a, bool split, int head_dim, int batch, int max_q_len, hipStream_t stream) {

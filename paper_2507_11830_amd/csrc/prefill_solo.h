@@ -1,0 +1,474 @@
+// The prefill attention kernel for head_dim 64 on grids that fill the chip: workgroups of four waves and 128 query columns, three of
+// them resident on a CU (attn_prefill.hip says what is computed; prefill_tile.h has the two-group kernel, the choice of work items
+// and the reasons for the operand layouts).
+//
+// Why.  At head_dim 64 a score has half the MFMAs and as much softmax, so the VALU is the longer pipe: 32 MFMAs (1024 cycles)
+// against 224 softmax instructions (1200) per SIMD, 64 keys and 256 columns; an issue probe of both takes 1497 cycles.  The
+// two-group kernel takes 2075: one wave's softmax is a serial stream of 112 instructions at 7 to 8 cycles each next to the other
+// wave's MFMAs, and at every change of phase both wait.  Here a wave interleaves its own multiplications and softmax (QK^T of one
+// 32-key block and PV of another around the exponentials of a third), needs 160 registers, and so three waves share a SIMD; as they
+// belong to different workgroups, one wave's barriers and dependent steps are covered by the others: 1650 cycles for three workgroups'
+// tiles of 128 columns, i.e. 1100 per 256 columns, at 1.5 instead of 1.8 GHz (power).
+// Measured (two-group kernel with 256 columns -> here): 2 sequences of 9001..16384 tokens at 16q/2kv 802 -> 758 us (972 TFLOP/s),
+// 4 x 1500 29.4 -> 26.8, 2 x 2500 42.0 -> 37.5, 8 x 1200 41.6 -> 37.2, 4 x 3000 at 12q/3kv 75.0 -> 67.8, 40 chunks of 400 on up to 1300
+// keys 65.1 -> 57.7; 6 x 600..900, most of it rows of few keys (the block by block part below), 20.5 -> 21.3.  Smaller grids stay
+// with 128 columns on two wave groups: one such workgroup alone on a CU takes half as long per tile as this one (1 x 2000 tokens 20.6 us, here 25.7).
+// Tried on the way: the same loop with eight waves and 256 columns, two waves per SIMD and one barrier for all (2250
+// cycles; 797 -> 834 us on 2 x 16k tokens), with 64-key blocks (1950 cycles, 773 us); at head_dim 128, where two such waves share a SIMD, 2250
+// cycles instead of 2380, but twice the tile loads: 1677 -> 1849 us on 1 x 32768 tokens.
+//
+// LDS: K[3] and V[2] tile slots in the swizzled layout of SwzTile.  In the period of tile t the waves read K(t) and V(t-1), and
+// the loads of K(t+2) and V(t) are issued into the slots last read in period t-1; they have landed when the period ends.  K is
+// one tile ahead of its use, so that the first operands of period t+1 are read before the barrier that opens it.
+#pragma once
+#include "prefill_tile.h"
+
+namespace sp {
+
+constexpr int kSoloThreads = 256, kSoloCols = 128, kSoloKSlots = 3, kSoloVSlots = 2;
+constexpr size_t kSoloSmem = (kSoloKSlots + kSoloVSlots) * (size_t)KVT * 64 * 2;
+
+template <typename Args>
+__global__ __launch_bounds__(kSoloThreads, 3) void prefill_solo_kernel(Args a) {
+  constexpr int D = 64;
+  using G = TileGeom<D>;
+  using Z = SwzTile<D>;
+  using std::integral_constant;
+  constexpr bool FRESH = std::is_same<Args, FreshArgs>::value;
+  constexpr int WAVES = kSoloThreads / 64;
+  constexpr int ROWB = D * 2;                     // bytes of one K or V row
+  constexpr int TBYTES = KVT * ROWB;              // one tile in LDS
+  constexpr int VBASE = kSoloKSlots * TBYTES;     // V slots behind the K slots
+  constexpr int NIW = TBYTES / 1024 / WAVES;      // 1 KiB load instructions per wave, matrix and tile
+  static_assert(KVT == 4 * kPage, "each of the four waves brings in one page of a tile");
+  extern __shared__ __align__(16) char smem_raw[];
+  lds_char *smem = (lds_char *)smem_raw;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
+  const int col = lane & 31, half = lane >> 5;
+  WorkItem it;
+  if (!take_item<0, true>(a, 7, lane, &it)) return;
+  const int tpt = kSoloCols >> a.gshift, tok0 = it.tile * tpt, q0 = it.q0, q_len = it.q_len, ctx = it.ctx, hg = it.hg;
+  if (tok0 >= q_len) return;
+  const int kv_end = ctx + min(q_len, tok0 + tpt);
+  const int kvh = (hg << a.gshift) / (a.Hq / a.Hkv);
+  const int32_t *bt_row = a.block_table + (long)it.seq * a.max_pages;
+
+  // ---- this lane's column and the resident Q^T operands
+  const int C = w * 32 + col, token = tok0 + (C >> a.gshift);
+  const bool valid = token < q_len;
+  const int lim = valid ? ctx + token + 1 : kv_end;  // a column without a query has scores of 0 and is not stored: any limit will do
+  const int wlim_min = min(ctx + tok0 + ((w * 32) >> a.gshift) + 1, kv_end);  // keys that all of the wave's columns see
+  const long out_off = ((long)(q0 + token) * a.Hq + ((hg << a.gshift) | (C & ((1 << a.gshift) - 1)))) * (D * 2);
+  bf16x8 qreg[G::kDSteps];
+#pragma unroll
+  for (int s = 0; s < G::kDSteps; ++s) {
+    if (valid) {
+      qreg[s] = *reinterpret_cast<const bf16x8 *>(a.q + out_off + 32 * s + 16 * half);
+    } else {
+      u32x4 z = {0, 0, 0, 0};
+      qreg[s] = *reinterpret_cast<bf16x8 *>(&z);
+    }
+  }
+  f32x16 o[G::kDBlocks];
+#pragma unroll
+  for (int db = 0; db < G::kDBlocks; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m_used = -INFINITY, l = 0.f, l2 = 0.f;  // running max; row sum in two chains
+  const int T = (kv_end + KVT - 1) / KVT;       // key tiles
+
+  // ---- tile loads (prefill_tile.h): wave w brings in page w of every tile
+  const int last_kv = kv_end - 1, last_page = last_kv >> 4;
+  const int dq = lane >> 4, dslot = lane & 15;
+  const bool fresh = FRESH && ctx == 0;  // workgroup-uniform
+  const int row_stride = fresh ? a.Hkv * ROWB : ROWB;
+  constexpr int BIAS = (NIW - 1) * 1024;  // keeps the offsets of clamped rows from going below zero
+  auto lane_off = [&](bool is_v, int j, int rip_lim) __attribute__((always_inline)) {  // instruction j of a page: this lane's source offset
+    const int lp = 4 * j + dq;  // line inside the page
+    const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
+    const int rip = 2 * lp + (cl >> 3);
+    const int chunk = cl & 7;
+    return (unsigned)(min(rip, rip_lim) * row_stride + chunk * 16 - 1024 * j + BIAS);
+  };
+  unsigned koff[NIW], voff[NIW];
+#pragma unroll
+  for (int j = 0; j < NIW; ++j) {
+    koff[j] = lane_off(false, j, 15);
+    voff[j] = lane_off(true, j, 15);
+  }
+  const bool my_last = (T - 1) * (KVT / kPage) + w >= last_page;  // the last tile's page of this wave holds the last key, or lies behind it
+  auto clamp_v = [&](int t) __attribute__((always_inline)) {  // before the load of V of tile t
+    if (t < T - 1 || !my_last) return;
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) voff[j] = lane_off(true, j, last_kv & 15);
+  };
+  auto clamp_k = [&](int t) __attribute__((always_inline)) {  // new rows end where the caller's buffer may end
+    if (!FRESH || t < T - 1 || !my_last) return;
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) koff[j] = lane_off(false, j, last_kv & 15);
+  };
+  const char *kpool, *vpool;  // this KV head's block of page 0
+  int most_pages = a.num_pages;
+  {
+    const size_t block = (size_t)kvh * (kPage * ROWB);
+    kpool = a.k_pages + block - BIAS;
+    vpool = a.v_pages + block - BIAS;
+    if constexpr (FRESH) {
+      const size_t first = ((size_t)q0 * a.Hkv + kvh) * ROWB;
+      if (fresh) {
+        kpool = a.k_new + first - BIAS;
+        vpool = a.v_new + first - BIAS;
+        most_pages = 0x7fffffff;
+      }
+    }
+  }
+  const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);  // sixteen new rows are as far apart
+  auto page_of = [&](int t) __attribute__((always_inline)) {  // all lanes read the same entry
+    const int idx = min(min(t, T - 1) * (KVT / kPage) + w, last_page);
+    if constexpr (FRESH) {
+      if (fresh) return idx;
+    }
+    return bt_row[idx];
+  };
+  auto page_pos = [&](int pg) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
+    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most_pages - 1) * page_bytes;
+  };
+  auto dma = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
+    static_assert(NIW == 2, "two instructions per page");
+    if (j == 0) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(pb));
+    else asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(off), "s"(pb));
+  };
+  const unsigned wave_dst = (unsigned)(w * (NIW * 1024));
+  // Every load of this wave has landed; then all waves'.  Not __syncthreads: that would also wait for the operands of the next
+  // period that are on their way from LDS (their slot is not written before the period after).  The clobber keeps the
+  // compiler from carrying LDS contents across.
+  auto next_period = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  // ---- LDS operand addresses of this lane in the slots that are being read
+  const unsigned lds0 = (unsigned)(size_t)smem;
+  unsigned kadr[G::kDSteps], vadr[G::kDBlocks];
+#pragma unroll
+  for (int s = 0; s < G::kDSteps; ++s) kadr[s] = lds0 + Z::template offset<false>(col, 2 * s + half);
+  {
+    const int n = lane & 15, dg = (lane >> 4) & 1;
+#pragma unroll
+    for (int db = 0; db < G::kDBlocks; ++db)
+      vadr[db] = lds0 + VBASE + Z::template offset<true>(4 * half + (n >> 2), 4 * db + 2 * dg + ((n & 3) >> 1)) + 8 * (n & 1);
+  }
+  int kslot = 0, vslot = 0;
+  auto k_next = [&]() __attribute__((always_inline)) {  // what the K addresses move by, to the next slot
+    const int d = kslot == kSoloKSlots - 1 ? -(kSoloKSlots - 1) * TBYTES : TBYTES;
+    kslot = kslot == kSoloKSlots - 1 ? 0 : kslot + 1;
+    return (unsigned)d;
+  };
+  auto v_next = [&]() __attribute__((always_inline)) {
+    const int d = vslot ? -TBYTES : TBYTES;
+    vslot ^= 1;
+    return (unsigned)d;
+  };
+
+  // Operands of a block: NK of K, each for one 16-channel step of QK^T, then NV of V^T (two transposing reads), each for one
+  // 32-channel block and 16-key step of PV.
+  constexpr int NK = G::kDSteps, NV = 2 * G::kDBlocks, NOP = NK + NV;
+  constexpr int PFD = 4;   // operands read ahead
+  auto k_op = [&](int b, int s) __attribute__((always_inline)) -> bf16x8 { return *(const lds_bf16x8 *)(size_t)(kadr[s] + (unsigned)(32 * b * ROWB)); };
+  auto v_op = [&](int b, int i) __attribute__((always_inline)) -> bf16x8 {
+    return lds_read_vt((const lds_char *)(size_t)(vadr[i % G::kDBlocks] + (unsigned)((32 * b + 16 * (i / G::kDBlocks)) * ROWB)), ROWB);
+  };
+  f32x16 sc[2];     // raw scores of the blocks being multiplied and exponentiated
+  bf16x8 pw[2][2];  // their weights
+  auto qk = [&](int s, bf16x8 x, f32x16 &dst) __attribute__((always_inline)) {
+    if (s == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dst[r] = 0.f;
+    }
+    dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, qreg[s], dst, 0, 0, 0);
+  };
+  auto pv = [&](int i, bf16x8 x, const bf16x8 (&p)[2]) __attribute__((always_inline)) {
+    o[i % G::kDBlocks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, p[i / G::kDBlocks], o[i % G::kDBlocks], 0, 0, 0);
+  };
+  auto mask = [&](int base, f32x16 &s) __attribute__((always_inline)) {  // keys base .. base + 31
+    if (base + 32 <= wlim_min) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (base + 8 * (r >> 2) + 4 * half + (r & 3) >= lim) s[r] = -INFINITY;
+  };
+  // The general softmax of a block: its max, the lazy rescale of O and l, weights from the raw scores and their sums.  keep: they
+  // stay in s.
+  auto full = [&](f32x16 &s, bf16x8 (&p)[2], float (&ls)[2], bool keep) __attribute__((always_inline)) {
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = fmaxf(mx, other_half(mx));
+    if (__builtin_amdgcn_ballot_w64(mx > m_used + a.tau) != 0) {  // wave-uniform
+      const float m_new = fmaxf(m_used, mx);
+      const float alpha = __builtin_amdgcn_exp2f((m_used - m_new) * a.sl2e);
+      m_used = m_new;
+      l *= alpha;
+      l2 *= alpha;
+#pragma unroll
+      for (int db = 0; db < G::kDBlocks; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
+    const float msc = m_used * a.sl2e;
+    ls[0] = ls[1] = 0.f;
+    f32x16 x;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      x[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], a.sl2e, -msc));
+      ls[r & 1] += x[r];
+    }
+    p[0] = pack8(x, 0);
+    p[1] = pack8(x, 8);
+    if (keep) s = x;
+  };
+
+  // ---- FRESH: a sequence with cached tokens after all, and the rows of this query tile (prefill_tile.h)
+  constexpr int CPR = ROWB / 16;  // 16-byte chunks per row
+  constexpr int NEW = FRESH ? kFreshChunks / kSoloThreads : 0;
+  if constexpr (FRESH) {
+    if (!fresh) {
+      for (int i = tid; i < (kv_end - ctx) * CPR; i += kSoloThreads) append_chunk<D>(a, bt_row, kvh, q0, ctx, i);
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+  }
+
+  // ---- the first tiles
+  int pg = 0;        // page id of the next K load
+  size_t pos_v = 0, pos_w = 0;  // where the pages of the next two V loads begin
+  constexpr int kPreciseKeys = 256;
+  const bool precise = ctx + tok0 < kPreciseKeys;  // some rows have at most that many keys
+  {
+    const int pg0 = page_of(0), pg1 = page_of(1);
+    pg = page_of(2);
+    clamp_k(0);
+    clamp_v(0);
+    const size_t pos0 = page_pos(pg0);
+    pos_v = page_pos(pg1);
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) dma(kpool + pos0, wave_dst, koff[j], j);
+    clamp_k(1);
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) dma(kpool + pos_v, TBYTES + wave_dst, koff[j], j);
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) dma(vpool + pos0, VBASE + wave_dst, voff[j], j);
+    clamp_k(2);
+    clamp_v(1);
+    if constexpr (FRESH) {
+      u32x4 knew[NEW], vnew[NEW];
+      int page_new[NEW];
+      const int chunks = fresh && (hg << a.gshift) == kvh * (a.Hq / a.Hkv) ? min(tpt, q_len - tok0) * CPR : 0;
+#pragma unroll
+      for (int u = 0; u < NEW; ++u) {
+        const int i = tid + kSoloThreads * u, pos = tok0 + i / CPR;
+        page_new[u] = -1;
+        if (i >= chunks) continue;
+        const size_t src = ((size_t)(q0 + pos) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
+        knew[u] = *reinterpret_cast<const u32x4 *>(a.k_new + src);
+        vnew[u] = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+        if ((pos >> 4) < a.max_pages) page_new[u] = bt_row[pos >> 4];
+      }
+      next_period();
+#pragma unroll
+      for (int u = 0; u < NEW; ++u)
+        if (page_new[u] >= 0 && page_new[u] < a.num_pages) {  // rows without a page are skipped, as in kv_append_kernel
+          const int i = tid + kSoloThreads * u;
+          const size_t dst = ((size_t)page_new[u] * a.Hkv + kvh) * (kPage * ROWB) + ((tok0 + i / CPR) & 15) * ROWB + (i % CPR) * 16;
+          *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = knew[u];
+          *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = vnew[u];
+        }
+    } else {
+      next_period();
+    }
+  }
+
+  if (precise) {
+    // Rows with at most kPreciseKeys keys take their weights as hi + lo: a second PV with what bf16 rounded away, so that the
+    // rounding of the weights (which only averages out over many keys) stays out of the output tolerance there.  The
+    // workgroups that hold such rows are at most eight tiles long and go through them block by block.
+    for (int t = 0; t < T; ++t) {
+      if (t + 1 < T) {  // K of tile 1 is there already
+        if (t + 2 < T) {
+          const size_t pos = page_pos(pg);
+          const int to = kslot == 0 ? 2 : kslot - 1;
+#pragma unroll
+          for (int j = 0; j < NIW; ++j) dma(kpool + pos, (unsigned)(to * TBYTES) + wave_dst, koff[j], j);
+          pos_w = pos;
+        }
+        const unsigned to = (unsigned)(VBASE + (1 - vslot) * TBYTES) + wave_dst;
+#pragma unroll
+        for (int j = 0; j < NIW; ++j) dma(vpool + pos_v, to, voff[j], j);
+        pos_v = pos_w;
+        pg = page_of(t + 3);
+        clamp_k(t + 3);
+        clamp_v(t + 2);
+      }
+#pragma unroll 1
+      for (int b = 0; b < 2; ++b) {
+        const int base = t * KVT + 32 * b;
+        const unsigned rows = (unsigned)(32 * b * ROWB);
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+          qk(s, *(const lds_bf16x8 *)(size_t)(kadr[s] + rows), sc[0]);
+        }
+        mask(base, sc[0]);
+        float ls[2];
+        full(sc[0], pw[0], ls, true);
+        l += ls[0];
+        l2 += ls[1];
+        const bool lo = base < kPreciseKeys;
+#pragma unroll 1
+        for (int pass = 0; pass < (lo ? 2 : 1); ++pass) {
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            pv(i, lds_read_vt((const lds_char *)(size_t)(vadr[i % G::kDBlocks] + rows + (unsigned)(16 * (i / G::kDBlocks) * ROWB)), ROWB), pw[0]);
+          }
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) pw[0][ks] = pack8_residual(sc[0], 8 * ks, pw[0][ks]);
+        }
+      }
+      const unsigned dk = k_next(), dv = v_next();
+#pragma unroll
+      for (int s = 0; s < NK; ++s) kadr[s] += dk;
+#pragma unroll
+      for (int db = 0; db < G::kDBlocks; ++db) vadr[db] += dv;
+      next_period();
+    }
+  } else {
+    bf16x8 ops[PFD];  // the first operands of the next block
+    // One 32-key block of the pipeline: QK^T of block B of the K slot into sc[B] and PV of block B of the V slot with pw[B],
+    // while the scores in sc[1 - B] become weights in pw[1 - B].  QKV: 3 both, 2 PV only (the end).  AFTER: reads the first operands
+    // of the block that follows.  emit: called behind every operand.
+    auto block = [&](auto bc, auto whatc, int base, auto emit, auto first_of_next) __attribute__((always_inline)) {
+      constexpr int B = decltype(bc)::value, I0 = decltype(whatc)::value == 3 ? 0 : NK, N = NOP - I0;
+      constexpr int NS = 16, SPO = NS / N;        // scores of a lane, and behind each multiplication
+      static_assert(NS % N == 0 && SPO % 2 == 0, "scores go in pairs");
+      mask(base, sc[1 - B]);
+      const float msc = m_used * a.sl2e;
+      float ls[2] = {0.f, 0.f}, x[NS];
+      union {
+        bf16x2 h[4];
+        bf16x8 v;
+      } u[2];
+      auto step = [&](int i) __attribute__((always_inline)) {  // each operation one step behind the one that feeds it
+#pragma unroll
+        for (int r = SPO * i; r < SPO * (i + 1) && r < NS; ++r) x[r] = __builtin_fmaf(sc[1 - B][r], a.sl2e, -msc);
+#pragma unroll
+        for (int e = 0; e < SPO; ++e) {
+          const int r = SPO * (i - 1) + e;
+          if (r >= 0 && r < NS) x[r] = __builtin_amdgcn_exp2f(x[r]);
+        }
+#pragma unroll
+        for (int e = 0; e < SPO; e += 2) {
+          const int r = SPO * (i - 2) + e;
+          if (r < 0 || r >= NS) continue;
+          ls[0] += x[r];
+          ls[1] += x[r + 1];
+          u[r / 8].h[r / 2 % 4] = __builtin_convertvector((f32x2){x[r], x[r + 1]}, bf16x2);
+        }
+      };
+      auto op = [&](int i) __attribute__((always_inline)) -> bf16x8 { return i < NK ? k_op(B, i) : v_op(B, i - NK); };
+      bf16x8 q[N];
+#pragma unroll
+      for (int i = 0; i < PFD; ++i) q[i] = I0 == 0 ? ops[i] : op(I0 + i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N + 2; ++i) {
+        if (i + PFD < N) q[i + PFD] = op(I0 + i + PFD);
+        else if (i < N) first_of_next(i + PFD - N);
+        if (i < N) {
+          if (I0 + i < NK) qk(I0 + i, q[i], sc[B]);
+          else pv(I0 + i - NK, q[i], pw[B]);
+          emit(i);
+        }
+        step(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      pw[1 - B][0] = u[0].v;
+      pw[1 - B][1] = u[1].v;
+      // some weight above 2^8, or NaN (a masked score against a running max that is still -inf): wave-uniform
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(ls[0] + ls[1] <= 256.0f)) != 0, 0)) full(sc[1 - B], pw[1 - B], ls, false);
+      l += ls[0];
+      l2 += ls[1];
+    };
+    using I0 = integral_constant<int, 0>;
+    using I1 = integral_constant<int, 1>;
+    using Both = integral_constant<int, 3>;
+    using PvOnly = integral_constant<int, 2>;
+    auto nothing = [](int) {};
+    // period 0: block 0 of tile 0 sets the running max
+#pragma unroll
+    for (int s = 0; s < NK; ++s) qk(s, k_op(0, s), sc[0]);
+    mask(0, sc[0]);
+    float ls[2];
+    full(sc[0], pw[0], ls, false);
+    l += ls[0];
+    l2 += ls[1];
+#pragma unroll
+    for (int s = 0; s < NK; ++s) qk(s, k_op(1, s), sc[1]);
+    if (T > 1) {
+      pos_w = page_pos(pg);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma(kpool + pos_w, 2 * TBYTES + wave_dst, koff[j], j);
+      pg = page_of(3);
+      clamp_k(3);
+      {
+        const unsigned dk = k_next();
+#pragma unroll
+        for (int s = 0; s < NK; ++s) kadr[s] += dk;
+      }
+#pragma unroll
+      for (int i = 0; i < PFD; ++i) ops[i] = k_op(0, i);
+      next_period();
+      for (int t = 1; t < T; ++t) {
+        const size_t pos = page_pos(pg);
+        const char *kb = kpool + pos, *vb = vpool + pos_v;
+        pos_v = pos_w;
+        pos_w = pos;
+        pg = page_of(t + 3);
+        const unsigned kto = (unsigned)((kslot == 0 ? 2 : kslot - 1) * TBYTES) + wave_dst, vto = (unsigned)(VBASE + (1 - vslot) * TBYTES) + wave_dst;
+        const int base = t * KVT;
+        const unsigned dk = k_next(), dv = v_next();
+        bf16x8 nx[PFD];
+        block(I0{}, Both{}, base - 32, [&](int i) __attribute__((always_inline)) {
+          if (i % 2 && i / 2 < NIW) dma(kb, kto, koff[i / 2], i / 2);
+        }, [&](int i) __attribute__((always_inline)) { nx[i] = k_op(1, i); });
+#pragma unroll
+        for (int i = 0; i < PFD; ++i) ops[i] = nx[i];
+        block(I1{}, Both{}, base, [&](int i) __attribute__((always_inline)) {
+          if (i % 2 && i / 2 < NIW) dma(vb, vto, voff[i / 2], i / 2);
+          if (i == NK - 1) {  // the last K operand of the tile has been read: on to the next slot
+#pragma unroll
+            for (int s = 0; s < NK; ++s) kadr[s] += dk;
+          }
+        }, [&](int i) __attribute__((always_inline)) { nx[i] = k_op(0, i); });
+#pragma unroll
+        for (int i = 0; i < PFD; ++i) ops[i] = nx[i];
+#pragma unroll
+        for (int db = 0; db < G::kDBlocks; ++db) vadr[db] += dv;
+        clamp_k(t + 3);
+        clamp_v(t + 1);
+        next_period();
+      }
+    }
+    block(I0{}, PvOnly{}, (T - 1) * KVT + 32, nothing, nothing);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) pv(i, v_op(1, i), pw[1]);
+  }
+
+  // ---- normalise and store
+  const float ln = l + l2, inv = 1.0f / (ln + other_half(ln));
+  if (valid) {
+    char *dst = a.out + out_off;
+#pragma unroll
+    for (int db = 0; db < G::kDBlocks; ++db)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        store4_bf16(dst + (32 * db + 8 * r4 + 4 * half) * 2, o[db][4 * r4] * inv, o[db][4 * r4 + 1] * inv, o[db][4 * r4 + 2] * inv,
+                    o[db][4 * r4 + 3] * inv);
+  }
+}
+
+}  // namespace sp

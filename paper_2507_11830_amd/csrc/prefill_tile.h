@@ -88,6 +88,8 @@ constexpr bool kScaledQSwitch = true;
 constexpr bool kScaledQSwitch = false;
 #endif
 
+constexpr int KVT = 64, PFD = 4;  // keys per tile; operands read ahead of the MFMAs
+
 // What the merge of a cut work item has to know; one per partial slot.
 struct CutEntry {
   int32_t q0, q_len, tile, hg;
@@ -294,6 +296,95 @@ __device__ __forceinline__ bool ranked_item(const PrefillArgs &a, int tpt_shift,
   return found;
 }
 
+// The work item of a workgroup of 2^cols_shift query columns, wave-uniform; false: there is none for it.
+// Workgroups are dispatched in blockIdx.x-major order: the longest key ranges of ALL sequences
+// go first, the short ones fill in behind them.
+// Consecutive workgroup ids go round-robin over the 8 XCDs; with the (sequence, head group)
+// index rotated by the tile index, the workgroups of one sequence spread over all XCDs even
+// when the batch size is a multiple of 8 (unrotated, each sequence would sit on one XCD and a
+// batch of unequal lengths would leave most of the chip idle).
+struct WorkItem {
+  int seq, hg, tile, q0, q_len, ctx;
+  int piece, pieces;  // which piece of the key range; CUT: of how many
+  int slot;           // CUT: partial slot of the piece
+};
+template <int CUT, bool SNAKE = false>
+__device__ __forceinline__ bool take_item(const PrefillArgs &a, int cols_shift, int lane, WorkItem *o) {
+  o->pieces = 1;
+  o->slot = 0;
+  unsigned lid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), bx = blockIdx.x, by = blockIdx.y;
+  if constexpr (SNAKE) {
+    // Several workgroups are resident on a CU: each round of 256 gives every CU one.  The second round goes from the lightest of
+    // its items up, so that no CU has the heaviest item of both.
+    if (lid >= 256 && lid < 512) {
+      const unsigned xcd = lid & 7, p = (lid >> 3) - 32, total = gridDim.x * gridDim.y * gridDim.z;
+      const unsigned n = ((total < 512 ? total : 512) - 256 - xcd + 7) >> 3;  // this XCD's of the round
+      lid = ((32 + n - 1 - p) << 3) | xcd;
+      by = lid / gridDim.x;
+      bx = lid - by * gridDim.x;
+    }
+  }
+  if (CUT || a.ranked) {
+    // linear id -> (item rank, head group, piece): the pieces and head groups of an item are
+    // neighbours in the dispatch order, i.e. they start together and spread over the XCDs
+    const unsigned per_item = (unsigned)(a.n_hgroups * a.kv_splits);
+    const int r = (int)(lid / per_item);
+    const int sub = (int)(lid - (unsigned)r * per_item);
+    o->hg = sub / a.kv_splits;
+    o->piece = sub - o->hg * a.kv_splits;
+    RankedItem it;
+    it.tile = o->hg;
+    if (!ranked_item<CUT>(a, cols_shift - a.gshift, r, lane, &it)) return false;
+    if (CUT) {
+      o->piece = __builtin_amdgcn_readfirstlane(it.piece);
+      o->pieces = __builtin_amdgcn_readfirstlane(it.pieces);
+      o->slot = (int)lid;  // pieces of cut items come first: the launch index is the partial's slot
+    }
+    o->seq = __builtin_amdgcn_readfirstlane(it.seq);
+    o->tile = __builtin_amdgcn_readfirstlane(it.tile);
+    o->q0 = __builtin_amdgcn_readfirstlane(it.q0);
+    o->q_len = __builtin_amdgcn_readfirstlane(it.q_len);
+    o->ctx = __builtin_amdgcn_readfirstlane(it.ctx);
+    return true;
+  }
+  int sh, row;
+  if ((gridDim.x & 7) == 0) {
+    // A multiple of 8 (sequence, head group) streams: every XCD gets its own streams with ALL their
+    // query tiles (workgroup ids go round-robin over the XCDs, so XCD x sees the ids = x mod 8),
+    // heaviest tiles first.  The workgroups an XCD runs at any moment then belong to a few
+    // streams and sit at neighbouring query tiles, so they walk the same K/V pages nearly in
+    // step and the XCD's L2 serves most of their tile loads (rotating streams over the XCDs
+    // instead puts about one workgroup per stream on an XCD, and every tile load misses L2).
+    const unsigned xcd = lid & 7, p = lid >> 3, spx = gridDim.x >> 3;
+    row = (int)(p / spx);
+    sh = (int)((p - (unsigned)row * spx) * 8 + xcd);
+  } else {
+    sh = (int)((bx + by + blockIdx.z) % gridDim.x);
+    row = (int)(by + gridDim.y * blockIdx.z);
+  }
+  o->seq = sh / a.n_hgroups;
+  o->hg = sh - o->seq * a.n_hgroups;
+  o->piece = row / (int)gridDim.y;
+  o->tile = a.ntiles_x - 1 - (row - o->piece * (int)gridDim.y);
+  o->q0 = a.cu_q[o->seq];
+  o->q_len = a.cu_q[o->seq + 1] - o->q0;
+  o->ctx = a.ctx_lens[o->seq];
+  return o->q_len > a.route_cap;  // mixed batch: the split kernel serves the others
+}
+
+// FRESH: chunk i of the new rows of a sequence and KV head to its page (rows without one are skipped, as in kv_append_kernel).
+template <int D>
+__device__ __forceinline__ void append_chunk(const FreshArgs &a, const int32_t *bt_row, int kvh, int q0, int ctx, int i) {
+  constexpr int ROWB = 2 * D, CPR = ROWB / 16;
+  const int t = i / CPR, pos = ctx + t;
+  const int page = (pos >> 4) < a.max_pages && pos >= 0 ? bt_row[pos >> 4] : -1;
+  if (page < 0 || page >= a.num_pages) return;
+  const size_t src = ((size_t)(q0 + t) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
+  const size_t dst = ((size_t)page * a.Hkv + kvh) * (kPage * ROWB) + (pos & 15) * ROWB + (i % CPR) * 16;
+  *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.k_new + src);
+  *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+}
+
 // The waves form two groups of four, one wave of each group per SIMD (waves w and w+4 share a
 // SIMD).  Inside every tile period the groups run the same two phases in opposite order: one
 // multiplies (PV of the previous tile, then QK^T of the current one) while the other runs its
@@ -368,62 +459,10 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   const int grp = w >> 2;  // wave-uniform; waves w and w+4 share a SIMD: one wave of each group per SIMD
   const int wq = w & 3;    // wave inside its group
   const int rb = SPLIT ? grp * REGION : 0;  // this group's tile buffers
-  // Workgroups are dispatched in blockIdx.x-major order: the longest key ranges of ALL sequences
-  // go first, the short ones fill in behind them.
-  // Consecutive workgroup ids go round-robin over the 8 XCDs; with the (sequence, head group)
-  // index rotated by the tile index, the workgroups of one sequence spread over all XCDs even
-  // when the batch size is a multiple of 8 (unrotated, each sequence would sit on one XCD and a
-  // batch of unequal lengths would leave most of the chip idle).
-  int seq, hg, tile, piece, q0, q_len, ctx, pieces = 1, slot = 0;
+  WorkItem it;
+  if (!take_item<CUT>(a, SPLIT ? 7 : 8, lane, &it)) return;
+  const int seq = it.seq, hg = it.hg, tile = it.tile, piece = it.piece, q0 = it.q0, q_len = it.q_len, ctx = it.ctx, pieces = it.pieces, slot = it.slot;
   const int tpt = COLS >> a.gshift;
-  if (CUT || a.ranked) {
-    // linear id -> (item rank, head group, piece): the pieces and head groups of an item are
-    // neighbours in the dispatch order, i.e. they start together and spread over the XCDs
-    const unsigned lid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const unsigned per_item = (unsigned)(a.n_hgroups * a.kv_splits);
-    const int r = (int)(lid / per_item);
-    const int sub = (int)(lid - (unsigned)r * per_item);
-    hg = sub / a.kv_splits;
-    piece = sub - hg * a.kv_splits;
-    RankedItem it;
-    it.tile = hg;
-    if (!ranked_item<CUT>(a, (SPLIT ? 7 : 8) - a.gshift, r, lane, &it)) return;
-    if (CUT) {
-      piece = __builtin_amdgcn_readfirstlane(it.piece);
-      pieces = __builtin_amdgcn_readfirstlane(it.pieces);
-      slot = (int)lid;  // pieces of cut items come first: the launch index is the partial's slot
-    }
-    seq = __builtin_amdgcn_readfirstlane(it.seq);
-    tile = __builtin_amdgcn_readfirstlane(it.tile);
-    q0 = __builtin_amdgcn_readfirstlane(it.q0);
-    q_len = __builtin_amdgcn_readfirstlane(it.q_len);
-    ctx = __builtin_amdgcn_readfirstlane(it.ctx);
-  } else {
-    int sh, row;
-    if ((gridDim.x & 7) == 0) {
-      // A multiple of 8 (sequence, head group) streams: every XCD gets its own streams with ALL their
-      // query tiles (workgroup ids go round-robin over the XCDs, so XCD x sees the ids = x mod 8),
-      // heaviest tiles first.  The workgroups an XCD runs at any moment then belong to a few
-      // streams and sit at neighbouring query tiles, so they walk the same K/V pages nearly in
-      // step and the XCD's L2 serves most of their tile loads (rotating streams over the XCDs
-      // instead puts about one workgroup per stream on an XCD, and every tile load misses L2).
-      const unsigned lid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-      const unsigned xcd = lid & 7, p = lid >> 3, spx = gridDim.x >> 3;
-      row = (int)(p / spx);
-      sh = (int)((p - (unsigned)row * spx) * 8 + xcd);
-    } else {
-      sh = (int)((blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x);
-      row = (int)(blockIdx.y + gridDim.y * blockIdx.z);
-    }
-    seq = sh / a.n_hgroups;
-    hg = sh - seq * a.n_hgroups;
-    piece = row / (int)gridDim.y;
-    tile = a.ntiles_x - 1 - (row - piece * (int)gridDim.y);
-    q0 = a.cu_q[seq];
-    q_len = a.cu_q[seq + 1] - q0;
-    ctx = a.ctx_lens[seq];
-    if (q_len <= a.route_cap) return;  // mixed batch: the split kernel serves this sequence
-  }
   const int tok0 = tile * tpt;
   if (tok0 >= q_len) return;
   const int kv_end = ctx + min(q_len, tok0 + tpt);
@@ -945,16 +984,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // same time, with the same bytes.
   if constexpr (FRESH) {
     if (!fresh) {
-      constexpr int CPR = ROWB / 16;
-      for (int i = tid; i < (kv_end - ctx) * CPR; i += 512) {
-        const int t = i / CPR, pos = ctx + t;
-        const int page = (pos >> 4) < a.max_pages && pos >= 0 ? bt_row[pos >> 4] : -1;
-        if (page < 0 || page >= a.num_pages) continue;
-        const size_t src = ((size_t)(q0 + t) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
-        const size_t dst = ((size_t)page * a.Hkv + kvh) * (kPage * ROWB) + (pos & 15) * ROWB + (i % CPR) * 16;
-        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.k_new + src);
-        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.v_new + src);
-      }
+      for (int i = tid; i < (kv_end - ctx) * (ROWB / 16); i += 512) append_chunk<D>(a, bt_row, kvh, q0, ctx, i);
       wait_loads();
       __syncthreads();
     }
@@ -1211,7 +1241,6 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
 }
 
 
-constexpr int KVT = 64, PFD = 4;
 template <int D>
 constexpr size_t kPrefillSmem = 4 * (size_t)KVT * D * 2;  // K[2] V[2], unpadded
 
@@ -1247,12 +1276,12 @@ inline int grant_smem(const void *fn, bool *done, size_t smem) {
 // Launches one prefill kernel instantiation with `cols` query columns per workgroup.
 template <typename Args>
 inline int launch_cfg(void (*fn)(Args), bool *attr_set, size_t smem, int cols, const Args &a0, int batch, int max_q_len,
-                      hipStream_t stream) {
+                      hipStream_t stream, int threads = 512) {
   Args a = a0;
   dim3 grid;
   if (int rc = prefill_grid(a, cols, batch, max_q_len, &grid)) return rc;
   if (int rc = grant_smem((const void *)fn, attr_set, smem)) return rc;
-  hipLaunchKernelGGL(fn, grid, dim3(512), smem, stream, a);
+  hipLaunchKernelGGL(fn, grid, dim3((unsigned)threads), smem, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SP_ERR_HIP, "prefill launch: %s", hipGetErrorString(e));
   return SP_OK;

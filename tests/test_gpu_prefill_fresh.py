@@ -64,10 +64,10 @@ def test_whole_prompts_of_one_length(batch, n, Hq, Hkv, d):
     chunk_step(custom_workload(f"fresh-{batch}x{n}-{Hq}-{Hkv}-{d}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=n), launches=ONE)
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,batch,n", [(32, 8, 128, 3, 1057), (16, 2, 64, 5, 1009)])
-def test_256_column_tiles(Hq, Hkv, d, batch, n):
+@pytest.mark.parametrize("Hq,Hkv,d,batch,n,threads", [(32, 8, 128, 3, 1057, 512), (16, 2, 64, 5, 1009, 256)])
+def test_grids_that_fill_the_chip(Hq, Hkv, d, batch, n, threads):
     lens = np.full(batch, n)
-    chunk_step(custom_workload(f"fresh-wide-{Hq}-{Hkv}-{d}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=5), launches=ONE)
+    chunk_step(custom_workload(f"fresh-wide-{Hq}-{Hkv}-{d}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=5), launches=[(threads, 1, 1)])
 
 
 @pytest.mark.parametrize("name,Hq,Hkv,d,new,ctx", [
