@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kSoloThreads, 3) void prefill_solo_kernel(Args a) {
   int pg = 0;        // page id of the next K load
   size_t pos_v = 0, pos_w = 0;  // where the pages of the next two V loads begin
   constexpr int kPreciseKeys = 256;
-  const bool precise = ctx + tok0 < kPreciseKeys;  // some rows have at most that many keys
+  const bool precise = ctx + (it.tile & ~1) * tpt < kPreciseKeys;  // some rows of this tile or its neighbour, as with 256 columns, have at most that many keys
   {
     const int pg0 = page_of(0), pg1 = page_of(1);
     pg = page_of(2);
@@ -284,6 +284,17 @@ __global__ __launch_bounds__(kSoloThreads, 3) void prefill_solo_kernel(Args a) {
     }
   }
 
+  // Tile 0 sets the running max, both blocks of it: a weight of 1 is exact, and the more keys, the more rows have their
+  // largest one there
+#pragma unroll
+  for (int s = 0; s < NK; ++s) qk(s, k_op(0, s), sc[0]);
+#pragma unroll
+  for (int s = 0; s < NK; ++s) qk(s, k_op(1, s), sc[1]);
+  mask(0, sc[0]);
+  mask(32, sc[1]);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) m_used = fmaxf(m_used, fmaxf(sc[0][r], sc[1][r]));
+  m_used = fmaxf(m_used, other_half(m_used));
   if (precise) {
     // Rows with at most kPreciseKeys keys take their weights as hi + lo: a second PV with what bf16 rounded away, so that the
     // rounding of the weights (which only averages out over many keys) stays out of the output tolerance there.  The
@@ -398,16 +409,10 @@ __global__ __launch_bounds__(kSoloThreads, 3) void prefill_solo_kernel(Args a) {
     using Both = integral_constant<int, 3>;
     using PvOnly = integral_constant<int, 2>;
     auto nothing = [](int) {};
-    // period 0: block 0 of tile 0 sets the running max
-#pragma unroll
-    for (int s = 0; s < NK; ++s) qk(s, k_op(0, s), sc[0]);
-    mask(0, sc[0]);
-    float ls[2];
+    float ls[2];  // period 0
     full(sc[0], pw[0], ls, false);
     l += ls[0];
     l2 += ls[1];
-#pragma unroll
-    for (int s = 0; s < NK; ++s) qk(s, k_op(1, s), sc[1]);
     if (T > 1) {
       pos_w = page_pos(pg);
 #pragma unroll
