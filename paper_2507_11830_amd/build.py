@@ -97,10 +97,10 @@ def spill_limit(kern: str) -> int:
     that cuts long ones) and the decode kernels: none.  The 128-column prefill forms: the reloads of their rarely taken
     short-row copy; next to the decode role also one reload in every second tile period of the second wave group.  The
     equal-share decode with fused append and two column tiles at head_dim 128: per row segment, not per block."""
+    if "solo_prefill_kernel" in kern:
+        return 0
     if "prefill_kernel" in kern:
         return 0 if re.search(r"ELb0ELb0E", kern) else 9 if "MixedArgs" in kern else 8
-    if "prefill_solo_kernel" in kern:
-        return 0
     if "decode_stream_kernelILi128ELb1ELb1ELi2E" in kern:
         return 8
     return 0 if "decode_s" in kern else 1 << 30

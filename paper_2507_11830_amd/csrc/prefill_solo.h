@@ -29,7 +29,7 @@ constexpr int kSoloThreads = 256, kSoloCols = 128, kSoloKSlots = 3, kSoloVSlots 
 constexpr size_t kSoloSmem = (kSoloKSlots + kSoloVSlots) * (size_t)KVT * 64 * 2;
 
 template <typename Args>
-__global__ __launch_bounds__(kSoloThreads, 3) void prefill_solo_kernel(Args a) {
+__global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
   constexpr int D = 64;
   using G = TileGeom<D>;
   using Z = SwzTile<D>;
