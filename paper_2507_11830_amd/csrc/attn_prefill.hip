@@ -224,7 +224,7 @@ static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void 
       a.part_o = a.part_ml + (size_t)slots * 512;
     }
   }
-  const bool split = small_grid || kvs > 1;
+  const bool split = kvs > 1 || (small_grid && !(g_split_mode == 0 && a.route_cap == 0 && whole_tiles_pay(rows, streams, max_kv_len)));
   // Append and prefill in one launch: only where the hints leave no room for cached tokens.  Sequences of max_q_len tokens at
   // most that together have batch x max_q_len are all that long, and with max_kv_len no larger have no prefix; anywhere else a
   // sequence may read, as its cached prefix, a page that another one appends in this call, and the append has to come first.  (A

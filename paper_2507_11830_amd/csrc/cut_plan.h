@@ -48,6 +48,19 @@ inline int kv_split_cap(long rows) {
 constexpr int kSmallGrid = 576;  // 128-column workgroups
 inline bool is_small_grid(long wg128) { return wg128 <= kSmallGrid; }
 
+// ... unless the halves are more than one round of workgroups, and short: a second round costs 5 to 8 us of starts, merges and
+// stores, where whole tiles of 256 columns (or several workgroups a CU at head_dim 64) are one round and take 0.35 us longer per
+// key tile.  The line over the longest key range in tiles and n = rows / 128, measured on 150 batches of 20 to 2350 tokens
+// (us in halves and whole): 24 x 79..132 tokens at 16q/2kv 21.8 and 13.7; 8 x 800..1200 at 8q/1kv (n 500, 19 tiles) 39.9 and
+// 29.7; 4 x 562..937 at 16q/2kv (375, 15) 27.5 and 24.2; 8 x 602 at 12q/3kv d 64 (451, 10) 16.0 and 13.8; 24 x 138 at 16q/2kv
+// d 64 12.3 and 9.3; on the other side 1 x 1032 at 32q/8kv (258, 17) 21.5 and 24.3, 2 x 2037 at 12q/3kv d 64 (382, 32) 23.1 and
+// 29.9, chunks of 256 tokens on prefixes of 1300 at 16q/2kv (512, 34) 57.0 and 76.2.  At the edge of the second round
+// (3 x 688 at 16q/2kv d 64, 258 workgroups) 11.8 and 12.2, so it starts a little past 256.
+inline bool whole_tiles_pay(long rows, long streams, long max_kv_len) {
+  const long n = rows / 128, tiles = (max_kv_len + 63) / 64;
+  return n + streams / 2 > 264 && tiles <= (n > 512 ? 40 : 13 + (n - 256) * 23 / 512);
+}
+
 // How many pieces the key range of a query tile of a small grid is cut into (1 = none): only when even the
 // 128-column workgroups leave most CUs idle and the key ranges are long.  A piece's partial costs about as much HBM time
 // as 500 keys cost matrix time, so pieces stay around 1500 keys or longer.
