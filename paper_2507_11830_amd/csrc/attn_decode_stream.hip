@@ -74,13 +74,16 @@ __global__ __launch_bounds__(64 * kWaves, NT > 1 ? 1 : 2) void decode_stream_ker
 // partials and NB of them are in flight together.  Lane group g adds the partials g, g + 8, ... in order,
 // the eight groups are added in a fixed butterfly.
 //
-// PG > 1 (rows in many pieces): PG such workgroups in one, each merging a contiguous run of the row's
-// partials; the PG results meet in LDS.
+// PG > 1 (rows in many pieces): a workgroup per slice too, of PG waves that merge a contiguous run of the row's
+// partials each; the PG results meet in LDS.  All slices of a row in one workgroup of 1024 threads send its 66 KB (129 pieces)
+// through one CU's address unit, a chain that four CUs share here: one sequence of 33000 keys at 8q/1kv, decode and merge
+// 11.2 -> 9.8 us, and 9.6 with six load instructions a wave instead of eight where they cover the row (half of those eight asked for the last
+// partial again).  Eight waves of four instructions: 10.0.  Rows of up to 64 pieces gain nothing by the same (8.6 us either way).
 template <int D, int NB, int PG, bool MQ>
-__global__ __launch_bounds__(2 * D * PG) void combine_rows_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(PG > 1 ? 64 * PG : 2 * D) void combine_rows_kernel(DecodeArgs a) {
   const int tc = blockIdx.x, row = blockIdx.y;
-  const int pg = threadIdx.x / (2 * D), lane = threadIdx.x & 63, g = lane >> 3;
-  const int ch = ((threadIdx.x & (2 * D - 1)) >> 6) * 32 + (lane & 7) * 4;
+  const int pg = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 3;  // pg: PG > 1
+  const int ch = (PG > 1 ? (int)blockIdx.z : (int)(threadIdx.x >> 6)) * 32 + (lane & 7) * 4;
   u32x2 tab = {(uint32_t)(row * a.row_splits), (uint32_t)a.row_splits};
   if (a.row_splits == 0) tab = *reinterpret_cast<const u32x2 *>(a.row_tab + 2 * (long)row);
   long orow = (long)row * a.geff + tc;  // a.Hq = head groups x geff
@@ -137,12 +140,12 @@ __global__ __launch_bounds__(2 * D * PG) void combine_rows_kernel(DecodeArgs a) 
     for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
   }
   if constexpr (PG > 1) {
-    __shared__ f32x4 x_acc[PG][D / 4];
+    __shared__ f32x4 x_acc[PG][8];
     __shared__ f32x2 x_ml[PG];
-    if (g == 0) x_acc[pg][ch / 4] = acc;
-    if ((threadIdx.x & (2 * D - 1)) == 0) x_ml[pg] = (f32x2){M, den};
+    if (g == 0) x_acc[pg][lane] = acc;
+    if (lane == 0) x_ml[pg] = (f32x2){M, den};
     __syncthreads();
-    if (threadIdx.x >= D / 4) return;
+    if (threadIdx.x >= 8) return;
     M = -INFINITY;
 #pragma unroll
     for (int u = 0; u < PG; ++u) M = fmaxf(M, x_ml[u][0]);
@@ -159,9 +162,8 @@ __global__ __launch_bounds__(2 * D * PG) void combine_rows_kernel(DecodeArgs a) 
   } else if (g != 0) {
     return;
   }
-  const int och = PG > 1 ? 4 * (int)threadIdx.x : ch;
   const float inv = M == -INFINITY ? 0.f : 1.0f / den;  // no keys at all: zeros
-  *reinterpret_cast<bf16x4 *>(a.out + (orow * D + och) * 2) = __builtin_convertvector(acc * inv, bf16x4);
+  *reinterpret_cast<bf16x4 *>(a.out + (orow * D + ch) * 2) = __builtin_convertvector(acc * inv, bf16x4);
 }
 
 template <int D, bool MQ>
@@ -169,7 +171,13 @@ static void launch_rows_combine(const DecodeArgs &a, int max_pieces, hipStream_t
   const dim3 grid((unsigned)a.cols, (unsigned)(a.batch * a.n_hgroups)), block(2 * D);
   if (max_pieces <= 16) hipLaunchKernelGGL((combine_rows_kernel<D, 2, 1, MQ>), grid, block, 0, stream, a);
   else if (max_pieces <= 64) hipLaunchKernelGGL((combine_rows_kernel<D, 8, 1, MQ>), grid, block, 0, stream, a);
-  else hipLaunchKernelGGL((combine_rows_kernel<D, 8, 4, MQ>), grid, dim3(8 * D), 0, stream, a);
+  else {
+    // 192 pieces: six instructions of eight pieces in each of four waves; beyond, eight have fewer rows in a second batch (one sequence
+    // of 60000 keys, 235 pieces, 10.3 us, with six 10.8).
+    const dim3 slices(grid.x, grid.y, D / 32);
+    if (max_pieces <= 192) hipLaunchKernelGGL((combine_rows_kernel<D, 6, 4, MQ>), slices, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((combine_rows_kernel<D, 8, 4, MQ>), slices, dim3(256), 0, stream, a);
+  }
 }
 
 void launch_decode_combine(const DecodeArgs &a, int max_pieces, int head_dim, hipStream_t stream) {
