@@ -186,12 +186,17 @@ int sp_attn_decode_static(const sp_cache_desc *cache, const void *q, void *out,
  *   same workspace size.
  * Where sp_attn_prefill would take its short-chunk path, the append happens inside the attention
  * kernel (the waves whose key range holds the new positions fetch the rows, use them and store
- * them to their pages): one launch less in a launch-bound step.  So it does where the hints say
- * that all sequences are prompts of one length without cached tokens (batch times max_q_len is
- * total_q_tokens, max_kv_len no larger than max_q_len) and the query heads per KV head are a power
- * of two of at least 4 (for some shapes 2): the prefill kernel reads their keys from k_new and v_new.
- * Otherwise the call is sp_kv_append + sp_attn_prefill.  Either way the cache afterwards holds the new rows exactly
- * as sp_kv_append would have written them and `out` equals sp_attn_prefill's on that cache.
+ * them to their pages): one launch less in a launch-bound step.  There (max_q_len times the query
+ * heads per KV head of at most 64), and in sp_decode_step, the cached tokens of a sequence must not
+ * be rows that the same call appends for another sequence: which of the two bytes it reads is then
+ * unspecified; sp_kv_append + sp_attn_prefill serve that.
+ * So it does where the hints say that all sequences are prompts of one length without cached tokens
+ * (batch times max_q_len is total_q_tokens, max_kv_len no larger than max_q_len) and the query heads
+ * per KV head are a power of two of at least 4 (for some shapes 1 or 2): the prefill kernel reads new
+ * keys from k_new and v_new.  Otherwise the call is sp_kv_append + sp_attn_prefill.  In both a prefix
+ * may lie on rows that the same call appends for another sequence.  In every form the cache afterwards
+ * holds the new rows exactly as sp_kv_append would have written them and `out` equals
+ * sp_attn_prefill's on that cache.
  */
 int sp_chunk_step(const sp_cache_desc *cache, const void *k_new, const void *v_new,
                   const void *q, void *out, const int32_t *cu_seqlens_q,

@@ -225,19 +225,21 @@ static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void 
     }
   }
   const bool split = kvs > 1 || (small_grid && !(g_split_mode == 0 && a.route_cap == 0 && whole_tiles_pay(rows, streams, max_kv_len)));
-  // Append and prefill in one launch: only where the hints leave no room for cached tokens.  Sequences of max_q_len tokens at
-  // most that together have batch x max_q_len are all that long, and with max_kv_len no larger have no prefix; anywhere else a
-  // sequence may read, as its cached prefix, a page that another one appends in this call, and the append has to come first.  (A
-  // sub-range call may pass hints for more tokens than it has: the kernel finds its prefixes and appends before it reads.)
-  // The heads of a KV head have to share query tiles, of few enough rows that a thread moves two chunks of them.
+  // Append and prefill in one launch: where the hints let it expect prompts without cached tokens.  Sequences of max_q_len tokens
+  // at most that together have batch x max_q_len are all that long, and with max_kv_len no larger have no prefix.  The hints may
+  // also stand for more tokens than there are (a sub-range, padded buffers), so that sequences do have prefixes, which may lie on
+  // pages that the call appends: a workgroup that meets one sees to it that what it reads is there (fresh_plan.h).
+  // The heads of a KV head have to share query tiles, of few enough rows that a thread moves a few chunks of them, and row offsets
+  // are products of 24 bits.
   if (k_new) {
     const int tile = (split || c.head_dim == 64 ? 128 : 256) >> gshift;
     if ((group & (group - 1)) == 0 && tile * (c.head_dim / 8) <= kFreshChunks && (long)batch * max_q_len == total_q && max_kv_len <= max_q_len &&
-        kvs == 1 && a.cut_slots == 0 && a.route_cap == 0) {
+        kvs == 1 && a.cut_slots == 0 && a.route_cap == 0 && (long)c.num_kv_heads * c.head_dim * 2 < (1L << 23)) {
       FreshArgs f;
       static_cast<PrefillArgs &>(f) = a;
       f.k_new = (const char *)k_new;
       f.v_new = (const char *)v_new;
+      f.new_pages = most_new_pages(max_q_len);
       return launch_prefill_fresh(f, split, c.head_dim, batch, max_q_len, stream);
     }
     if (int rc = launch_kv_append(c, k_new, v_new, cu_q, ctx_lens, block_table, batch, max_pages, total_q, stream)) return rc;

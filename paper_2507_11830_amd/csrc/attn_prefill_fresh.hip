@@ -3,8 +3,9 @@
 // Why.  As two launches the append comes first and costs a launch and three dependent memory round trips, 5 to 7 us, before the
 // prefill kernel spends as much again on its own first tiles.  A prompt's keys are the step's own new rows, so a workgroup takes
 // its tiles from them (which also saves the page ids' round trip) and stores the rows of its query tile to their pages while it works.
-// Where sequences have cached tokens the order of the two steps may matter (a prefix that another sequence of the same call
-// appends), so those keep the two launches: launch_prefill says which hints rule it out.
+// Where the hints say that sequences have cached tokens the two launches are kept.  Where they say that there are none, they may
+// still stand for more tokens than the call has, and nothing orders the workgroups of a launch: fresh_plan.h says how a sequence
+// with cached tokens then gets the rows that the call appends, its own and those that other sequences append under its prefix.
 // Measured (append and prefill, 8q/1kv d 128 where not said otherwise): 1 x 128 tokens at 2q/1kv d 64 9.2 -> 6.8 us, 1 x 300
 // 14.7 -> 12.3, 1 x 1500 23.9 -> 22.0, 4 x 2048 51.6 -> 46.1, 1 x 9000 at 16q/2kv d 64 199 -> 193, 4 x 8192 at 32q/8kv 1822 -> 1800.
 // Bound: as attn_prefill.hip; small prompts are a chain of the lengths, the first tiles and the stores.

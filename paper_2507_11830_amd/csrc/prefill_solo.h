@@ -54,6 +54,14 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
   const int kvh = (hg << a.gshift) / (a.Hq / a.Hkv);
   const int32_t *bt_row = a.block_table + (long)it.seq * a.max_pages;
 
+  // ---- FRESH: a sequence with cached tokens after all (prefill_tile.h)
+  if constexpr (FRESH) {
+    if (__builtin_expect(ctx > 0, 0)) {
+      append_to_pool_pages<D, kSoloThreads>(a, smem, bt_row, it, kvh);
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+  }
+
   // ---- this lane's column and the resident Q^T operands
   const int C = w * 32 + col, token = tok0 + (C >> a.gshift);
   const bool valid = token < q_len;
@@ -80,59 +88,74 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
 
   // ---- tile loads (prefill_tile.h): wave w brings in page w of every tile
   const int last_kv = kv_end - 1, last_page = last_kv >> 4;
-  const int dq = lane >> 4, dslot = lane & 15;
-  const bool fresh = FRESH && ctx == 0;  // workgroup-uniform
-  const int row_stride = fresh ? a.Hkv * ROWB : ROWB;
+  int new_tile = 0x7fffffff;  // FRESH: tiles from here on are read from the new rows
+  if (FRESH && first_new_tile(ctx) < T) new_tile = first_new_tile(ctx);
   constexpr int BIAS = (NIW - 1) * 1024;  // keeps the offsets of clamped rows from going below zero
-  auto lane_off = [&](bool is_v, int j, int rip_lim) __attribute__((always_inline)) {  // instruction j of a page: this lane's source offset
+  auto lane_off = [&](bool is_v, int j, int rip_lim, int row_stride) __attribute__((always_inline)) {  // instruction j of a page: this lane's source offset
+    int ln = lane;
+    if constexpr (FRESH) asm volatile("" : "+v"(ln));  // not kept in registers over the tile loop
+    const int dq = ln >> 4, dslot = ln & 15;
     const int lp = 4 * j + dq;  // line inside the page
     const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
     const int rip = 2 * lp + (cl >> 3);
     const int chunk = cl & 7;
-    return (unsigned)(min(rip, rip_lim) * row_stride + chunk * 16 - 1024 * j + BIAS);
+    return (unsigned)((FRESH ? __mul24(min(rip, rip_lim), row_stride) : min(rip, rip_lim) * row_stride) + chunk * 16 - 1024 * j + BIAS);
   };
+  const int new_stride = a.Hkv * ROWB, first_stride = FRESH && new_tile == 0 ? new_stride : ROWB, last_stride = FRESH && new_tile < T ? new_stride : ROWB;
   unsigned koff[NIW], voff[NIW];
 #pragma unroll
   for (int j = 0; j < NIW; ++j) {
-    koff[j] = lane_off(false, j, 15);
-    voff[j] = lane_off(true, j, 15);
+    koff[j] = lane_off(false, j, 15, first_stride);
+    voff[j] = lane_off(true, j, 15, first_stride);
+  }
+  // This KV head's block of page 0; of new rows, the row that would be the first of page 0.
+  const size_t block = (size_t)kvh * (kPage * ROWB);
+  const long new_block = FRESH ? ((long)(q0 - ctx) * a.Hkv + kvh) * ROWB - BIAS : 0;
+  const char *kpool = a.k_pages + block - BIAS, *vpool = a.v_pages + block - BIAS;
+  if constexpr (FRESH) {
+    if (new_tile == 0) {
+      kpool = a.k_new + new_block;
+      vpool = a.v_new + new_block;
+    }
   }
   const bool my_last = (T - 1) * (KVT / kPage) + w >= last_page;  // the last tile's page of this wave holds the last key, or lies behind it
   auto clamp_v = [&](int t) __attribute__((always_inline)) {  // before the load of V of tile t
-    if (t < T - 1 || !my_last) return;
-#pragma unroll
-    for (int j = 0; j < NIW; ++j) voff[j] = lane_off(true, j, last_kv & 15);
-  };
-  auto clamp_k = [&](int t) __attribute__((always_inline)) {  // new rows end where the caller's buffer may end
-    if (!FRESH || t < T - 1 || !my_last) return;
-#pragma unroll
-    for (int j = 0; j < NIW; ++j) koff[j] = lane_off(false, j, last_kv & 15);
-  };
-  const char *kpool, *vpool;  // this KV head's block of page 0
-  int most_pages = a.num_pages;
-  {
-    const size_t block = (size_t)kvh * (kPage * ROWB);
-    kpool = a.k_pages + block - BIAS;
-    vpool = a.v_pages + block - BIAS;
     if constexpr (FRESH) {
-      const size_t first = ((size_t)q0 * a.Hkv + kvh) * ROWB;
-      if (fresh) {
-        kpool = a.k_new + first - BIAS;
-        vpool = a.v_new + first - BIAS;
-        most_pages = 0x7fffffff;
+      if (__builtin_expect(t == new_tile, 0)) {
+        vpool = a.v_new + new_block;
+#pragma unroll
+        for (int j = 0; j < NIW; ++j) voff[j] = lane_off(true, j, 15, new_stride);
       }
     }
-  }
-  const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);  // sixteen new rows are as far apart
-  auto page_of = [&](int t) __attribute__((always_inline)) {  // all lanes read the same entry
-    const int idx = min(min(t, T - 1) * (KVT / kPage) + w, last_page);
-    if constexpr (FRESH) {
-      if (fresh) return idx;
-    }
-    return bt_row[idx];
+    if (t < T - 1 || !my_last) return;
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) voff[j] = lane_off(true, j, last_kv & 15, last_stride);
   };
-  auto page_pos = [&](int pg) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
-    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most_pages - 1) * page_bytes;
+  auto clamp_k = [&](int t) __attribute__((always_inline)) {  // new rows end where the caller's buffer may end
+    if constexpr (FRESH) {
+      if (__builtin_expect(t == new_tile, 0)) {
+        kpool = a.k_new + new_block;
+#pragma unroll
+        for (int j = 0; j < NIW; ++j) koff[j] = lane_off(false, j, 15, new_stride);
+      }
+    }
+    if (!FRESH || t < T - 1 || !my_last) return;
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) koff[j] = lane_off(false, j, last_kv & 15, last_stride);
+  };
+  const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);  // sixteen new rows are as far apart
+  auto page_idx = [&](int t) __attribute__((always_inline)) { return min(min(t, T - 1) * (KVT / kPage) + w, last_page); };  // this wave's page of a tile
+  auto page_of = [&](int t) __attribute__((always_inline)) {  // all lanes read the same entry
+    if constexpr (FRESH) {
+      if (min(t, T - 1) >= new_tile) return 0;
+    }
+    return bt_row[page_idx(t)];
+  };
+  auto page_pos = [&](int t, int pg) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
+    int n = 0;
+    if (FRESH && min(t, T - 1) >= new_tile) n = page_idx(t);
+    else n = min(max(__builtin_amdgcn_readfirstlane(pg), 0), a.num_pages - 1);
+    return (size_t)(unsigned)n * page_bytes;
   };
   auto dma = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
     static_assert(NIW == 2, "two instructions per page");
@@ -225,28 +248,22 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     if (keep) s = x;
   };
 
-  // ---- FRESH: a sequence with cached tokens after all, and the rows of this query tile (prefill_tile.h)
-  constexpr int CPR = ROWB / 16;  // 16-byte chunks per row
-  constexpr int NEW = FRESH ? kFreshChunks / kSoloThreads : 0;
-  if constexpr (FRESH) {
-    if (!fresh) {
-      for (int i = tid; i < (kv_end - ctx) * CPR; i += kSoloThreads) append_chunk<D>(a, bt_row, kvh, q0, ctx, i);
-      asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    }
-  }
-
   // ---- the first tiles
   int pg = 0;        // page id of the next K load
   size_t pos_v = 0, pos_w = 0;  // where the pages of the next two V loads begin
   constexpr int kPreciseKeys = 256;
   const bool precise = ctx + (it.tile & ~1) * tpt < kPreciseKeys;  // some rows of this tile or its neighbour, as with 256 columns, have at most that many keys
   {
-    const int pg0 = page_of(0), pg1 = page_of(1);
-    pg = page_of(2);
+    int pg0 = 0, pg1 = 0;
+    if (!FRESH || new_tile != 0) {
+      pg0 = page_of(0);
+      pg1 = page_of(1);
+      pg = page_of(2);
+    }
     clamp_k(0);
     clamp_v(0);
-    const size_t pos0 = page_pos(pg0);
-    pos_v = page_pos(pg1);
+    const size_t pos0 = page_pos(0, pg0);
+    pos_v = page_pos(1, pg1);
 #pragma unroll
     for (int j = 0; j < NIW; ++j) dma(kpool + pos0, wave_dst, koff[j], j);
     clamp_k(1);
@@ -256,32 +273,10 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     for (int j = 0; j < NIW; ++j) dma(vpool + pos0, VBASE + wave_dst, voff[j], j);
     clamp_k(2);
     clamp_v(1);
-    if constexpr (FRESH) {
-      u32x4 knew[NEW], vnew[NEW];
-      int page_new[NEW];
-      const int chunks = fresh && (hg << a.gshift) == kvh * (a.Hq / a.Hkv) ? min(tpt, q_len - tok0) * CPR : 0;
-#pragma unroll
-      for (int u = 0; u < NEW; ++u) {
-        const int i = tid + kSoloThreads * u, pos = tok0 + i / CPR;
-        page_new[u] = -1;
-        if (i >= chunks) continue;
-        const size_t src = ((size_t)(q0 + pos) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
-        knew[u] = *reinterpret_cast<const u32x4 *>(a.k_new + src);
-        vnew[u] = *reinterpret_cast<const u32x4 *>(a.v_new + src);
-        if ((pos >> 4) < a.max_pages) page_new[u] = bt_row[pos >> 4];
-      }
-      next_period();
-#pragma unroll
-      for (int u = 0; u < NEW; ++u)
-        if (page_new[u] >= 0 && page_new[u] < a.num_pages) {  // rows without a page are skipped, as in kv_append_kernel
-          const int i = tid + kSoloThreads * u;
-          const size_t dst = ((size_t)page_new[u] * a.Hkv + kvh) * (kPage * ROWB) + ((tok0 + i / CPR) & 15) * ROWB + (i % CPR) * 16;
-          *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = knew[u];
-          *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = vnew[u];
-        }
-    } else {
-      next_period();
-    }
+    TileRows<D, kSoloThreads> rows;
+    if constexpr (FRESH) rows.request(a, bt_row, it, kvh, tok0, tpt);
+    next_period();
+    if constexpr (FRESH) rows.store(a, it, kvh, tok0);
   }
 
   // Tile 0 sets the running max, both blocks of it: a weight of 1 is exact, and the more keys, the more rows have their
@@ -302,7 +297,7 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     for (int t = 0; t < T; ++t) {
       if (t + 1 < T) {  // K of tile 1 is there already
         if (t + 2 < T) {
-          const size_t pos = page_pos(pg);
+          const size_t pos = page_pos(t + 2, pg);
           const int to = kslot == 0 ? 2 : kslot - 1;
 #pragma unroll
           for (int j = 0; j < NIW; ++j) dma(kpool + pos, (unsigned)(to * TBYTES) + wave_dst, koff[j], j);
@@ -414,7 +409,7 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     l += ls[0];
     l2 += ls[1];
     if (T > 1) {
-      pos_w = page_pos(pg);
+      pos_w = page_pos(2, pg);
 #pragma unroll
       for (int j = 0; j < NIW; ++j) dma(kpool + pos_w, 2 * TBYTES + wave_dst, koff[j], j);
       pg = page_of(3);
@@ -428,7 +423,7 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
       for (int i = 0; i < PFD; ++i) ops[i] = k_op(0, i);
       next_period();
       for (int t = 1; t < T; ++t) {
-        const size_t pos = page_pos(pg);
+        const size_t pos = page_pos(t + 2, pg);
         const char *kb = kpool + pos, *vb = vpool + pos_v;
         pos_v = pos_w;
         pos_w = pos;

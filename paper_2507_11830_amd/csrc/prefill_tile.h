@@ -5,6 +5,7 @@
 
 #include "attn_tile.h"
 #include "cut_plan.h"
+#include "fresh_plan.h"
 
 namespace sp {
 
@@ -120,12 +121,13 @@ struct PrefillArgs {
   int32_t *cut_used;  // number of slots in use
 };
 
-// FreshArgs: the chunks' rows are not in the cache yet.  A workgroup takes the keys of a sequence without cached tokens from
-// the new rows themselves, and appends the rows of its own query tile.
+// FreshArgs: the chunks' rows are not in the cache yet.  A workgroup takes its new keys from the new rows themselves, its
+// cached ones from the pool (fresh_plan.h), and appends the rows of its own query tile.
 struct FreshArgs : PrefillArgs {
   const char *k_new, *v_new;  // bf16 [total_q][Hkv][D]
+  int new_pages;              // pages that the new rows of a sequence reach into, at most
 };
-constexpr int kFreshChunks = 1024;  // 16-byte chunks of K (and of V) in the rows of a query tile, at most: two per thread
+constexpr int kFreshChunks = 1024;  // 16-byte chunks of K (and of V) in the rows of a query tile, at most: a few per thread
 
 __device__ __forceinline__ int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan_incl(x), 63); }
 // Wave-wide max of non-negative values, wave-uniform (same DPP steps; a lane without a source lane
@@ -366,24 +368,116 @@ __device__ __forceinline__ bool take_item(const PrefillArgs &a, int cols_shift, 
   o->hg = sh - o->seq * a.n_hgroups;
   o->piece = row / (int)gridDim.y;
   o->tile = a.ntiles_x - 1 - (row - o->piece * (int)gridDim.y);
+  o->ctx = a.ctx_lens[o->seq];
   o->q0 = a.cu_q[o->seq];
   o->q_len = a.cu_q[o->seq + 1] - o->q0;
-  o->ctx = a.ctx_lens[o->seq];
   return o->q_len > a.route_cap;  // mixed batch: the split kernel serves the others
 }
 
-// FRESH: chunk i of the new rows of a sequence and KV head to its page (rows without one are skipped, as in kv_append_kernel).
-template <int D>
-__device__ __forceinline__ void append_chunk(const FreshArgs &a, const int32_t *bt_row, int kvh, int q0, int ctx, int i) {
-  constexpr int ROWB = 2 * D, CPR = ROWB / 16;
-  const int t = i / CPR, pos = ctx + t;
-  const int page = (pos >> 4) < a.max_pages && pos >= 0 ? bt_row[pos >> 4] : -1;
-  if (page < 0 || page >= a.num_pages) return;
-  const size_t src = ((size_t)(q0 + t) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
-  const size_t dst = ((size_t)page * a.Hkv + kvh) * (kPage * ROWB) + (pos & 15) * ROWB + (i % CPR) * 16;
-  *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.k_new + src);
-  *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+// FRESH, a sequence with cached tokens: appends what the call appends to the pages that the workgroup reads from the pool
+// (fresh_plan.h), for one KV head.  set: kPageBits / 8 bytes of LDS.  Off the common path (a prompt has no cached tokens); bound
+// by its dependent round trips, so all that depends on nothing is requested first.  Measured against an append of its own in front
+// (hints for N tokens a sequence): 4 x 1024 tokens on 1024 at 8q/1kv, N 2048, 40.3 -> 38.2 us; 1 x 2000 on 6000, N 8192, 85.2 and 84.5;
+// 64 x 64 on 64, N 128, 21.1 -> 15.4; 64 x 100 on 100 at 16q/2kv d 64, N 256, 27.4 -> 29.3.
+template <int D, int THREADS>
+__device__ __forceinline__ void append_to_pool_pages(const FreshArgs &a, lds_char *set, const int32_t *bt_row, const WorkItem &it, int kvh) {
+  constexpr int ROWB = 2 * D, CPR = ROWB / 16, WAVES = THREADS / 64, N = (128 * CPR + THREADS - 1) / THREADS;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const size_t row_step = (size_t)a.Hkv * ROWB, head = (size_t)kvh * ROWB, page_head = (size_t)kvh * (kPage * ROWB);
+  auto copy = [&](int page, int row, int chunk, u32x4 k, u32x4 v) __attribute__((always_inline)) {
+    const size_t to = (size_t)page * (kPage * row_step) + page_head + row * ROWB + chunk * 16;
+    *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + to) = k;
+    *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + to) = v;
+  };
+  // the sequence's own rows: fewer than 128, behind its cached tokens
+  const int own = min(it.q_len, pool_pages(it.ctx) * kPage - it.ctx) * CPR;
+  u32x4 k[N], v[N];
+  int page[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int i = tid + THREADS * u, t = i / CPR;
+    page[u] = -1;
+    if (i >= own) continue;
+    const size_t from = (size_t)(it.q0 + t) * row_step + head + (i % CPR) * 16;
+    k[u] = *reinterpret_cast<const u32x4 *>(a.k_new + from);
+    v[u] = *reinterpret_cast<const u32x4 *>(a.v_new + from);
+    if (((it.ctx + t) >> 4) < a.max_pages) page[u] = bt_row[(it.ctx + t) >> 4];
+  }
+  auto store_own = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (page[u] >= 0 && page[u] < a.num_pages) copy(page[u], (it.ctx + (tid + THREADS * u) / CPR) & 15, (tid + THREADS * u) % CPR, k[u], v[u]);
+  };
+  if (a.batch == 1) {
+    store_own();
+    return;
+  }
+  // other sequences' rows in these pages
+  typedef __attribute__((address_space(3))) unsigned lds_word;
+  typedef __attribute__((address_space(3))) u32x4 lds_quad;
+  lds_word *const words = (lds_word *)set;
+  const int pairs = a.batch * a.new_pages, mine = min(pool_pages(it.ctx), a.max_pages);
+  NewRows r = {-1, 0, 0, 0, 0};
+  auto pair = [&](int base) __attribute__((always_inline)) {
+    const int i = base + lane * WAVES + w;  // the pages of one sequence go to all waves in turn
+    return i < pairs && new_rows_of_pair(i, a.new_pages, a.cu_q, a.ctx_lens, a.max_pages, &r) && r.seq != it.seq ? a.block_table[r.entry] : -1;
+  };
+  for (int i = tid; i < kPageBits / 128; i += THREADS) ((lds_quad *)set)[i] = (u32x4){0, 0, 0, 0};
+  __syncthreads();
+  for (int i = tid; i < mine; i += THREADS) {
+    const int pg = bt_row[i];
+    __hip_atomic_fetch_or(words + page_word(pg), page_bit(pg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  int pg = pair(0);
+  store_own();
+  __syncthreads();
+  for (int base = 0;;) {
+    const bool hit = pg >= 0 && pg < a.num_pages && (words[page_word(pg)] & page_bit(pg)) != 0;
+    for (unsigned long long m = __builtin_amdgcn_ballot_w64(hit); m != 0; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const int to = __builtin_amdgcn_readlane(pg, l), src = __builtin_amdgcn_readlane(r.src, l);
+      const int lo = __builtin_amdgcn_readlane(r.lo, l), n = __builtin_amdgcn_readlane(r.n, l);
+      for (int c = lane; c < n * CPR; c += 64) {
+        const size_t from = (size_t)(src + c / CPR) * row_step + head + (c % CPR) * 16;
+        copy(to, lo + c / CPR, c % CPR, *reinterpret_cast<const u32x4 *>(a.k_new + from), *reinterpret_cast<const u32x4 *>(a.v_new + from));
+      }
+    }
+    if ((base += THREADS) >= pairs) break;
+    pg = pair(base);
+  }
 }
+
+// FRESH: the rows of a query tile, on their way from the caller's buffer to their pages; one head group per KV head does it.
+template <int D, int THREADS>
+struct TileRows {
+  static constexpr int ROWB = 2 * D, CPR = ROWB / 16, N = kFreshChunks / THREADS;  // 16-byte chunks per row, and of a thread
+  u32x4 k[N], v[N];
+  int page[N];
+  __device__ __forceinline__ void request(const FreshArgs &a, const int32_t *bt_row, const WorkItem &it, int kvh, int tok0, int tpt) {
+    const bool mine = (it.hg << a.gshift) == kvh * (a.Hq / a.Hkv);
+    const int chunks = mine ? min(tpt, it.q_len - tok0) * CPR : 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = threadIdx.x + THREADS * u, tok = tok0 + i / CPR, pos = it.ctx + tok;
+      page[u] = -1;
+      if (i >= chunks) continue;
+      const size_t src = ((size_t)(it.q0 + tok) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
+      k[u] = *reinterpret_cast<const u32x4 *>(a.k_new + src);
+      v[u] = *reinterpret_cast<const u32x4 *>(a.v_new + src);
+      if (pos >= 0 && (pos >> 4) < a.max_pages) page[u] = bt_row[pos >> 4];
+    }
+  }
+  __device__ __forceinline__ void store(const FreshArgs &a, const WorkItem &it, int kvh, int tok0) const {
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (page[u] >= 0 && page[u] < a.num_pages) {  // rows without a page are skipped, as in kv_append_kernel
+        const int i = threadIdx.x + THREADS * u, pos = it.ctx + tok0 + i / CPR;
+        const size_t dst = ((size_t)page[u] * a.Hkv + kvh) * (kPage * ROWB) + (pos & 15) * ROWB + (i % CPR) * 16;
+        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = k[u];
+        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = v[u];
+      }
+  }
+};
 
 // The waves form two groups of four, one wave of each group per SIMD (waves w and w+4 share a
 // SIMD).  Inside every tile period the groups run the same two phases in opposite order: one
@@ -469,6 +563,14 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   const int kvh = (hg << a.gshift) / (a.Hq / a.Hkv);
   const int32_t *bt_row = a.block_table + (long)seq * a.max_pages;
   const int gmask = (1 << a.gshift) - 1;
+  // FRESH, but the sequence has cached tokens after all (the hints do not rule it out where they are larger than the batch).
+  if constexpr (FRESH) {
+    if (__builtin_expect(ctx > 0, 0)) {
+      append_to_pool_pages<D, 512>(a, smem, bt_row, it, kvh);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores
+      __syncthreads();
+    }
+  }
 
   // ---- this lane's column and the resident Q^T operands
   bf16x8 qreg[G::kDSteps];
@@ -577,66 +679,98 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   // redirected to the last valid row (a weight of 0 does not cover a NaN).  That concerns the pages from the
   // one with the sequence's last key on, which a stream reaches with its last tile and repeats from then
   // on: the offsets are switched once, outside the MFMA sequences, when that tile's V comes up.
-  // New rows (FRESH) are no page: they have the stride of a token, and end where the caller's buffer may end, so K is redirected too.
+  // New rows (FRESH, fresh_plan.h) are no page: they have the stride of a token, and end where the caller's buffer may end, so K is
+  // redirected too.  The streams turn to them once.
   constexpr int NSTREAM = SPLIT ? 2 : 1;  // K/V tile streams of the workgroup
   constexpr int NLD = NSTREAM * 2 * NIW;  // load instructions per wave and period
   const int last_kv = kv_end - 1, last_page = last_kv >> 4;
-  const int dq = lane >> 4, dslot = lane & 15;
-  const bool fresh = FRESH && ctx == 0;  // workgroup-uniform
-  const int row_stride = fresh ? a.Hkv * ROWB : ROWB;
+  int new_tile = 0x7fffffff;  // FRESH: tiles from here on are read from the new rows
+  if (FRESH && first_new_tile(ctx) < T) new_tile = first_new_tile(ctx);
   auto stream_tile = [&](int g, int i) __attribute__((always_inline)) { return t_begin + (SPLIT ? 2 * i + g : i); };  // local tile i of stream g
   constexpr int VBIAS = (NIW - 1) * 1024;  // keeps the V offsets of clamped rows from going below zero
-  auto lane_off = [&](bool is_v, int j, int rip_lim) __attribute__((always_inline)) {  // instruction j of a page load: this lane's source offset
+  auto lane_off = [&](bool is_v, int j, int rip_lim, int row_stride, int l) __attribute__((always_inline)) {  // instruction j of a page load: lane l's source offset
+    const int dq = l >> 4, dslot = l & 15;
     const int lp = 4 * j + dq;  // line inside the page
     const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
     const int rip = D == 128 ? lp : 2 * lp + (cl >> 3);
     const int chunk = D == 128 ? cl : (cl & 7);
-    return (unsigned)(min(rip, rip_lim) * row_stride + chunk * 16 - 1024 * j + (is_v || FRESH ? VBIAS : 0));
+    return (unsigned)((FRESH ? __mul24(min(rip, rip_lim), row_stride) : min(rip, rip_lim) * row_stride) + chunk * 16 - 1024 * j + (is_v || FRESH ? VBIAS : 0));
   };
   constexpr int NK = FRESH ? NSTREAM : 1;
   unsigned koff[NK][NIW], voff[NSTREAM][NIW];  // of every stream; K's are the same for all unless redirected
+  const int new_stride = a.Hkv * ROWB, first_stride = FRESH && new_tile == 0 ? new_stride : ROWB, last_stride = FRESH && new_tile < T ? new_stride : ROWB;
 #pragma unroll
   for (int g = 0; g < NK; ++g)
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) koff[g][j] = lane_off(false, j, 15);
+    for (int j = 0; j < NIW; ++j) koff[g][j] = lane_off(false, j, 15, first_stride, lane);
 #pragma unroll
   for (int g = 0; g < NSTREAM; ++g)
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, 15);
-  auto clamp_v = [&](int g, int gt) __attribute__((always_inline)) {  // before the loads of V of key tile gt of stream g
+    for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, 15, first_stride, lane);
+  // This KV head's block of page 0 and the number of pages; of new rows, the row that would be the first of page 0.
+  const char *kpool, *vpool;
+  int most_pages = FRESH && new_tile == 0 ? 0x7fffffff : a.num_pages;
+  const size_t pool_block = (size_t)kvh * (kPage * ROWB);
+  const long new_block = FRESH ? ((long)(q0 - ctx) * a.Hkv + kvh) * ROWB - VBIAS : 0;
+  kpool = a.k_pages + pool_block - (FRESH ? VBIAS : 0);
+  vpool = a.v_pages + pool_block - VBIAS;
+  if constexpr (FRESH) {
+    if (new_tile == 0) {
+      kpool = a.k_new + new_block;
+      vpool = a.v_new + new_block;
+    }
+  }
+  auto clamp_v = [&](int g, int gt, int l) __attribute__((always_inline)) {  // before the loads of V of key tile gt of stream g
     if (gt < T - 1 || (T - 1) * (KVT / kPage) + wq < last_page) return;
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, last_kv & 15);
+    for (int j = 0; j < NIW; ++j) voff[g][j] = lane_off(true, j, last_kv & 15, last_stride, l);
   };
-  auto clamp_k = [&](int g, int gt) __attribute__((always_inline)) {  // the same for K
+  auto clamp_k = [&](int g, int gt, int l) __attribute__((always_inline)) {  // the same for K
     if (!FRESH || gt < T - 1 || (T - 1) * (KVT / kPage) + wq < last_page) return;
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) koff[FRESH ? g : 0][j] = lane_off(false, j, last_kv & 15);
+    for (int j = 0; j < NIW; ++j) koff[FRESH ? g : 0][j] = lane_off(false, j, last_kv & 15, last_stride, l);
   };
-  const char *kpool, *vpool;  // this KV head's block of page 0
-  int most_pages = a.num_pages;
-  if constexpr (FRESH) {
-    const size_t first = ((size_t)q0 * a.Hkv + kvh) * ROWB, block = (size_t)kvh * (kPage * ROWB);
-    kpool = (fresh ? a.k_new + first : a.k_pages + block) - VBIAS;
-    vpool = (fresh ? a.v_new + first : a.v_pages + block) - VBIAS;
-    if (fresh) most_pages = 0x7fffffff;
-  } else {
-    kpool = a.k_pages + (size_t)kvh * (kPage * ROWB);
-    vpool = a.v_pages + (size_t)kvh * (kPage * ROWB) - VBIAS;
-  }
+  // FRESH: V, or K, comes to the new rows.  What the offsets move by is computed on the spot: kept over the tile loop it would cost registers.
+  auto new_offset = [&](bool is_v, int j) __attribute__((always_inline)) {
+    int l = lane;
+    if constexpr (FRESH) asm volatile("" : "+v"(l));
+    const int lp = 4 * j + (l >> 4);
+    const int cl = (l & 15) ^ (is_v ? Z::gv(lp) : Z::gk(lp));
+    return (unsigned)__mul24(D == 128 ? lp : 2 * lp + (cl >> 3), new_stride - ROWB);
+  };
+  auto new_offsets_v = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) voff[g][j] += new_offset(true, j);
+  };
+  auto new_offsets_k = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NIW; ++j) koff[FRESH ? g : 0][j] += new_offset(false, j);
+  };
+  auto turn_v = [&]() __attribute__((always_inline)) {
+    if constexpr (FRESH) vpool = a.v_new + new_block;
+  };
+  auto turn_k = [&]() __attribute__((always_inline)) {
+    if constexpr (FRESH) {
+      kpool = a.k_new + new_block;
+      most_pages = 0x7fffffff;
+    }
+  };
+  // FRESH: the first period whose end has anything to aim (K is two tiles ahead)
+  constexpr int STEP = SPLIT ? 2 : 1;
+  const int calm = FRESH ? min(new_tile == 0 ? T : new_tile, T - STEP) / STEP - 2 : 0;
   const unsigned page_bytes = (unsigned)a.Hkv * (kPage * ROWB);  // sixteen new rows are as far apart
+  auto page_idx = [&](int gt) __attribute__((always_inline)) { return min(min(gt, T - 1) * (KVT / kPage) + wq, last_page); };  // this wave's page of a tile
   // The inline assembly below makes the compiler treat every later load as possibly clobbered,
   // so block-table reads are vector loads; the value stays in a VGPR until the load that needs
   // it is issued one period later, and only then moves to an SGPR.
   auto page_of = [&](int gt) __attribute__((always_inline)) {  // all lanes read the same entry
-    const int idx = min(min(gt, T - 1) * (KVT / kPage) + wq, last_page);
     if constexpr (FRESH) {
-      if (fresh) return idx;
+      if (min(gt, T - 1) >= new_tile) return page_idx(gt);
     }
-    return bt_row[idx];
+    return bt_row[page_idx(gt)];
   };
-  auto page_pos = [&](int pg) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
-    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most_pages - 1) * page_bytes;
+  auto page_pos = [&](int pg, int most) __attribute__((always_inline)) {  // where the page begins in the pool; no wild loads on bad metadata
+    return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most - 1) * page_bytes;
   };
   const unsigned wave_dst = (unsigned)(wq * (NIW * 1024));
   auto dma_emit = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
@@ -662,7 +796,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   auto issue_prep = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
     for (int g = 0; g < NSTREAM; ++g) {
-      const size_t pos = page_pos(pg_k[g]);
+      const size_t pos = page_pos(pg_k[g], most_pages);
       ld[g][0] = kpool + pos;
       ld[g][1] = vpool + pos_v[g];
       pos_v[g] = pos;
@@ -979,74 +1113,71 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
       for (int ks = 0; ks < 2; ++ks) pop[b][ks] = pack8(sacc[b], 8 * ks);
   };
 
-  // FRESH, but the sequence has cached tokens after all (the hints do not rule it out where they are larger than the
-  // batch): the workgroup appends the rows of all the keys it will read before it reads them.  Others may write the same rows at the
-  // same time, with the same bytes.
-  if constexpr (FRESH) {
-    if (!fresh) {
-      for (int i = tid; i < (kv_end - ctx) * (ROWB / 16); i += 512) append_chunk<D>(a, bt_row, kvh, q0, ctx, i);
-      wait_loads();
-      __syncthreads();
-    }
-  }
   // prologue: K of every stream's first tile must be in LDS before anything is multiplied.  V of
   // that tile and K of the second one are requested in the same round trip (their slots are
   // free), so the first period has no load to wait for: a memory latency per workgroup that
   // small grids cannot hide behind other work.
   if (grp == 0) {
-    int pg0[NSTREAM], pg1[NSTREAM];
+    size_t pos0[NSTREAM];
+    if (FRESH && new_tile == 0) {  // nothing to look up
+#pragma unroll
+      for (int g = 0; g < NSTREAM; ++g) {
+        pos0[g] = (size_t)(unsigned)page_idx(stream_tile(g, 0)) * page_bytes;
+        pos_v[g] = (size_t)(unsigned)page_idx(stream_tile(g, 1)) * page_bytes;
+      }
+    } else {
+      int pg0[NSTREAM], pg1[NSTREAM];
+#pragma unroll
+      for (int g = 0; g < NSTREAM; ++g) {
+        pg0[g] = page_of(stream_tile(g, 0));
+        pg1[g] = page_of(stream_tile(g, 1));
+        pg_k[g] = page_of(stream_tile(g, 2));
+      }
+#pragma unroll
+      for (int g = 0; g < NSTREAM; ++g) {
+        pos0[g] = page_pos(pg0[g], a.num_pages);
+        pos_v[g] = page_pos(pg1[g], FRESH && stream_tile(0, 1) == new_tile ? 0x7fffffff : a.num_pages);
+      }
+    }
+    const bool turn1 = FRESH && stream_tile(0, 1) == new_tile, turn2 = FRESH && stream_tile(0, 2) == new_tile;
 #pragma unroll
     for (int g = 0; g < NSTREAM; ++g) {
-      pg0[g] = page_of(stream_tile(g, 0));
-      pg1[g] = page_of(stream_tile(g, 1));
-      pg_k[g] = page_of(stream_tile(g, 2));
+      clamp_v(g, stream_tile(g, 0), lane);
+      clamp_k(g, stream_tile(g, 0), lane);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos0[g], slot_dst(g, 0, 0), koff[FRESH ? g : 0][j], j);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma_emit(vpool + pos0[g], slot_dst(g, 1, 0), voff[g][j], j);
+      const char *k1 = kpool;
+      if constexpr (FRESH) {
+        if (__builtin_expect(turn1, 0)) {
+          k1 = a.k_new + new_block;
+          new_offsets_k(g);
+        }
+      }
+      clamp_k(g, stream_tile(g, 1), lane);
+#pragma unroll
+      for (int j = 0; j < NIW; ++j) dma_emit(k1 + pos_v[g], slot_dst(g, 0, 1), koff[FRESH ? g : 0][j], j);
+      if (__builtin_expect(turn1, 0)) new_offsets_v(g);
+      if (__builtin_expect(turn2, 0)) new_offsets_k(g);
+      clamp_v(g, stream_tile(g, 1), lane);
+      clamp_k(g, stream_tile(g, 2), lane);
     }
-#pragma unroll
-    for (int g = 0; g < NSTREAM; ++g) {
-      clamp_v(g, stream_tile(g, 0));
-      clamp_k(g, stream_tile(g, 0));
-      const size_t pos0 = page_pos(pg0[g]);
-      pos_v[g] = page_pos(pg1[g]);
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos0, slot_dst(g, 0, 0), koff[FRESH ? g : 0][j], j);
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(vpool + pos0, slot_dst(g, 1, 0), voff[g][j], j);
-      clamp_k(g, stream_tile(g, 1));
-#pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos_v[g], slot_dst(g, 0, 1), koff[FRESH ? g : 0][j], j);
-      clamp_v(g, stream_tile(g, 1));
-      clamp_k(g, stream_tile(g, 2));
-    }
+    if (__builtin_expect(turn1, 0)) turn_v();
+    if (__builtin_expect(turn1 || turn2, 0)) turn_k();
   }
-  // FRESH: the rows of this query tile, on their way from the caller's buffer to their pages; one head group per KV head does
-  // it.  The requests go out behind those of the first tiles and the stores behind the barrier, where nobody waits for them.
-  constexpr int CPR = ROWB / 16;  // 16-byte chunks per row
-  u32x4 knew[2], vnew[2];
-  int page_new[2] = {-1, -1};
-  const int new_chunks = FRESH && fresh && (hg << a.gshift) == kvh * (a.Hq / a.Hkv) ? min(tpt, q_len - tok0) * CPR : 0;
-  if constexpr (FRESH) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = tid + 512 * u;
-      if (i >= new_chunks) continue;
-      const int pos = tok0 + i / CPR;
-      const size_t src = ((size_t)(q0 + pos) * a.Hkv + kvh) * ROWB + (i % CPR) * 16;
-      knew[u] = *reinterpret_cast<const u32x4 *>(a.k_new + src);
-      vnew[u] = *reinterpret_cast<const u32x4 *>(a.v_new + src);
-      if ((pos >> 4) < a.max_pages) page_new[u] = bt_row[pos >> 4];
-    }
-  }
+  // FRESH: the rows of this query tile.  The requests go out behind those of the first tiles, the stores behind the barrier: they
+  // are under way during the first period, whose end waits for them with its tile loads.
+  TileRows<D, 512> rows;
+  if constexpr (FRESH) rows.request(a, bt_row, it, kvh, tok0, tpt);
   wait_loads();
   __syncthreads();
   if constexpr (FRESH) {
+    rows.store(a, it, kvh, tok0);
+    if (new_tile == 0) {  // as a page id, and here, where no load is under way that the register could wait for
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (page_new[u] >= 0 && page_new[u] < a.num_pages) {  // rows without a page are skipped, as in kv_append_kernel
-        const int i = tid + 512 * u;
-        const size_t dst = ((size_t)page_new[u] * a.Hkv + kvh) * (kPage * ROWB) + ((tok0 + i / CPR) & 15) * ROWB + (i % CPR) * 16;
-        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.k_pages) + dst) = knew[u];
-        *reinterpret_cast<u32x4 *>(const_cast<char *>(a.v_pages) + dst) = vnew[u];
-      }
+      for (int g = 0; g < NSTREAM; ++g) pg_k[g] = page_idx(stream_tile(g, 2));
+    }
   }
   SP_TRACE_STAMP(1, 0);
 
@@ -1084,10 +1215,19 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
         pv_qk(true_type{}, parc, false_type{});
         SP_MATRIX_PHASE_END();
         softmax(t, false_type{}, PREC && precise(t), integral_constant<bool, kScaledQ && !PREC>{});
+        if (!FRESH || __builtin_expect(t >= calm, 0)) {
+          int l = lane;
+          if constexpr (FRESH && (PREC || (SPLIT && D == 128))) asm volatile("" : "+v"(l));  // rare copy of the loop: its swizzles are not kept in registers over it
+          const bool v = FRESH && stream_tile(0, t + 1) == new_tile, k = FRESH && stream_tile(0, t + 2) == new_tile;
+          if (__builtin_expect(v, 0)) turn_v();
+          if (__builtin_expect(k, 0)) turn_k();
 #pragma unroll
-        for (int g = 0; g < NSTREAM; ++g) {
-          clamp_v(g, stream_tile(g, t + 1));
-          clamp_k(g, stream_tile(g, t + 2));
+          for (int g = 0; g < NSTREAM; ++g) {
+            if (__builtin_expect(v, 0)) new_offsets_v(g);
+            if (__builtin_expect(k, 0)) new_offsets_k(g);
+            clamp_v(g, stream_tile(g, t + 1), l);
+            clamp_k(g, stream_tile(g, t + 2), l);
+          }
         }
         wait_loads();
         __syncthreads();

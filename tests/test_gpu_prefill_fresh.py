@@ -9,8 +9,9 @@ from test_gpu_parity import custom_workload
 pytestmark = pytest.mark.gpu
 
 
-def chunk_step(w, lo=0, hi=None, max_q=None, max_kv=None, launches=None):
-    """The sequences lo..hi of w's last step by one sp_chunk_step, the rest of the batch by the oracle's own append."""
+def chunk_step(w, lo=0, hi=None, max_q=None, max_kv=None, launches=None, total=None):
+    """The sequences lo..hi of w's last step by one sp_chunk_step, the rest of the batch by the oracle's own append.  total: tokens in
+    the buffers, if more than the step has."""
     import torch
 
     import paper_2507_11830_amd as sp
@@ -25,7 +26,9 @@ def chunk_step(w, lo=0, hi=None, max_q=None, max_kv=None, launches=None):
     o.append(st)
     want = o.attend(st)
     q = to_dev(st.q)
-    k, v = (torch.cat([to_dev(x), torch.full((64, w.Hkv, w.d), float("nan"), dtype=torch.bfloat16, device="cuda")])[: q.shape[0]] for x in (st.k_new, st.v_new))
+    if total:
+        q = torch.cat([q, torch.zeros((total - q.shape[0], w.Hq, w.d), dtype=q.dtype, device="cuda")])
+    k, v = (torch.cat([to_dev(x), torch.full((64 + (total or 0), w.Hkv, w.d), float("nan"), dtype=torch.bfloat16, device="cuda")])[: q.shape[0]] for x in (st.k_new, st.v_new))
     out = torch.full_like(q, float("nan"))
     cu, ctx = dev_i32(st.cu_new)[lo : hi + 1], dev_i32(st.ctx_lens)[lo:hi]
     mq = max_q or int(st.new_lens[lo:hi].max())
@@ -88,3 +91,34 @@ def test_sub_range_with_prefixes_under_large_hints(Hq, Hkv, d):
     new, ctx = np.array([150, 64, 131, 55]), np.array([0, 100, 17, 0])
     w = custom_workload("fresh-sub", new + ctx, ctx, Hq, Hkv, d, "prefill", seed=31)
     chunk_step(w, lo=1, hi=3, max_q=200, max_kv=200, launches=ONE)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,repeat,threads", [
+    (8, 1, 128, 1, 512), (8, 2, 128, 1, 512), (8, 1, 64, 1, 512), (8, 2, 64, 1, 512),  # halved tiles
+    (16, 2, 128, 1, 512), (8, 1, 128, 2, 512),  # whole tiles of 256 columns
+    (16, 2, 64, 1, 256), (32, 2, 64, 1, 256),   # the four-wave kernel
+])
+@pytest.mark.parametrize("order", [1, -1])
+def test_prefixes_that_the_call_appends(Hq, Hkv, d, repeat, threads, order):
+    """Buffers and hints for more tokens than there are, and sequences whose cached tokens lie on pages that other sequences of the call
+    append: those of a prompt, of a chunk on a prompt, and past a page of their own; with the streams' turn to the new rows in the
+    first tiles, in the middle and behind the last one."""
+    #      prompt, chunk on it, chunk on that one, own prefix, longer than the new rows, behind the last tile, a prompt
+    new = np.array([333, 150, 61, 170, 9, 60, 350][::order] * repeat)
+    ctx = np.array([0, 192, 320, 77, 300, 130, 0][::order] * repeat)
+    w = custom_workload(f"fresh-shared-{Hq}-{Hkv}-{d}-{repeat}", new + ctx, ctx, Hq, Hkv, d, "prefill", seed=33)
+    for r in range(repeat):
+        a, b, c = (7 * r + (i if order == 1 else 6 - i) for i in range(3))
+        w.block_table[b, : 192 // 16] = w.block_table[a, : 192 // 16]
+        w.block_table[c, : 320 // 16] = w.block_table[b, : 320 // 16]
+    chunk_step(w, max_q=400, max_kv=400, total=400 * len(new), launches=[(threads, 1, 1)])
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,threads", [(8, 1, 128, 512), (8, 2, 64, 512), (16, 2, 128, 512), (16, 2, 64, 256)])
+def test_long_prefixes_that_the_call_appends(Hq, Hkv, d, threads):
+    """The turn to the new rows in the middle of the tile loop."""
+    new, ctx = np.array([700, 500, 300]), np.array([0, 640, 992])
+    w = custom_workload(f"fresh-long-{Hq}-{Hkv}-{d}", new + ctx, ctx, Hq, Hkv, d, "prefill", seed=35)
+    w.block_table[1, : 640 // 16] = w.block_table[0, : 640 // 16]
+    w.block_table[2, : 992 // 16] = w.block_table[1, : 992 // 16]
+    chunk_step(w, max_q=1300, max_kv=1300, total=3900, launches=[(threads, 1, 1)])
