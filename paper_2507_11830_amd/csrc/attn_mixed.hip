@@ -33,7 +33,7 @@ static int launch_mixed_d(const PrefillArgs &a, const DecodeArgs &d, int shares,
   static_cast<PrefillArgs &>(m) = a;
   m.d = d;
   dim3 grid;
-  if (int rc = prefill_grid(m, SPLIT ? 128 : 256, batch, max_q_len, &grid)) return rc;
+  if (int rc = prefill_grid(m, SPLIT ? 128 : 256, batch, max_q_len, 1, &grid)) return rc;
   if (!m.ranked || grid.x > 0x7fffffffu - (unsigned)shares) return 1;
   m.first_other = grid.x;
   grid.x += (unsigned)shares;

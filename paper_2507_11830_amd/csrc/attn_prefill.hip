@@ -88,7 +88,7 @@ static int launch_prefill_d(const PrefillArgs &a, bool split, int batch, int max
   // budget of two workgroups per CU).
   if (a.kv_splits > 1) return launch_cfg(prefill_kernel<D, KVT, PFD, true, true, 0>, &set[0], 2 * smem, 128, a, batch, max_q_len, stream);
   if (split) return launch_cfg(prefill_kernel<D, KVT, PFD, true, false, 0>, &set[1], 2 * smem, 128, a, batch, max_q_len, stream);
-  if constexpr (D == 64) return launch_cfg(solo_prefill_kernel<PrefillArgs>, &set[2], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads);
+  if constexpr (D == 64) return launch_cfg(solo_prefill_kernel<PrefillArgs>, &set[2], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads, kSoloLayers);
   else return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0>, &set[2], smem, 256, a, batch, max_q_len, stream);
 }
 

@@ -18,7 +18,7 @@ static int launch_fresh_d(const FreshArgs &a, bool split, int batch, int max_q_l
   constexpr size_t smem = kPrefillSmem<D>;
   static bool set[2] = {false, false};
   if (split) return launch_cfg(prefill_kernel<D, KVT, PFD, true, false, 0, FreshArgs>, &set[0], 2 * smem, 128, a, batch, max_q_len, stream);
-  if constexpr (D == 64) return launch_cfg(solo_prefill_kernel<FreshArgs>, &set[1], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads);
+  if constexpr (D == 64) return launch_cfg(solo_prefill_kernel<FreshArgs>, &set[1], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads, kSoloLayers);
   else return launch_cfg(prefill_kernel<D, KVT, PFD, false, false, 0, FreshArgs>, &set[1], smem, 256, a, batch, max_q_len, stream);
 }
 

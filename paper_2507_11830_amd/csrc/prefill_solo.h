@@ -26,6 +26,7 @@
 namespace sp {
 
 constexpr int kSoloThreads = 256, kSoloCols = 128, kSoloKSlots = 3, kSoloVSlots = 2;
+constexpr int kSoloLayers = 2;  // half as many columns as the two-group kernel: twice as many query tiles, for the same longest chunk
 constexpr size_t kSoloSmem = (kSoloKSlots + kSoloVSlots) * (size_t)KVT * 64 * 2;
 
 template <typename Args>

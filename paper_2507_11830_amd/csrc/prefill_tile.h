@@ -366,8 +366,9 @@ __device__ __forceinline__ bool take_item(const PrefillArgs &a, int cols_shift, 
   }
   o->seq = sh / a.n_hgroups;
   o->hg = sh - o->seq * a.n_hgroups;
-  o->piece = row / (int)gridDim.y;
+  o->piece = SNAKE ? 0 : row / (int)gridDim.y;  // SNAKE kernels have no pieces: their blockIdx.z is the second half of many tiles
   o->tile = a.ntiles_x - 1 - (row - o->piece * (int)gridDim.y);
+  if (SNAKE && o->tile < 0) return false;
   o->ctx = a.ctx_lens[o->seq];
   o->q0 = a.cu_q[o->seq];
   o->q_len = a.cu_q[o->seq + 1] - o->q0;
@@ -1385,13 +1386,14 @@ template <int D>
 constexpr size_t kPrefillSmem = 4 * (size_t)KVT * D * 2;  // K[2] V[2], unpadded
 
 // Launch index space of `cols` query columns per workgroup; completes a.  SP_ERR_BAD_SHAPE if it exceeds the limits.
-inline int prefill_grid(PrefillArgs &a, int cols, int batch, int max_q_len, dim3 *grid) {
+inline int prefill_grid(PrefillArgs &a, int cols, int batch, int max_q_len, int layers, dim3 *grid) {
   int tpt = cols >> a.gshift;
   a.ntiles_x = (max_q_len + tpt - 1) / tpt;
   long gx = (long)batch * a.n_hgroups;
-  if (gx > 0x7fffffffL || a.ntiles_x > 65535)
+  if (gx > 0x7fffffffL || a.ntiles_x > 65535 * layers)
     return fail(SP_ERR_BAD_SHAPE, "sp_attn_prefill: grid %ld x %d exceeds the launch limits", gx, a.ntiles_x);
-  *grid = dim3((unsigned)gx, (unsigned)a.ntiles_x, (unsigned)a.kv_splits);
+  const int z = a.ntiles_x > 65535 ? layers : 1;
+  *grid = dim3((unsigned)gx, (unsigned)((a.ntiles_x + z - 1) / z), (unsigned)(a.kv_splits * z));
   if (a.ranked) {
     // Ranked workgroups take items by linear id, so the launch only needs as many workgroups as
     // there can be items (ranked_workgroups).  (The grid of
@@ -1413,13 +1415,14 @@ inline int grant_smem(const void *fn, bool *done, size_t smem) {
   return SP_OK;
 }
 
-// Launches one prefill kernel instantiation with `cols` query columns per workgroup.
+// Launches one prefill kernel instantiation with `cols` query columns per workgroup.  layers: how many times 65535 query tiles of a
+// sequence it takes (a kernel without pieces: blockIdx.z is theirs).
 template <typename Args>
 inline int launch_cfg(void (*fn)(Args), bool *attr_set, size_t smem, int cols, const Args &a0, int batch, int max_q_len,
-                      hipStream_t stream, int threads = 512) {
+                      hipStream_t stream, int threads = 512, int layers = 1) {
   Args a = a0;
   dim3 grid;
-  if (int rc = prefill_grid(a, cols, batch, max_q_len, &grid)) return rc;
+  if (int rc = prefill_grid(a, cols, batch, max_q_len, layers, &grid)) return rc;
   if (int rc = grant_smem((const void *)fn, attr_set, smem)) return rc;
   hipLaunchKernelGGL(fn, grid, dim3((unsigned)threads), smem, stream, a);
   hipError_t e = hipGetLastError();

@@ -29,3 +29,30 @@ def whole_grids():
 def test_rounds_of_resident_workgroups(name, Hq, Hkv, new, ctx):
     new, ctx = np.array(new), np.array(ctx)
     run_full_compare(custom_workload(f"solo-{name}", new + ctx, ctx, Hq, Hkv, 64, "prefill", seed=77))
+
+
+@pytest.mark.parametrize("new", [[700, 650], [330, 300, 340, 310]])  # with and without streams of their own for the XCDs
+def test_chunk_hints_of_more_tiles_than_one_grid_dimension_holds(new):
+    """32 heads a query tile leave it 4 tokens: 75000 tiles of a longest chunk of 300000, as a caller's fixed bound may be."""
+    import torch
+
+    import paper_2507_11830_amd as sp
+    from harness import TOL, GpuRunner, OracleRunner, bits_of, dev_i32, report_err, to_dev
+
+    new = np.array(new)
+    w = custom_workload("solo-many-tiles", new, 0 * new, 64, 1, 64, "prefill", seed=79)
+    g, o = GpuRunner(w), OracleRunner(w)
+    (st,) = w.steps()
+    o.append(st)
+    q = to_dev(st.q)
+    want = o.attend(st)
+    for step in (False, True):  # attention after an append of its own, and with it
+        out = torch.full_like(q, float("nan"))
+        hint = 300000
+        if step:
+            sp.sp_chunk_step(g.cache, to_dev(st.k_new), to_dev(st.v_new), q, out, dev_i32(st.cu_new), dev_i32(st.ctx_lens), g.bt, hint, hint, float(w.scale))
+        else:
+            g.append(st)
+            sp.sp_attn_prefill(g.cache, q, out, dev_i32(st.cu_new), dev_i32(st.ctx_lens), g.bt, hint, hint, float(w.scale))
+        torch.cuda.synchronize()
+        assert report_err(w.name, bits_of(out), want) <= TOL
