@@ -58,4 +58,10 @@ SP_HD bool new_rows_of_pair(int i, int per, const int *cu_q, const int *ctx_lens
   return true;
 }
 
+// Whether n bytes at p and m bytes at q have none in common.
+inline bool apart(const void *p, long n, const void *q, long m) {
+  const unsigned long a = (unsigned long)p, b = (unsigned long)q;
+  return a < b ? b - a >= (unsigned long)n : a - b >= (unsigned long)m;
+}
+
 }  // namespace sp

@@ -6,6 +6,8 @@
 
 extern "C" {
 
+int apart(const void *p, long n, const void *q, long m) { return sp::apart(p, n, q, m); }
+
 int pool_pages(int ctx) { return sp::pool_pages(ctx); }
 
 // Rows (page, row of it, new row) that a workgroup of sequence seq appends to the pages it reads from the pool; returns their number.

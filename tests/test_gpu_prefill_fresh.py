@@ -9,9 +9,9 @@ from test_gpu_parity import custom_workload
 pytestmark = pytest.mark.gpu
 
 
-def chunk_step(w, lo=0, hi=None, max_q=None, max_kv=None, launches=None, total=None):
+def chunk_step(w, lo=0, hi=None, max_q=None, max_kv=None, launches=None, total=None, buffers=None):
     """The sequences lo..hi of w's last step by one sp_chunk_step, the rest of the batch by the oracle's own append.  total: tokens in
-    the buffers, if more than the step has."""
+    the buffers, if more than the step has.  buffers: (k, v, out) -> the ones to use."""
     import torch
 
     import paper_2507_11830_amd as sp
@@ -30,6 +30,8 @@ def chunk_step(w, lo=0, hi=None, max_q=None, max_kv=None, launches=None, total=N
         q = torch.cat([q, torch.zeros((total - q.shape[0], w.Hq, w.d), dtype=q.dtype, device="cuda")])
     k, v = (torch.cat([to_dev(x), torch.full((64 + (total or 0), w.Hkv, w.d), float("nan"), dtype=torch.bfloat16, device="cuda")])[: q.shape[0]] for x in (st.k_new, st.v_new))
     out = torch.full_like(q, float("nan"))
+    if buffers:
+        k, v, out = buffers(k, v, out)
     cu, ctx = dev_i32(st.cu_new)[lo : hi + 1], dev_i32(st.ctx_lens)[lo:hi]
     mq = max_q or int(st.new_lens[lo:hi].max())
     mkv = max_kv or int(st.seq_lens[lo:hi].max())
@@ -122,3 +124,20 @@ def test_long_prefixes_that_the_call_appends(Hq, Hkv, d, threads):
     w.block_table[1, : 640 // 16] = w.block_table[0, : 640 // 16]
     w.block_table[2, : 992 // 16] = w.block_table[1, : 992 // 16]
     chunk_step(w, max_q=1300, max_kv=1300, total=3900, launches=[(threads, 1, 1)])
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,reuse", [(2, 2, 64, "k"), (2, 2, 64, "v"), (4, 1, 128, "v"), (4, 1, 128, None)])
+def test_out_in_the_new_rows_buffers(Hq, Hkv, d, reuse):
+    """The caller has no more use for the new rows once they are appended."""
+    import torch
+
+    def buffers(k, v, out):
+        if reuse is None:
+            return k, v, out
+        big = torch.empty_like(out)  # the rows at its end
+        rows = big.view(-1)[big.numel() - k.numel() :].view(k.shape)
+        rows.copy_(k if reuse == "k" else v)
+        return (rows, v, big) if reuse == "k" else (k, rows, big)
+
+    lens = np.full(2, 300)
+    chunk_step(custom_workload(f"fresh-reuse-{Hq}-{d}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=11), launches=TWO if reuse else ONE, buffers=buffers)

@@ -81,3 +81,10 @@ def test_sequences_without_cached_tokens_read_nothing_from_the_pool(plan):
     assert plan.pool_pages(0) == 0
     assert [plan.pool_pages(c) for c in (1, 128, 129)] == [8, 8, 16]
     assert plan.pool_pages(-5) * 16 > 1 << 30  # bad lengths: never the caller's buffer
+
+
+@pytest.mark.parametrize("p,n,q,m,want", [(1000, 24, 1024, 8, 1), (1000, 25, 1024, 8, 0), (1024, 8, 1000, 24, 1), (1024, 8, 1000, 25, 0),
+                                          (1000, 8, 1000, 8, 0), (1000, 100, 1010, 5, 0), (1010, 5, 1000, 100, 0)])
+def test_buffers_that_share_bytes(plan, p, n, q, m, want):
+    arg = [ctypes.c_void_p(p), ctypes.c_long(n), ctypes.c_void_p(q), ctypes.c_long(m)]
+    assert plan.apart(*arg) == want
