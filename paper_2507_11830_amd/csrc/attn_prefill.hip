@@ -229,14 +229,16 @@ static int prefill_chunks(const sp_cache_desc &c, const void *k_new, const void 
   // at most that together have batch x max_q_len are all that long, and with max_kv_len no larger have no prefix.  The hints may
   // also stand for more tokens than there are (a sub-range, padded buffers), so that sequences do have prefixes, which may lie on
   // pages that the call appends: a workgroup that meets one sees to it that what it reads is there (fresh_plan.h).
-  // An `out` that reuses the new rows' buffers would be written while others still read them.
+  // An `out` that reuses the new rows' buffers would be written while others still read them; and the loads to LDS take 16 bytes of
+  // the new rows at a time, which the append kernel does from any address.
   // The heads of a KV head have to share query tiles, of few enough rows that a thread moves a few chunks of them, and row offsets
   // are products of 24 bits.
   if (k_new) {
     const int tile = (split || c.head_dim == 64 ? 128 : 256) >> gshift;
     if ((group & (group - 1)) == 0 && tile * (c.head_dim / 8) <= kFreshChunks && (long)batch * max_q_len == total_q && max_kv_len <= max_q_len &&
         kvs == 1 && a.cut_slots == 0 && a.route_cap == 0 && (long)c.num_kv_heads * c.head_dim * 2 < (1L << 23) &&
-        apart(out, rows * c.head_dim * 2, k_new, rows / group * c.head_dim * 2) && apart(out, rows * c.head_dim * 2, v_new, rows / group * c.head_dim * 2)) {
+        apart(out, rows * c.head_dim * 2, k_new, rows / group * c.head_dim * 2) && apart(out, rows * c.head_dim * 2, v_new, rows / group * c.head_dim * 2) &&
+        (((uintptr_t)k_new | (uintptr_t)v_new) & 15) == 0) {
       FreshArgs f;
       static_cast<PrefillArgs &>(f) = a;
       f.k_new = (const char *)k_new;

@@ -141,3 +141,17 @@ def test_out_in_the_new_rows_buffers(Hq, Hkv, d, reuse):
 
     lens = np.full(2, 300)
     chunk_step(custom_workload(f"fresh-reuse-{Hq}-{d}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=11), launches=TWO if reuse else ONE, buffers=buffers)
+
+
+@pytest.mark.parametrize("which,launches", [("k", TWO), ("v", TWO), ("", ONE)])
+def test_new_rows_off_a_16_byte_boundary(which, launches):
+    import torch
+
+    def moved(x):
+        big = torch.empty(x.numel() + 4, dtype=x.dtype, device=x.device)
+        big[4:] = x.reshape(-1)
+        return big[4:].view(x.shape)
+
+    lens = np.full(2, 300)
+    chunk_step(custom_workload(f"fresh-moved-{which}", lens, 0 * lens, 8, 1, 128, "prefill", seed=13), launches=launches,
+               buffers=lambda k, v, out: (moved(k) if which == "k" else k, moved(v) if which == "v" else v, out))
