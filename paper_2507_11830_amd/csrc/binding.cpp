@@ -6,6 +6,7 @@
 // conversion of 15 arguments cost 5 us, where the launch itself costs 2 to 3.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+#include <pthread.h>
 #include <stdint.h>
 
 #include "shiftattn.h"
@@ -22,7 +23,7 @@ Entry entries[kEntries] = {{"sp_kv_append", nullptr},   {"sp_attn_prefill", null
 PyObject *s_data_ptr, *s_shape, *s_numel, *s_element_size, *s_cuda_stream, *s_desc, *s_value;
 PyObject *argument_error;                         // ctypes.ArgumentError
 PyObject *get_device, *get_stream, *first_stream;  // torch's raw accessors; the public one, for the first call of the process
-bool stream_used = false;
+bool stream_used = false;  // the public accessor has been called in this process
 
 // Every helper returns false with a Python exception set.
 bool pointer(PyObject *t, void **p) {
@@ -292,6 +293,10 @@ PyMODINIT_FUNC PyInit__binding(void) {
     const char *text;
   } names[] = {{&s_data_ptr, "data_ptr"},       {&s_shape, "shape"}, {&s_numel, "numel"}, {&s_element_size, "element_size"},
                {&s_cuda_stream, "cuda_stream"}, {&s_desc, "desc"},   {&s_value, "value"}};
+  // In a forked child torch's device state is unusable: the public accessor says so, the raw ones go on.
+  static bool registered = false;
+  if (!registered && pthread_atfork(nullptr, nullptr, [] { stream_used = false; }) != 0) return PyErr_NoMemory();
+  registered = true;
   for (auto &x : names)
     if (!(*x.slot = PyUnicode_InternFromString(x.text))) return nullptr;
   return PyModule_Create(&module);

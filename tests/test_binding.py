@@ -108,3 +108,34 @@ def test_refuses_what_ctypes_refused(stub):
         N.attn_decode(Cache, q, out, lens, table, 5, "x", None, 0)
     with pytest.raises((TypeError, ValueError)):
         N.attn_decode(Cache, q, out, lens, table, 5, 0.1, None, "stream")
+
+
+def test_a_forked_child_asks_torch_for_the_stream_again(stub):
+    """torch's public accessor refuses to work in a child of a process that has used the device; the raw ones do not."""
+    N = sp._native
+    asked = []
+    L, _ = stub
+    table, q, out, lens = T(1 << 20, 6, 11), T(2 << 20, 40, 8, 128), T(3 << 20, 40, 8, 128), T(4 << 20, 6)
+    names = ("sp_kv_append", "sp_attn_prefill", "sp_chunk_step", "sp_attn_decode", "sp_attn_decode_static", "sp_decode_step")
+    N.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, ctypes.ArgumentError, lambda: 0, lambda dev: 0x1234, lambda: asked.append(1) or Stream())
+    try:
+        call = lambda: N.attn_decode(Cache, q, out, lens, table, 5, 0.1, None, None)
+        call()
+        first = len(asked)
+        call()
+        assert len(asked) == first  # the raw accessors from then on
+        r, w = os.pipe()
+        pid = os.fork()
+        if pid == 0:
+            try:
+                call()
+                os.write(w, bytes([len(asked) - first]))
+            finally:
+                os._exit(0)
+        os.close(w)
+        seen = os.read(r, 1)
+        os.close(r)
+        os.waitpid(pid, 0)
+        assert seen == b"\x01"
+    finally:
+        sp._bind(L)
