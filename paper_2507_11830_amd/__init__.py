@@ -67,7 +67,7 @@ def _bind(L: ctypes.CDLL):
     module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
     loader.exec_module(module)
     names = ("sp_kv_append", "sp_attn_prefill", "sp_chunk_step", "sp_attn_decode", "sp_attn_decode_static", "sp_decode_step")
-    module.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, ctypes.ArgumentError,
+    module.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, ctypes.ArgumentError, ctypes.c_int32, sp_cache_desc,
                 torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, torch.cuda.current_stream)
     _native = module
     return module

@@ -20,8 +20,8 @@ struct Entry {
 enum { kAppend, kPrefill, kChunkStep, kDecode, kDecodeStatic, kDecodeStep, kEntries };
 Entry entries[kEntries] = {{"sp_kv_append", nullptr},   {"sp_attn_prefill", nullptr},       {"sp_chunk_step", nullptr},
                            {"sp_attn_decode", nullptr}, {"sp_attn_decode_static", nullptr}, {"sp_decode_step", nullptr}};
-PyObject *s_data_ptr, *s_shape, *s_numel, *s_element_size, *s_cuda_stream, *s_desc, *s_value;
-PyObject *argument_error;                         // ctypes.ArgumentError
+PyObject *s_data_ptr, *s_shape, *s_numel, *s_element_size, *s_cuda_stream, *s_desc, *s_value, *s_as_parameter;
+PyObject *argument_error, *c_int32, *desc_type;    // ctypes.ArgumentError, ctypes.c_int32, sp_cache_desc
 PyObject *get_device, *get_stream, *first_stream;  // torch's raw accessors; the public one, for the first call of the process
 bool stream_used = false;  // the public accessor has been called in this process
 
@@ -36,17 +36,24 @@ bool pointer(PyObject *t, void **p) {
   return !(*p == nullptr && PyErr_Occurred());
 }
 
-bool int32(PyObject *o, int32_t *out) {  // out-of-range values keep their low bits, as in ctypes
+// What ctypes takes for a c_int32: one itself, an integer (out-of-range values keep their low bits), or an object that names either
+// of them in _as_parameter_.
+bool int32(PyObject *o, int32_t *out) {
   PyObject *v = PyFloat_Check(o) ? nullptr : PyNumber_Index(o);
   if (!v) {
     PyErr_Clear();
-    PyObject *inner = PyObject_GetAttr(o, s_value);  // a ctypes integer
-    if (inner) v = PyFloat_Check(inner) ? nullptr : PyNumber_Index(inner);
-    Py_XDECREF(inner);
-    if (!v) {
+    const int own = PyObject_IsInstance(o, c_int32);
+    PyObject *inner = own < 0 ? nullptr : PyObject_GetAttr(o, own ? s_value : s_as_parameter);
+    if (!inner) {
+      PyErr_Clear();
       PyErr_SetString(argument_error, "wrong type");
       return false;
     }
+    const bool deep = Py_EnterRecursiveCall(" while converting an argument") != 0;
+    const bool ok = !deep && int32(inner, out);
+    if (!deep) Py_LeaveRecursiveCall();
+    Py_DECREF(inner);
+    return ok;
   }
   *out = (int32_t)PyLong_AsUnsignedLongMask(v);
   Py_DECREF(v);
@@ -123,12 +130,10 @@ struct Desc {  // cache.desc, a ctypes structure: its memory
   bool take(PyObject *cache) {
     PyObject *d = PyObject_GetAttr(cache, s_desc);
     if (!d) return false;
-    held = PyObject_GetBuffer(d, &view, PyBUF_SIMPLE) == 0;
+    const int is = PyObject_IsInstance(d, desc_type);
+    if (is > 0) held = PyObject_GetBuffer(d, &view, PyBUF_SIMPLE) == 0;
+    else if (is == 0) PyErr_SetString(argument_error, "cache.desc is not a cache descriptor");
     Py_DECREF(d);
-    if (held && view.len != (Py_ssize_t)sizeof(sp_cache_desc)) {
-      PyErr_SetString(argument_error, "cache.desc is not a cache descriptor");
-      return false;
-    }
     return held;
   }
   const sp_cache_desc *get() const { return (const sp_cache_desc *)view.buf; }
@@ -259,11 +264,11 @@ PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   });
 }
 
-// bind(addresses, ArgumentError, get_device, get_stream, first_stream): addresses maps the C-ABI names to the loaded
-// library's functions
+// bind(addresses, ArgumentError, c_int32, sp_cache_desc, get_device, get_stream, first_stream): addresses maps the C-ABI names to the
+// loaded library's functions
 PyObject *bind(PyObject *, PyObject *args) {
-  PyObject *table, *err, *dev, *raw, *first;
-  if (!PyArg_ParseTuple(args, "O!OOOO", &PyDict_Type, &table, &err, &dev, &raw, &first)) return nullptr;
+  PyObject *table, *values[6];
+  if (!PyArg_ParseTuple(args, "O!OOOOOO", &PyDict_Type, &table, values, values + 1, values + 2, values + 3, values + 4, values + 5)) return nullptr;
   void *fn[kEntries];
   for (int i = 0; i < kEntries; ++i) {
     PyObject *v = PyDict_GetItemString(table, entries[i].name);
@@ -271,8 +276,8 @@ PyObject *bind(PyObject *, PyObject *args) {
     fn[i] = PyLong_AsVoidPtr(v);
     if (!fn[i]) return PyErr_Occurred() ? nullptr : PyErr_Format(PyExc_ValueError, "%s is NULL", entries[i].name);
   }
-  PyObject **slots[4] = {&argument_error, &get_device, &get_stream, &first_stream}, *values[4] = {err, dev, raw, first};
-  for (int i = 0; i < 4; ++i) {
+  PyObject **slots[6] = {&argument_error, &c_int32, &desc_type, &get_device, &get_stream, &first_stream};
+  for (int i = 0; i < 6; ++i) {
     Py_INCREF(values[i]);
     Py_XSETREF(*slots[i], values[i]);
   }
@@ -292,7 +297,7 @@ PyMODINIT_FUNC PyInit__binding(void) {
     PyObject **slot;
     const char *text;
   } names[] = {{&s_data_ptr, "data_ptr"},       {&s_shape, "shape"}, {&s_numel, "numel"}, {&s_element_size, "element_size"},
-               {&s_cuda_stream, "cuda_stream"}, {&s_desc, "desc"},   {&s_value, "value"}};
+               {&s_cuda_stream, "cuda_stream"}, {&s_desc, "desc"},   {&s_value, "value"},   {&s_as_parameter, "_as_parameter_"}};
   // In a forked child torch's device state is unusable: the public accessor says so, the raw ones go on.
   static bool registered = false;
   if (!registered && pthread_atfork(nullptr, nullptr, [] { stream_used = false; }) != 0) return PyErr_NoMemory();

@@ -51,7 +51,12 @@ def by_ctypes(L, name, desc, *args):
     return getattr(L, name)(ctypes.byref(desc), *args)
 
 
-I32S = (5, np.int64(9), np.int32(-3), True, 2**32 + 7, -1, ctypes.c_int32(4))
+class AsParameter:  # ctypes' own way to pass an object of the caller's
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+I32S = (5, np.int64(9), np.int32(-3), True, 2**32 + 7, -1, ctypes.c_int32(4), AsParameter(6), AsParameter(ctypes.c_int32(8)))
 STREAMS = ((0, 0), (0x1234_5678_9ABC, 0x1234_5678_9ABC), (Stream(), Stream.cuda_stream))
 
 
@@ -92,7 +97,10 @@ def test_same_arguments_as_ctypes(stub, n):
 def test_refuses_what_ctypes_refused(stub):
     N = sp._native
     table, q, out, lens = T(1 << 20, 6, 11), T(2 << 20, 40, 8, 128), T(3 << 20, 40, 8, 128), T(4 << 20, 6)
-    for bad in (5.0, "5", None, [1]):
+    class Value:  # an enumeration's member, say
+        value = 5
+
+    for bad in (5.0, "5", None, [1], Value(), ctypes.c_int64(5), ctypes.c_float(5), AsParameter(5.0), AsParameter(Value())):
         with pytest.raises(ctypes.ArgumentError):
             N.attn_decode(Cache, q, out, lens, table, bad, 0.1, None, 0)
     for bad_table in (T(1, 6), T(1, 6, 11, 2)):
@@ -104,6 +112,9 @@ def test_refuses_what_ctypes_refused(stub):
         N.attn_decode(Cache, q, object(), lens, table, 5, 0.1, None, 0)
     with pytest.raises(AttributeError):
         N.attn_decode(object(), q, out, lens, table, 5, 0.1, None, 0)
+    for desc in (bytes(32), bytearray(32), np.zeros(4), (ctypes.c_int64 * 4)(), None):  # of the descriptor's size, but none
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            N.attn_decode(type("Cache", (), {"desc": desc}), q, out, lens, table, 5, 0.1, None, 0)
     with pytest.raises((TypeError, ValueError)):
         N.attn_decode(Cache, q, out, lens, table, 5, "x", None, 0)
     with pytest.raises((TypeError, ValueError)):
@@ -117,7 +128,7 @@ def test_a_forked_child_asks_torch_for_the_stream_again(stub):
     L, _ = stub
     table, q, out, lens = T(1 << 20, 6, 11), T(2 << 20, 40, 8, 128), T(3 << 20, 40, 8, 128), T(4 << 20, 6)
     names = ("sp_kv_append", "sp_attn_prefill", "sp_chunk_step", "sp_attn_decode", "sp_attn_decode_static", "sp_decode_step")
-    N.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, ctypes.ArgumentError, lambda: 0, lambda dev: 0x1234, lambda: asked.append(1) or Stream())
+    N.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names}, ctypes.ArgumentError, ctypes.c_int32, sp.sp_cache_desc, lambda: 0, lambda dev: 0x1234, lambda: asked.append(1) or Stream())
     try:
         call = lambda: N.attn_decode(Cache, q, out, lens, table, 5, 0.1, None, None)
         call()
