@@ -22,7 +22,7 @@ if os.environ.get("SP_LIB_SANITIZE", "") == "1":
     # process must run with the matching sanitizer runtime preloaded)
     LIB_PATH = os.path.join(_HERE, "_build", "san", "libshiftattn_san.so")
 
-BINDING_PATH = os.path.join(_HERE, "_binding.so")
+BINDING_PATH = os.path.join(_HERE, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])  # built for this interpreter
 
 SP_OK = 0
 SP_ERR_NULL = -1

@@ -1,7 +1,7 @@
 """Build step: every HIP source under csrc/ compiled for gfx950 with hipcc and linked into
 libshiftattn.so next to this file (in-tree, so it travels with the repo), the Python entry points'
-argument marshalling into _binding.so; the benchmark's
-reference kernels under bench_kernels/ go into a shared object of their own, libspceilings.so.
+argument marshalling into _binding, named for the interpreter it is built for; the benchmark's reference
+kernels under bench_kernels/ go into a shared object of their own, libspceilings.so.
 
 ``python -m paper_2507_11830_amd.build --sanitize-host`` builds a second copy of libshiftattn
 whose HOST code is instrumented with AddressSanitizer + UndefinedBehaviorSanitizer
@@ -24,7 +24,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 BENCH_SRC = os.path.join(HERE, "bench_kernels")
 LIB = os.path.join(HERE, "libshiftattn.so")
 CEIL_LIB = os.path.join(HERE, "libspceilings.so")
-BINDING_LIB = os.path.join(HERE, "_binding.so")
+BINDING_LIB = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 SAN_LIB = os.path.join(OBJ_DIR, "san", "libshiftattn_san.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -47,6 +47,13 @@ def stub(tmp_path_factory):
     sp._bind(real)
 
 
+def test_the_file_is_named_for_its_interpreter():
+    """Another one does not find it, rather than load code made for other object layouts."""
+    import sysconfig
+
+    assert os.path.basename(sp.BINDING_PATH) == "_binding" + sysconfig.get_config_var("EXT_SUFFIX")
+
+
 def by_ctypes(L, name, desc, *args):
     return getattr(L, name)(ctypes.byref(desc), *args)
 
