@@ -17,12 +17,12 @@ from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libshiftattn.so")
+BINDING_PATH = os.path.join(_HERE, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])  # built for this interpreter
 if os.environ.get("SP_LIB_SANITIZE", "") == "1":
-    # the copy whose host code carries ASan + UBSan instrumentation (CPU-only boundary tests; the
+    # the copies whose host code carries ASan + UBSan instrumentation (CPU-only boundary tests; the
     # process must run with the matching sanitizer runtime preloaded)
     LIB_PATH = os.path.join(_HERE, "_build", "san", "libshiftattn_san.so")
-
-BINDING_PATH = os.path.join(_HERE, "_binding" + importlib.machinery.EXTENSION_SUFFIXES[0])  # built for this interpreter
+    BINDING_PATH = os.path.join(_HERE, "_build", "san", os.path.basename(BINDING_PATH))
 
 SP_OK = 0
 SP_ERR_NULL = -1

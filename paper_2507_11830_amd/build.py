@@ -4,7 +4,7 @@ argument marshalling into _binding, named for the interpreter it is built for; t
 kernels under bench_kernels/ go into a shared object of their own, libspceilings.so.
 
 ``python -m paper_2507_11830_amd.build --sanitize-host`` builds a second copy of libshiftattn
-whose HOST code is instrumented with AddressSanitizer + UndefinedBehaviorSanitizer
+and of the binding whose HOST code is instrumented with AddressSanitizer + UndefinedBehaviorSanitizer
 (_build/san/libshiftattn_san.so; device code is unchanged) for the CPU-only boundary tests."""
 from __future__ import annotations
 
@@ -26,6 +26,7 @@ LIB = os.path.join(HERE, "libshiftattn.so")
 CEIL_LIB = os.path.join(HERE, "libspceilings.so")
 BINDING_LIB = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 SAN_LIB = os.path.join(OBJ_DIR, "san", "libshiftattn_san.so")
+SAN_BINDING_LIB = os.path.join(OBJ_DIR, "san", os.path.basename(BINDING_LIB))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -149,15 +150,15 @@ def _link(objs, lib: str, extra_flags=()) -> None:
     os.replace(tmp, lib)
 
 
-def _build_binding() -> None:
+def _build_binding(lib: str = BINDING_LIB, compiler: str = "g++", flags=()) -> None:
     """The native argument marshalling (plain host code against the CPython C API)."""
-    tmp = BINDING_LIB + f".tmp{os.getpid()}"
-    r = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+    tmp = lib + f".tmp{os.getpid()}"
+    r = subprocess.run([compiler, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *flags, "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
                         os.path.join(CSRC, "binding.cpp"), "-o", tmp], capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("g++ failed on binding.cpp")
-    os.replace(tmp, BINDING_LIB)
+        raise RuntimeError(f"{compiler} failed on binding.cpp")
+    os.replace(tmp, lib)
 
 
 def build(verbose: bool = False) -> str:
@@ -176,9 +177,11 @@ def build(verbose: bool = False) -> str:
 
 
 def build_sanitized(verbose: bool = False) -> str:
-    """libshiftattn with ASan + UBSan on the host side (argument validation, launch set-up)."""
+    """libshiftattn with ASan + UBSan on the host side (argument validation, launch set-up), and the binding with both."""
     out_dir = os.path.dirname(SAN_LIB)
     os.makedirs(out_dir, exist_ok=True)
+    _build_binding(SAN_BINDING_LIB, os.path.join(os.path.dirname(HIPCC), "..", "llvm", "bin", "clang++"),
+                   [*(f for f in SAN_FLAGS if f != "-Xarch_host"), "-shared-libsan"])
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
         objs = list(ex.map(lambda s_: _compile(s_, out_dir, SAN_FLAGS, product=False), srcs))

@@ -51,3 +51,22 @@ def test_boundary_host_code_under_asan_ubsan():
                ["tests/test_boundary.py", "-k",
                 "argument_validation or tuning_keys or workspace_size or hint_validation or per_thread or status_strings"])
     assert " passed" in out
+
+
+def test_native_marshalling_under_asan_ubsan():
+    """The sanitized build is a package of its own: its binding is built with it, and is the one that is loaded."""
+    from paper_2507_11830_amd import build as b
+
+    rt = subprocess.check_output([os.path.join(os.path.dirname(b.HIPCC), "..", "llvm", "bin", "clang"),
+                                  "--print-file-name=libclang_rt.asan-x86_64.so"], text=True).strip()
+    if not os.path.isabs(rt) or not os.path.exists(rt):
+        pytest.skip("clang's ASan runtime is not installed")
+    if os.path.exists(b.SAN_BINDING_LIB):
+        os.remove(b.SAN_BINDING_LIB)
+    b.build_sanitized()
+    env = {"SP_LIB_SANITIZE": "1", "LD_PRELOAD": _preload(rt)}
+    loaded = subprocess.run([sys.executable, "-c", "import paper_2507_11830_amd as sp; sp.lib(); print(sp.BINDING_PATH)"], cwd=ROOT,
+                            env={**os.environ, **env, "ASAN_OPTIONS": "detect_leaks=0"}, capture_output=True, text=True, timeout=300)
+    assert loaded.stdout.strip() == b.SAN_BINDING_LIB, loaded.stderr[-3000:]
+    out = _run(env, ["tests/test_binding.py"])
+    assert " passed" in out
