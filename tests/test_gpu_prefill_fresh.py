@@ -155,3 +155,12 @@ def test_new_rows_off_a_16_byte_boundary(which, launches):
     lens = np.full(2, 300)
     chunk_step(custom_workload(f"fresh-moved-{which}", lens, 0 * lens, 8, 1, 128, "prefill", seed=13), launches=launches,
                buffers=lambda k, v, out: (moved(k) if which == "k" else k, moved(v) if which == "v" else v, out))
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,batch,n,threads", [
+    (4, 4, 64, 2, 200, 512), (4, 4, 64, 1, 129, 512), (4, 4, 64, 12, 700, 256),  # 128 tokens a tile, 8 chunks each
+    (4, 2, 128, 2, 200, 512), (4, 2, 128, 1, 65, 512),                           # 64 tokens, 16 chunks
+])
+def test_tiles_with_as_many_new_chunks_as_threads_move(Hq, Hkv, d, batch, n, threads):
+    lens = np.full(batch, n)
+    chunk_step(custom_workload(f"fresh-full-{Hq}-{Hkv}-{d}-{n}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=n), launches=[(threads, 1, 1)])
