@@ -6,12 +6,15 @@
 // against 224 softmax instructions (1200) per SIMD, 64 keys and 256 columns; an issue probe of both takes 1497 cycles.  The
 // two-group kernel takes 2075: one wave's softmax is a serial stream of 112 instructions at 7 to 8 cycles each next to the other
 // wave's MFMAs, and at every change of phase both wait.  Here a wave interleaves its own multiplications and softmax (QK^T of one
-// 32-key block and PV of another around the exponentials of a third), needs 160 registers, and so three waves share a SIMD; as they
-// belong to different workgroups, one wave's barriers and dependent steps are covered by the others: 1650 cycles for three workgroups'
-// tiles of 128 columns, i.e. 1100 per 256 columns, at 1.5 instead of 1.8 GHz (power).
+// 32-key block and PV of another around the exponentials of a third), needs 166 registers, and so three waves share a SIMD; as they
+// belong to different workgroups, one wave's barriers and dependent steps are covered by the others: 1880 cycles (counters, 2 x 9001..16384
+// tokens: 1.30 M cycles that a CU is busy, 692 units of 64 keys and 256 columns).  Bound: instruction issue.  In 78 % of the busy cycles a
+// SIMD issues a VALU or MFMA instruction (271 VALU per unit), the matrix pipe is busy in 54 %, the waves wait for memory or a barrier in
+// 15 %; the launch takes 1.37 to 1.42 M cycles at 1.6 to 1.8 GHz.
 // Measured (two-group kernel with 256 columns -> here): 2 sequences of 9001..16384 tokens at 16q/2kv 802 -> 758 us (972 TFLOP/s),
 // 4 x 1500 29.4 -> 26.8, 2 x 2500 42.0 -> 37.5, 8 x 1200 41.6 -> 37.2, 4 x 3000 at 12q/3kv 75.0 -> 67.8, 40 chunks of 400 on up to 1300
-// keys 65.1 -> 57.7; 6 x 600..900, most of it rows of few keys (the block by block part below), 20.5 -> 21.3.  Smaller grids stay
+// keys 65.1 -> 57.7; 6 x 600..900 24.7 (halves) -> 20.9.  Rows of few keys, which take the block by block part below, are the least:
+// 17 chunks of 422 on up to 595 keys 31.9 -> 32.9, 24 x 320..527 at 12q/3kv 32.3 -> 33.0.  Smaller grids stay
 // with 128 columns on two wave groups: one such workgroup alone on a CU takes half as long per tile as this one (1 x 2000 tokens 20.6 us, here 25.7).
 // Tried on the way: the same loop with eight waves and 256 columns, two waves per SIMD and one barrier for all (2250
 // cycles; 797 -> 834 us on 2 x 16k tokens), with 64-key blocks (1950 cycles, 773 us); at head_dim 128, where two such waves share a SIMD, 2250

@@ -48,7 +48,8 @@ __device__ __forceinline__ void sgb_steady() {  // MFMAs [I, NE) of a sequence o
 // scale * log2(e) into the resident Q operand and anchors the running max at 0 where the first
 // tile allows it, so that the common softmax pass is exp2, add and half a convert per score (2.5
 // VALU instructions instead of 3.5) — no change in time at head_dim 128, 9 % faster at head_dim
-// 64, at the price of a score error that grows with the score; -DSP_PREFILL_BARRIER_IN_SEQ puts the
+// 64 while this kernel served its whole tiles (those are prefill_solo.h's now; here head_dim 64 is the halved, cut and mixed forms),
+// at the price of a score error that grows with the score; -DSP_PREFILL_BARRIER_IN_SEQ puts the
 // second group's barrier before the last four MFMAs of its matrix phase, so that the first
 // group's operand reads after the barrier run behind them — no change in time either.
 // -DSP_PREFILL_TRACE makes launches that do not use the workspace otherwise (no key-range pieces,
@@ -317,7 +318,8 @@ __device__ __forceinline__ bool take_item(const PrefillArgs &a, int cols_shift, 
   unsigned lid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), bx = blockIdx.x, by = blockIdx.y;
   if constexpr (SNAKE) {
     // Several workgroups are resident on a CU: each round of 256 gives every CU one.  The second round goes from the lightest of
-    // its items up, so that no CU has the heaviest item of both.
+    // its items up, so that no CU has the heaviest item of both (head_dim 64, without and with: 4 x 1500 tokens at 16q/2kv 30.7 and
+    // 28.8 us, 4 x 3000 at 12q/3kv 71.5 and 69.2, 8 x 1200 38.6 and 39.0; more rounds even themselves out, 2 x 16k 774 and 775).
     if (lid >= 256 && lid < 512) {
       const unsigned xcd = lid & 7, p = (lid >> 3) - 32, total = gridDim.x * gridDim.y * gridDim.z;
       const unsigned n = ((total < 512 ? total : 512) - 256 - xcd + 7) >> 3;  // this XCD's of the round
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   const bool precise_wg = ctx + tok0 < kPreciseKeys;  // group-uniform
   // The scaled-Q form (measurement switch): 2.5 instead of 3.5 VALU instructions per score.  At
   // head_dim 64, where halving the MFMAs per score leaves the softmax phase longer than the other
-  // wave's matrix phase, it is 9 % faster; at head_dim 128 it changes nothing.  It is not the
+  // wave's matrix phase, it was 9 % faster on whole tiles (prefill_solo.h's now); at head_dim 128 it changes nothing.  It is not the
   // product form at either: Q * scale * log2(e) is rounded to bf16 again, so the error of a score
   // grows with the score (relative 2^-9 per term), which is invisible on unit-variance inputs and
   // several per cent of a weight once scores reach the tens — the product keeps Q's products exact.
@@ -774,6 +776,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
     return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most - 1) * page_bytes;
   };
   const unsigned wave_dst = (unsigned)(wq * (NIW * 1024));
+  // M0 stays what the first instruction of a page sets it to until the page's last: between these statements nothing else may write
+  // it, and the build refuses a listing in which anything does.
   auto dma_emit = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
     static_assert(NIW <= 4, "an offset field holds up to 4095");
     if (j == 0) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(pb));
