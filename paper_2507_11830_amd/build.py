@@ -114,16 +114,25 @@ def _check_loop_spills(src: str, asm: str) -> None:
                                "the register allocation moved, look at the listing")
 
 
+def _source_text(src: str) -> str:
+    """A source and the headers of csrc/ that it includes, theirs as well: kernels may live in a shared header."""
+    seen, todo, text = set(), [src], ""
+    while todo:
+        path = todo.pop()
+        if path in seen or not os.path.exists(path):
+            continue
+        seen.add(path)
+        with open(path) as f:
+            part = f.read()
+        text += part
+        todo += [os.path.join(CSRC, inc) for inc in re.findall(r'#include "(\w+\.h)"', part)]
+    return text
+
+
 def _compile(src: str, obj_dir: str = OBJ_DIR, extra_flags=(), product: bool = True) -> str:
     base = os.path.basename(src).replace(".hip", "")
     obj = os.path.join(obj_dir, base + ".o")
-    with open(src) as f:
-        text = f.read()
-    for inc in re.findall(r'#include "(\w+\.h)"', text):  # kernels may live in a shared header
-        if os.path.exists(os.path.join(CSRC, inc)):
-            with open(os.path.join(CSRC, inc)) as f:
-                text += f.read()
-    uses_lds_dma = "global_load_lds" in text
+    uses_lds_dma = "global_load_lds" in _source_text(src)
     extra = ["-save-temps=obj"] if uses_lds_dma else []
     r = subprocess.run([HIPCC, *FLAGS, *extra_flags, *extra, "-c", src, "-o", obj], capture_output=True, text=True)
     if r.returncode != 0:

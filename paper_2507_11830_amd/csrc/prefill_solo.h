@@ -98,12 +98,8 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
   auto lane_off = [&](bool is_v, int j, int rip_lim, int row_stride) __attribute__((always_inline)) {  // instruction j of a page: this lane's source offset
     int ln = lane;
     if constexpr (FRESH) asm volatile("" : "+v"(ln));  // not kept in registers over the tile loop
-    const int dq = ln >> 4, dslot = ln & 15;
-    const int lp = 4 * j + dq;  // line inside the page
-    const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
-    const int rip = 2 * lp + (cl >> 3);
-    const int chunk = cl & 7;
-    return (unsigned)((FRESH ? __mul24(min(rip, rip_lim), row_stride) : min(rip, rip_lim) * row_stride) + chunk * 16 - 1024 * j + BIAS);
+    const PageChunk c = page_chunk<D>(is_v, j, ln);
+    return (unsigned)((FRESH ? __mul24(min(c.row, rip_lim), row_stride) : min(c.row, rip_lim) * row_stride) + c.chunk * 16 - 1024 * j + BIAS);
   };
   const int new_stride = a.Hkv * ROWB, first_stride = FRESH && new_tile == 0 ? new_stride : ROWB, last_stride = FRESH && new_tile < T ? new_stride : ROWB;
   unsigned koff[NIW], voff[NIW];
@@ -161,11 +157,7 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     else n = min(max(__builtin_amdgcn_readfirstlane(pg), 0), a.num_pages - 1);
     return (size_t)(unsigned)n * page_bytes;
   };
-  auto dma = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
-    static_assert(NIW == 2, "two instructions per page");
-    if (j == 0) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(pb));
-    else asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(off), "s"(pb));
-  };
+  static_assert(NIW == 2, "two instructions per page");
   const unsigned wave_dst = (unsigned)(w * (NIW * 1024));
   // Every load of this wave has landed; then all waves'.  Not __syncthreads: that would also wait for the operands of the next
   // period that are on their way from LDS (their slot is not written before the period after).  The clobber keeps the
@@ -269,12 +261,12 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     const size_t pos0 = page_pos(0, pg0);
     pos_v = page_pos(1, pg1);
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) dma(kpool + pos0, wave_dst, koff[j], j);
+    for (int j = 0; j < NIW; ++j) page_load(kpool + pos0, wave_dst, koff[j], j);
     clamp_k(1);
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) dma(kpool + pos_v, TBYTES + wave_dst, koff[j], j);
+    for (int j = 0; j < NIW; ++j) page_load(kpool + pos_v, TBYTES + wave_dst, koff[j], j);
 #pragma unroll
-    for (int j = 0; j < NIW; ++j) dma(vpool + pos0, VBASE + wave_dst, voff[j], j);
+    for (int j = 0; j < NIW; ++j) page_load(vpool + pos0, VBASE + wave_dst, voff[j], j);
     clamp_k(2);
     clamp_v(1);
     TileRows<D, kSoloThreads> rows;
@@ -304,12 +296,12 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
           const size_t pos = page_pos(t + 2, pg);
           const int to = kslot == 0 ? 2 : kslot - 1;
 #pragma unroll
-          for (int j = 0; j < NIW; ++j) dma(kpool + pos, (unsigned)(to * TBYTES) + wave_dst, koff[j], j);
+          for (int j = 0; j < NIW; ++j) page_load(kpool + pos, (unsigned)(to * TBYTES) + wave_dst, koff[j], j);
           pos_w = pos;
         }
         const unsigned to = (unsigned)(VBASE + (1 - vslot) * TBYTES) + wave_dst;
 #pragma unroll
-        for (int j = 0; j < NIW; ++j) dma(vpool + pos_v, to, voff[j], j);
+        for (int j = 0; j < NIW; ++j) page_load(vpool + pos_v, to, voff[j], j);
         pos_v = pos_w;
         pg = page_of(t + 3);
         clamp_k(t + 3);
@@ -415,7 +407,7 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
     if (T > 1) {
       pos_w = page_pos(2, pg);
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) dma(kpool + pos_w, 2 * TBYTES + wave_dst, koff[j], j);
+      for (int j = 0; j < NIW; ++j) page_load(kpool + pos_w, 2 * TBYTES + wave_dst, koff[j], j);
       pg = page_of(3);
       clamp_k(3);
       {
@@ -437,12 +429,12 @@ __global__ __launch_bounds__(kSoloThreads, 3) void solo_prefill_kernel(Args a) {
         const unsigned dk = k_next(), dv = v_next();
         bf16x8 nx[PFD];
         block(I0{}, Both{}, base - 32, [&](int i) __attribute__((always_inline)) {
-          if (i % 2 && i / 2 < NIW) dma(kb, kto, koff[i / 2], i / 2);
+          if (i % 2 && i / 2 < NIW) page_load(kb, kto, koff[i / 2], i / 2);
         }, [&](int i) __attribute__((always_inline)) { nx[i] = k_op(1, i); });
 #pragma unroll
         for (int i = 0; i < PFD; ++i) ops[i] = nx[i];
         block(I1{}, Both{}, base, [&](int i) __attribute__((always_inline)) {
-          if (i % 2 && i / 2 < NIW) dma(vb, vto, voff[i / 2], i / 2);
+          if (i % 2 && i / 2 < NIW) page_load(vb, vto, voff[i / 2], i / 2);
           if (i == NK - 1) {  // the last K operand of the tile has been read: on to the next slot
 #pragma unroll
             for (int s = 0; s < NK; ++s) kadr[s] += dk;

@@ -377,6 +377,29 @@ __device__ __forceinline__ bool take_item(const PrefillArgs &a, int cols_shift, 
   return o->q_len > a.route_cap;  // mixed batch: the split kernel serves the others
 }
 
+// What lane l of load instruction j of a page brings in: the 16-byte chunk `chunk` of the page's row `row`, as the swizzle of K's, or V's,
+// tile has it.
+struct PageChunk {
+  int row, chunk;
+};
+template <int D>
+__device__ __forceinline__ PageChunk page_chunk(bool is_v, int j, int l) {
+  using Z = SwzTile<D>;
+  const int lp = 4 * j + (l >> 4);  // line inside the page
+  const int cl = (l & 15) ^ (is_v ? Z::gv(lp) : Z::gk(lp));
+  return D == 128 ? PageChunk{lp, cl} : PageChunk{2 * lp + (cl >> 3), cl & 7};
+}
+
+// Instruction j of a page load: 1 KiB of the page whose block begins at pb to LDS at dst, both 1024 j further on; off: the lane's rest.
+// M0 stays what the first instruction of a page sets it to until the page's last: between these statements nothing else may write
+// it, and the build refuses a listing in which anything does.
+__device__ __forceinline__ void page_load(const char *pb, unsigned dst, unsigned off, int j) {
+  if (j == 0) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(pb));
+  else if (j == 1) asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(off), "s"(pb));
+  else if (j == 2) asm volatile("global_load_lds_dwordx4 %0, %1 offset:2048" ::"v"(off), "s"(pb));
+  else asm volatile("global_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(off), "s"(pb));
+}
+
 // FRESH, a sequence with cached tokens: appends what the call appends to the pages that the workgroup reads from the pool
 // (fresh_plan.h), for one KV head.  set: kPageBits / 8 bytes of LDS.  Off the common path (a prompt has no cached tokens); bound
 // by its dependent round trips, so all that depends on nothing is requested first.  Measured against an append of its own in front
@@ -698,12 +721,8 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   auto stream_tile = [&](int g, int i) __attribute__((always_inline)) { return t_begin + (SPLIT ? 2 * i + g : i); };  // local tile i of stream g
   constexpr int VBIAS = (NIW - 1) * 1024;  // keeps the V offsets of clamped rows from going below zero
   auto lane_off = [&](bool is_v, int j, int rip_lim, int row_stride, int l) __attribute__((always_inline)) {  // instruction j of a page load: lane l's source offset
-    const int dq = l >> 4, dslot = l & 15;
-    const int lp = 4 * j + dq;  // line inside the page
-    const int cl = dslot ^ (is_v ? Z::gv(lp) : Z::gk(lp));
-    const int rip = D == 128 ? lp : 2 * lp + (cl >> 3);
-    const int chunk = D == 128 ? cl : (cl & 7);
-    return (unsigned)((FRESH ? __mul24(min(rip, rip_lim), row_stride) : min(rip, rip_lim) * row_stride) + chunk * 16 - 1024 * j + (is_v || FRESH ? VBIAS : 0));
+    const PageChunk c = page_chunk<D>(is_v, j, l);
+    return (unsigned)((FRESH ? __mul24(min(c.row, rip_lim), row_stride) : min(c.row, rip_lim) * row_stride) + c.chunk * 16 - 1024 * j + (is_v || FRESH ? VBIAS : 0));
   };
   constexpr int NK = FRESH ? NSTREAM : 1;
   unsigned koff[NK][NIW], voff[NSTREAM][NIW];  // of every stream; K's are the same for all unless redirected
@@ -743,9 +762,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   auto new_offset = [&](bool is_v, int j) __attribute__((always_inline)) {
     int l = lane;
     if constexpr (FRESH) asm volatile("" : "+v"(l));
-    const int lp = 4 * j + (l >> 4);
-    const int cl = (l & 15) ^ (is_v ? Z::gv(lp) : Z::gk(lp));
-    return (unsigned)__mul24(D == 128 ? lp : 2 * lp + (cl >> 3), new_stride - ROWB);
+    return (unsigned)__mul24(page_chunk<D>(is_v, j, l).row, new_stride - ROWB);
   };
   auto new_offsets_v = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
@@ -782,15 +799,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
     return (size_t)(unsigned)min(max(__builtin_amdgcn_readfirstlane(pg), 0), most - 1) * page_bytes;
   };
   const unsigned wave_dst = (unsigned)(wq * (NIW * 1024));
-  // M0 stays what the first instruction of a page sets it to until the page's last: between these statements nothing else may write
-  // it, and the build refuses a listing in which anything does.
-  auto dma_emit = [&](const char *pb, unsigned dst, unsigned off, int j) __attribute__((always_inline)) {  // instruction j of a page whose block begins at pb
-    static_assert(NIW <= 4, "an offset field holds up to 4095");
-    if (j == 0) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(pb));
-    else if (j == 1) asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(off), "s"(pb));
-    else if (j == 2) asm volatile("global_load_lds_dwordx4 %0, %1 offset:2048" ::"v"(off), "s"(pb));
-    else asm volatile("global_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(off), "s"(pb));
-  };
+  static_assert(NIW <= 4, "an offset field holds up to 4095");
   using std::false_type;
   using std::integral_constant;
   using std::true_type;
@@ -819,7 +828,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
   };
   auto issue_emit = [&](int n, int par) __attribute__((always_inline)) {  // n-th instruction of the period, n < NLD: streams and matrices in turn
     const int j = n % NIW, u = n / NIW, g = u % NSTREAM, m = u / NSTREAM;
-    dma_emit(ld[g][m], slot_dst(g, m, m ? par : 1 - par), m ? voff[g][j] : koff[FRESH ? g : 0][j], j);
+    page_load(ld[g][m], slot_dst(g, m, m ? par : 1 - par), m ? voff[g][j] : koff[FRESH ? g : 0][j], j);
   };
   auto wait_loads = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };  // vmcnt(0) only
 
@@ -1156,9 +1165,9 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
       clamp_v(g, stream_tile(g, 0), lane);
       clamp_k(g, stream_tile(g, 0), lane);
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(kpool + pos0[g], slot_dst(g, 0, 0), koff[FRESH ? g : 0][j], j);
+      for (int j = 0; j < NIW; ++j) page_load(kpool + pos0[g], slot_dst(g, 0, 0), koff[FRESH ? g : 0][j], j);
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(vpool + pos0[g], slot_dst(g, 1, 0), voff[g][j], j);
+      for (int j = 0; j < NIW; ++j) page_load(vpool + pos0[g], slot_dst(g, 1, 0), voff[g][j], j);
       const char *k1 = kpool;
       if constexpr (FRESH) {
         if (__builtin_expect(turn1, 0)) {
@@ -1168,7 +1177,7 @@ __global__ __launch_bounds__(512, 2) void prefill_kernel(Args a) {
       }
       clamp_k(g, stream_tile(g, 1), lane);
 #pragma unroll
-      for (int j = 0; j < NIW; ++j) dma_emit(k1 + pos_v[g], slot_dst(g, 0, 1), koff[FRESH ? g : 0][j], j);
+      for (int j = 0; j < NIW; ++j) page_load(k1 + pos_v[g], slot_dst(g, 0, 1), koff[FRESH ? g : 0][j], j);
       if (__builtin_expect(turn1, 0)) new_offsets_v(g);
       if (__builtin_expect(turn2, 0)) new_offsets_k(g);
       clamp_v(g, stream_tile(g, 1), lane);

@@ -249,3 +249,14 @@ def test_prefill_loops_hold_no_spill_code(built_lib):
     assert len(counts) == 6
     for kern, n in counts.items():
         assert n <= (0 if "ELb0ELb0E" in kern else 8), (kern, n)
+
+
+def test_listing_checks_see_loads_in_nested_headers(tmp_path, monkeypatch):
+    """The build checks the listing of every source that loads straight to LDS, also where only a header's header says so."""
+    from paper_2507_11830_amd import build as b
+
+    monkeypatch.setattr(b, "CSRC", str(tmp_path))
+    (tmp_path / "inner.h").write_text('#include "outer.h"\n// global_load_lds\n')
+    (tmp_path / "outer.h").write_text('#include "inner.h"\n#include "absent.h"\n')
+    (tmp_path / "k.hip").write_text('#include "outer.h"\n')
+    assert "global_load_lds" in b._source_text(str(tmp_path / "k.hip"))
