@@ -16,6 +16,7 @@ namespace sp {
 template <int D>
 static int launch_fresh_d(const FreshArgs &a, bool split, int batch, int max_q_len, hipStream_t stream) {
   constexpr size_t smem = kPrefillSmem<D>;
+  static_assert(kPageBits / 8 <= smem && kPageBits / 8 <= kSoloSmem, "the set of pages lies where the tiles will");
   static bool set[2] = {false, false};
   if (split) return launch_cfg(prefill_kernel<D, KVT, PFD, true, false, 0, FreshArgs>, &set[0], 2 * smem, 128, a, batch, max_q_len, stream);
   if constexpr (D == 64) return launch_cfg(solo_prefill_kernel<FreshArgs>, &set[1], kSoloSmem, kSoloCols, a, batch, max_q_len, stream, kSoloThreads, kSoloLayers);

@@ -164,3 +164,14 @@ def test_new_rows_off_a_16_byte_boundary(which, launches):
 def test_tiles_with_as_many_new_chunks_as_threads_move(Hq, Hkv, d, batch, n, threads):
     lens = np.full(batch, n)
     chunk_step(custom_workload(f"fresh-full-{Hq}-{Hkv}-{d}-{n}", lens, 0 * lens, Hq, Hkv, d, "prefill", seed=n), launches=[(threads, 1, 1)])
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,threads", [(2, 1, 128, 512), (2, 1, 64, 512), (8, 1, 128, 512), (16, 2, 64, 256)])
+def test_prefixes_on_more_sequences_than_one_look_covers(Hq, Hkv, d, threads):
+    """More (sequence, page) pairs than threads: every prompt has two chunks on it, one in front of it and one behind it in the batch."""
+    new, ctx = np.array([40, 150, 90] * 14), np.array([96, 0, 112] * 14)
+    w = custom_workload(f"fresh-many-{Hq}-{Hkv}-{d}", new + ctx, ctx, Hq, Hkv, d, "prefill", seed=37)
+    for p in range(14):
+        for reader, prompt in ((3 * p, 3 * (13 - p) + 1), (3 * p + 2, 3 * (13 - p) + 1)):
+            w.block_table[reader, : ctx[reader] // 16] = w.block_table[prompt, : ctx[reader] // 16]
+    chunk_step(w, max_q=210, max_kv=210, total=210 * len(new), launches=[(threads, 1, 1)])
